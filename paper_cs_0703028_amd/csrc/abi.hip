@@ -696,12 +696,16 @@ rt_status rt_set_line_tolerance(rt_ctx c, double eps) {
 }
 
 // The FP64-derived cell factors (c->cells: G, beta, theta, lam2, P and the
-// further gases' G), formed once per grid and line list.
+// further gases' G) and the plain march's Planck cubics, formed once per grid
+// and line list.
 static rt_status ensure_cells(rt_ctx c) {
   if (c->cells_valid) return RT_OK;
   RT_HIP(c, rt::launch_cell_params(c));
   for (int g = 1; g < rt::kMaxGases; ++g)
     if (c->gas[g - 1].active) RT_HIP(c, rt::launch_gas_factor(c, g));
+  c->planck_cubic = rt::planck_cubic_fits(c->T_min, c->T_max, c->nu0, c->dnu, c->n_nu);
+  if (c->planck_cubic)
+    RT_HIP(c, rt::launch_planck_cubics(c, c->cells.theta, c->n_cells, c->d_poly, c->stream));
   c->cells_valid = true;
   return RT_OK;
 }
@@ -737,10 +741,17 @@ rt_status rt_compute_kappa(rt_ctx c, int mode, float* kappa_dev, float* planck_d
     return fail(c, RT_EINVAL, "rt_compute_kappa: buffers must be 16-byte aligned");
   if (rt_status s = set_device(c)) return s;
   c->have_kappa = false;
-  if (c->bwall_len < ld) {
+  // the walls' row and the march's Planck cubics in one allocation (here, so
+  // that rt_trace_rays_noalloc finds them)
+  const int64_t poly = c->n_cells * rt::plain_chunks(c->n_nu);
+  if (c->bwall_len < ld || c->poly_cap < poly) {
     dev_free(c->d_bwall);
-    RT_HIP(c, dev_alloc(&c->d_bwall, (size_t)ld));
+    c->bwall_len = c->poly_cap = 0;
+    c->cells_valid = false;  // the cubics are formed with the cell factors
+    RT_HIP(c, dev_alloc(&c->d_bwall, (size_t)(ld + 4 * poly)));
+    c->d_poly = reinterpret_cast<float4*>(c->d_bwall + ld);  // ld: a multiple of 1536
     c->bwall_len = ld;
+    c->poly_cap = poly;
   }
   if (adaptive) {
     const int64_t runs = (c->n_cells + RT_ADAPTIVE_GROUP - 1) / RT_ADAPTIVE_GROUP;
@@ -821,7 +832,7 @@ static rt_status trace_with(rt_ctx c, const rt::RayScratch& rs, uint64_t seed, u
     if (rt_status s = record_begin(c, c->trace_events)) return s;
   // A launch adds at most (rays x chunks) terms to one accumulator word
   // (a ray crosses a cell once); the words are normalised after every launch.
-  const int64_t n_chunks = std::max<int64_t>(1, c->ld / rt::kChunk);
+  const int64_t n_chunks = f64 ? std::max<int64_t>(1, c->ld / rt::kChunk) : rt::plain_chunks(c->n_nu);
   const int64_t per_launch =
       std::max<int64_t>(1, std::min<int64_t>(rs.cap, rt::kAccMaxTerms / n_chunks));
   for (uint64_t off = 0; off < count; off += (uint64_t)per_launch) {

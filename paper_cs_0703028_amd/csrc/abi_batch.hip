@@ -103,13 +103,13 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   pl.cases.assign(n_cases, BatchCase());
   int64_t cell_off = 0, seg_off = 0, ray_off = 0, blk_off = 0, max_cells = 0;
   double evals = 0;
-  double T_min = INFINITY, T_max = 0;
   for (int k = 0; k < n_cases; ++k) {
     const rt_case& q = cases[k];
     BatchCase& b = pl.cases[k];
     const int64_t nc = (int64_t)q.nx * q.ny * q.nz;
-    T_min = std::min(T_min, *std::min_element(q.T_K, q.T_K + nc));
-    T_max = std::max(T_max, *std::max_element(q.T_K, q.T_K + nc));
+    const auto T_range = std::minmax_element(q.T_K, q.T_K + nc);
+    b.cubic = planck_cubic_fits(*T_range.first, *T_range.second, c->nu0, c->dnu, c->n_nu) ? 1 : 0;
+    (b.cubic ? pl.any_cubic : pl.any_general) = true;
     b.nx = q.nx; b.ny = q.ny; b.nz = q.nz;
     b.max_segs = q.nx + q.ny + q.nz;
     b.n_cells = (int64_t)q.nx * q.ny * q.nz;
@@ -137,8 +137,8 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
     cell_off += b.n_cells;
     seg_off += b.n_rays * b.max_segs;
     ray_off += b.n_rays;
-    // march blocks of 4 rays, an eighth per XCD, for each kChunk part
-    blk_off += (int64_t)(t.chunk_points / kChunk) * (((b.n_rays + 3) / 4 + 7) / 8);
+    // march blocks of 4 rays, an eighth per XCD
+    blk_off += ((b.n_rays + 3) / 4 + 7) / 8;
     max_cells = std::max(max_cells, b.n_cells);
     evals += c->line_evals_per_cell * (double)b.n_cells;
   }
@@ -148,7 +148,6 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   if (pl.chunked && 8 * blk_off > 0x7fffffffLL)
     return bfail(c, RT_EINVAL, "rt_batch: too many rays for one chunked march launch "
                                "(use RT_BATCH_PERSISTENT or fewer chunk_points)");
-  pl.planck_quad = planck_needs_quadratic(T_min, T_max, c->nu0, c->dnu, c->n_nu);
   pl.max_cells = max_cells;
   pl.line_evals = limit_points > 0 ? 0.0 : evals;
   pl.slab_stride = (pl.chunked ? cell_off : max_cells) * t.chunk_points;
@@ -219,6 +218,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   int64_t o_abs = take(nc * 8), o_emi = take(nc * 8);
   int64_t o_acc = take(((nc + (int64_t)n_cases * kCaseBalRows) * kAccRow + 1) * 8), o_bal = take((int64_t)n_cases * 4 * 8);
   int64_t o_bw = take((int64_t)n_cases * pl.bwall_ld * 4);
+  int64_t o_poly = take(nc * plain_chunks(c->n_nu) * 16);
   int64_t o_segs = take(seg_off * 8), o_cnt = take(ray_off * 4);
   int64_t o_keys = take(ray_off * 4), o_perm = take(ray_off * 4);
   int64_t o_hist = take((int64_t)n_cases * kOrderBuckets * 4);
@@ -242,6 +242,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   pl.d_acc = reinterpret_cast<unsigned long long*>(o_acc);
   pl.d_balance = reinterpret_cast<double*>(o_bal);
   pl.d_bwall = reinterpret_cast<float*>(o_bw);
+  pl.d_poly = reinterpret_cast<float4*>(o_poly);
   pl.d_segs = reinterpret_cast<int2*>(o_segs);
   pl.d_counts = reinterpret_cast<int32_t*>(o_cnt);
   pl.d_keys = reinterpret_cast<uint32_t*>(o_keys);
@@ -263,7 +264,7 @@ void carve(BatchPlan& pl, void* ws) {
   rebase(pl.cells.G, b); rebase(pl.cells.beta, b); rebase(pl.cells.theta, b);
   rebase(pl.cells.lam2, b); rebase(pl.cells.P, b);
   rebase(pl.d_abs, b); rebase(pl.d_emi, b); rebase(pl.d_acc, b); rebase(pl.d_balance, b);
-  rebase(pl.d_bwall, b); rebase(pl.d_segs, b); rebase(pl.d_counts, b); rebase(pl.d_slabs, b);
+  rebase(pl.d_bwall, b); rebase(pl.d_poly, b); rebase(pl.d_segs, b); rebase(pl.d_counts, b); rebase(pl.d_slabs, b);
   rebase(pl.d_keys, b); rebase(pl.d_perm, b); rebase(pl.d_hist, b);
   rebase(pl.d_counters, b); rebase(pl.d_stages, b); rebase(pl.d_cases, b);
 }

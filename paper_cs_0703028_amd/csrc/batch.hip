@@ -33,6 +33,8 @@
 #include "device_common.h"
 #include "batch_plan.h"
 
+#include <algorithm>
+
 namespace rt {
 namespace {
 
@@ -58,6 +60,8 @@ struct BatchArgs {
   const uint32_t* perm;  // per case: slot -> ray index (coherent order)
   const float* bwall;  // [case][bwall_ld]
   int64_t bwall_ld;
+  const float4* poly;  // Planck cubics, packed over the cases
+  int64_t n_poly;
   unsigned long long* acc;  // accumulator rows (see BatchPlan::d_acc)
   unsigned* ovf;
   double nu0, dnu, c1;
@@ -88,7 +92,6 @@ __device__ __forceinline__ bool wait_count(const unsigned* p, unsigned target, u
   return true;
 }
 
-template <bool QUAD>
 // Five wavefronts per SIMD (at most 102 VGPRs): the march items wait on memory
 // and need the wavefronts to hide it.  Left alone the combined code paths take
 // 142 VGPRs and three wavefronts; at five, 33 VGPRs go to scratch, a few
@@ -99,7 +102,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   // line-sum tiles stage line records here; march items stage their
   // per-segment partial sums (4 wavefronts) in the same memory
   constexpr int kLdsFloats = kLineTile * (4 + 2 * kKappaCells);
-  static_assert(kLdsFloats >= 4 * TallyStage<false>::kEntries, "march staging fits");
+  static_assert(kLdsFloats >= 4 * PlainStage::kEntries, "march staging fits");
   __shared__ float4 lds4[kLdsFloats / 4];
   __shared__ long long s_item;
   __shared__ int s_ok;
@@ -205,6 +208,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     w.ld = a.chunk_points;
     w.col0 = (int64_t)st.chunk * a.chunk_points;
     w.theta = a.C.theta + cs.cell_off;
+    w.poly = a.poly + cs.cell_off * a.n_poly;
+    w.n_poly = a.n_poly;
     w.bwall = a.bwall + (int64_t)st.cas * a.bwall_ld;
     w.nu0 = a.nu0;
     w.dnu = a.dnu;
@@ -215,15 +220,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     w.bal_row0 = w.row0 + cs.n_cells;
     w.bal_mask = kCaseBalRows - 1;
     w.ovf = a.ovf;
-    float* stage = lds + wave * TallyStage<false>::kEntries;
+    float* stage = lds + wave * PlainStage::kEntries;
     const int64_t r0 = local * a.march_rays;
     const int64_t r1 = min(r0 + a.march_rays, cs.n_rays);
     for (int64_t r = r0 + wave; r < r1; r += 4) {
       const int2* sg = a.segs + cs.seg_off + r * cs.max_segs;
       const int ns = a.counts[cs.ray_off + r];
-      for (int sub = 0; sub < a.chunk_points / kChunk; ++sub) {
-        const int64_t j = w.col0 + (int64_t)sub * kChunk + lane * kQ;
-        march_wave<false, false, QUAD>(w, sg, ns, j, lane, nullptr, stage, r);
+      for (int64_t j0 = w.col0; j0 < min(w.col0 + a.chunk_points, (int64_t)a.n_nu); j0 += kMarchPoints) {
+        if (cs.cubic) march_plain<false, true, false>(w, sg, ns, j0, lane, nullptr, stage, r);
+        else march_plain<false, false, false>(w, sg, ns, j0, lane, nullptr, stage, r);
       }
     }
     __syncthreads();
@@ -377,6 +382,8 @@ struct ChunkMarchArgs {
   int chunk_points;
   int64_t col0;          // first point of the chunk
   const double* theta;   // packed over the cases
+  const float4* poly;    // Planck cubics, likewise
+  int64_t n_poly;
   const float* bwall;    // [case][bwall_ld]
   int64_t bwall_ld;
   double nu0, dnu, c1;
@@ -397,25 +404,26 @@ __device__ __forceinline__ int case_of_block(const BatchCase* cases, int n_cases
 }
 
 // Chunked mode, march: block = 4 wavefronts = 4 consecutive slots of one
-// case on one kChunk-point part of the chunk.  Workgroups go to the 8 XCDs
-// round-robin (block b runs on XCD b % 8); the rows of 8 blocks (b / 8) run
-// case after case, and within a case each XCD takes a contiguous eighth of
-// its ray blocks, part-major: the single-case kernel's order, so that all
-// XCDs work on one case's slab rows at a time and its working set stays in
-// the last-level cache.  Each wavefront adds to the same accumulator rows as
-// the persistent kernel's march items.
-template <bool QUAD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void chunk_march_kernel(
+// case on one kMarchPoints-point part of the chunk (blockIdx.y).  Workgroups
+// go to the 8 XCDs round-robin (block b runs on XCD b % 8, the grid's x size
+// being a multiple of 8); the rows of 8 blocks (b / 8) run case after case,
+// and within a case each XCD takes a contiguous eighth of its ray blocks: the
+// single-case kernel's order, so that all XCDs work on one case's slab rows
+// at a time and its working set stays in the last-level cache.  Each
+// wavefront adds to the same accumulator rows as the persistent kernel's
+// march items.  CUBIC: takes the cases whose Planck cubics fit, else the
+// others (one launch each, as a plan holds both kinds).
+template <bool CUBIC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void chunk_march_kernel(
     ChunkMarchArgs a) {
-  __shared__ float stage[4][TallyStage<false>::kEntries];
+  __shared__ float stage[4][PlainStage::kEntries];
   const int64_t b = blockIdx.x;
   const int64_t xcd = b & 7, local = b >> 3;
   const int k = case_of_block(a.cases, a.n_cases, local);
   const BatchCase& cs = a.cases[k];
+  if ((cs.cubic != 0) != CUBIC) return;
   const int64_t nb = (cs.n_rays + 3) / 4, rbx = (nb + 7) / 8;
-  const int64_t idx = local - cs.blk_off;
-  const int part = (int)(idx / rbx);
-  const int64_t rb = xcd * rbx + idx % rbx;
+  const int64_t rb = xcd * rbx + (local - cs.blk_off);
   if (rb >= nb) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -427,6 +435,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   w.ld = a.chunk_points;
   w.col0 = a.col0;
   w.theta = a.theta + cs.cell_off;
+  w.poly = a.poly + cs.cell_off * a.n_poly;
+  w.n_poly = a.n_poly;
   w.bwall = a.bwall + (int64_t)k * a.bwall_ld;
   w.nu0 = a.nu0;
   w.dnu = a.dnu;
@@ -437,9 +447,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   w.bal_row0 = w.row0 + cs.n_cells;
   w.bal_mask = kCaseBalRows - 1;
   w.ovf = a.ovf;
-  const int64_t j = a.col0 + (int64_t)part * kChunk + lane * kQ;
-  march_wave<false, false, QUAD>(w, a.segs + cs.seg_off + r * cs.max_segs,
-                                 a.counts[cs.ray_off + r], j, lane, nullptr, stage[wave], r);
+  march_plain<false, CUBIC, true>(w, a.segs + cs.seg_off + r * cs.max_segs,
+                                  a.counts[cs.ray_off + r],
+                                  a.col0 + (int64_t)blockIdx.y * kMarchPoints, lane, nullptr,
+                                  stage[wave], r);
 }
 
 __global__ void fill_u32_kernel(unsigned* p, int64_t n) {
@@ -478,7 +489,10 @@ hipError_t launch_batch_prep(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
   hipLaunchKernelGGL(case_wall_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s,
                      pl.d_cases, pl.n_cases, c->n_nu, pl.bwall_ld, host_pair(c->nu0),
                      host_pair(c->dnu), c1, pl.d_bwall);
-  return hipGetLastError();
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && pl.any_cubic)
+    e = launch_planck_cubics(c, pl.cells.theta, pl.total_cells, pl.d_poly, s);
+  return e;
 }
 
 hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
@@ -528,6 +542,8 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
     m.slab = pl.d_slabs;
     m.chunk_points = cp;
     m.theta = pl.cells.theta;
+    m.poly = pl.d_poly;
+    m.n_poly = plain_chunks(c->n_nu);
     m.bwall = pl.d_bwall;
     m.bwall_ld = pl.bwall_ld;
     m.nu0 = c->nu0;
@@ -566,10 +582,15 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
       if (e != hipSuccess) break;
       m.slab = slab;
       m.col0 = t.col0;
-      if (pl.planck_quad)
-        hipLaunchKernelGGL(chunk_march_kernel<true>, dim3((unsigned)march_blocks), dim3(256), 0, s, m);
-      else
-        hipLaunchKernelGGL(chunk_march_kernel<false>, dim3((unsigned)march_blocks), dim3(256), 0, s, m);
+      // the chunk's parts that hold a point of the spectrum
+      const dim3 mg((unsigned)march_blocks,
+                    (unsigned)plain_chunks(std::min<int64_t>(cp, c->n_nu - t.col0)));
+      // six wavefronts per SIMD: fewer rows compete for L2 (6 cases of 16^3 to
+      // 32^3 cells, 2^15 and 2^16 rays, per launch: 127.1 ms with eight, 124.4
+      // with seven, 122.5 with six, 121.0 with five; dense rays lose below six)
+      const unsigned pad = 10000;
+      if (pl.any_cubic) hipLaunchKernelGGL(chunk_march_kernel<true>, mg, dim3(256), pad, s, m);
+      if (pl.any_general) hipLaunchKernelGGL(chunk_march_kernel<false>, mg, dim3(256), pad, s, m);
       if (two) e = hipEventRecord(ev[1 + pl.n_chunks + ch], s);
     }
     if (e != hipSuccess) return e;
@@ -598,6 +619,8 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
   a.perm = pl.d_perm;
   a.bwall = pl.d_bwall;
   a.bwall_ld = pl.bwall_ld;
+  a.poly = pl.d_poly;
+  a.n_poly = plain_chunks(c->n_nu);
   a.acc = pl.d_acc;
   a.ovf = ovf;
   a.nu0 = c->nu0;
@@ -609,10 +632,7 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
   a.k_done = a.rg_done + pl.n_cases;
   a.m_done = a.k_done + pl.n_pairs;
   a.spin_limit = 1u << 24;
-  if (pl.planck_quad)
-    hipLaunchKernelGGL(batch_kernel<true>, dim3((unsigned)pl.grid_blocks), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(batch_kernel<false>, dim3((unsigned)pl.grid_blocks), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(batch_kernel, dim3((unsigned)pl.grid_blocks), dim3(256), 0, s, a);
   return finish();
 }
 

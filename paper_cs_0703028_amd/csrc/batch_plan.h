@@ -28,6 +28,7 @@ struct BatchCase {
   int nx, ny, nz, max_segs;
   int64_t n_cells, cell_off, n_rays, seg_off, ray_off;
   int64_t blk_off;  // chunked mode: first row of 8 march blocks of the case
+  int cubic;        // the march's Planck cubics fit the case (planck_cubic_fits)
   uint64_t seed;
   double weight, unit_cm;
   float2 theta_wall;  // c2 / T_wall as an FP32 pair (0: cold walls)
@@ -37,7 +38,7 @@ struct BatchPlan {
   rt_batch_tuning tuning;
   bool comp = false;
   bool chunked = true;      // tuning.mode == RT_BATCH_CHUNKED
-  bool planck_quad = true;  // second-order Planck expansion in the march
+  bool any_cubic = false, any_general = false;  // over the cases' `cubic`
   int n_cases = 0, n_chunks = 0, n_pairs = 0, n_stages = 0;
   int64_t total_items = 0, total_cells = 0, total_rays = 0, max_cells = 0;
   int64_t ray_blocks = 0;  // chunked mode: rows of 8 march blocks over all cases
@@ -56,6 +57,7 @@ struct BatchPlan {
   unsigned long long* d_acc = nullptr;
   double *d_abs = nullptr, *d_emi = nullptr, *d_balance = nullptr;
   float* d_bwall = nullptr;
+  float4* d_poly = nullptr;  // Planck cubics, [total_cells][march chunks]
   int2* d_segs = nullptr;
   int32_t* d_counts = nullptr;
   uint32_t* d_keys = nullptr;  // coherent-order key per ray (all cases)

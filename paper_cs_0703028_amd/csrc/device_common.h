@@ -16,7 +16,8 @@ constexpr int kLineTile = 256;
 constexpr int kKappaCells = 8;   // cells per lane in the line sum
 constexpr int kKappaPoints = 2;  // nu points per lane in the line sum
 constexpr int kKappaTilePoints = kKappaThreads * kKappaPoints;
-constexpr int kQ = kChunk / 64;  // contiguous nu points per lane in the march
+constexpr int kQ = kChunk / 64;  // contiguous nu points per lane, precision form's march
+constexpr int kPlainQ = 12;      // the same in the plain form's (kMarchPoints = 64 kPlainQ)
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -555,11 +556,10 @@ __device__ __forceinline__ double dpp_f64(double v) {
 // a = 1 - e^{-tau} for tau >= 0, two accuracy levels.
 //   precision form: degree-5 Taylor polynomial of (1 - e^{-tau})/tau below
 //     tau = 1/4 (truncation < 5e-8), 1 - 2^{-tau log2 e} above (<= 5e-7);
-//   plain form (in march_wave): the same series to tau^3 below tau = 1/32
+//   plain form (march_plain): the same series to tau^3 below tau = 1/32
 //     (truncation < 1.3e-6), written in the exponent argument, and
 //     1 - 2^{-tau log2 e} above (<= 1.5e-6 just above the switch, falling
-//     as 1/tau); the series is skipped by the whole wavefront when no lane
-//     needs it.
+//     as 1/tau).
 // The exponent is folded into base 2 per segment, as the paper's listing
 // folds 1/ln 2 into the per-volume scalar.
 __device__ __forceinline__ float poly5(float tau) {
@@ -570,16 +570,6 @@ __device__ __forceinline__ float poly5(float tau) {
   p = fmaf(tau, p, 1.0f);
   return tau * p;
 }
-
-template <bool F64>
-struct Partial { using T = float; };
-template <>
-struct Partial<true> { using T = double; };
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_pt(float v) { return dpp_f32<CTRL>(v); }
-template <int CTRL>
-__device__ __forceinline__ double dpp_pt(double v) { return dpp_f64<CTRL>(v); }
 
 // ------------------------------------------------------ fixed-point tallies
 // The absorbed and emitted power of every cell, and the entering and escaped
@@ -603,22 +593,21 @@ __device__ __forceinline__ void acc_add(unsigned long long* d, double v, unsigne
     atomicOr(ovf, 1u);
     return;
   }
-  if (v == 0.0) return;
-  int e;
-  const double mant = frexp(v, &e);  // v = mant 2^e, 1/2 <= mant < 1, e <= 80
-  unsigned long long m = (unsigned long long)rint(ldexp(mant, kAccSig));
-  if (m >> kAccSig) {                // rounded up to 2^kAccSig
-    m >>= 1;
-    ++e;
-  }
+  // v = mant 2^e, 1/2 <= mant < 1, e <= 80 (0 gives 0 and adds nothing); the
+  // hardware frexp and 32-bit conversion, without the library's special cases
+  int e = __builtin_amdgcn_frexp_exp(v);
+  unsigned m = (unsigned)rint(ldexp(__builtin_amdgcn_frexp_mant(v), kAccSig));
+  const unsigned up = m >> kAccSig;  // rounded up to 2^kAccSig
+  m >>= up;
+  e += (int)up;
   int p = e - kAccSig - kAccLsb;     // accumulator bit of m's lowest bit
-  if (p < 0) {
-    if (p <= -kAccSig) return;       // wholly below the lowest digit
-    m >>= -p;
+  if (p < 0) {                       // partly or wholly below the lowest digit
+    m = p <= -kAccSig ? 0u : m >> -p;
     p = 0;
   }
-  const int k = p / kAccBits, s = p % kAccBits;
-  const unsigned long long w = m << s;  // below 2^(2 kAccBits): digits k, k + 1
+  if (m == 0) return;
+  const unsigned k = (unsigned)p / kAccBits, s = (unsigned)p % kAccBits;
+  const unsigned long long w = (unsigned long long)m << s;  // below 2^(2 kAccBits): digits k, k + 1
   atomicAdd(d + k, w & kAccMask);
   const unsigned long long hi = w >> kAccBits;
   if (hi) atomicAdd(d + k + 1, hi);
@@ -645,28 +634,25 @@ __device__ __forceinline__ double acc_value(const unsigned long long* d) {
 }
 
 // --------------------------------------------------------------- the march
-// One wavefront, one ray, one chunk of kChunk points: Eq. (3) cell after cell
-// for every point, I <- I - (I - B) a with a = 1 - e^{-tau}.  Each lane owns
-// kQ contiguous points starting at the absolute index j.  Per segment every
+// One wavefront, one ray, one spectral chunk: Eq. (3) cell after cell for
+// every point, I <- I - (I - B) a with a = 1 - e^{-tau}.  Per segment every
 // lane's partial sums of the chunk's absorbed (sum I a) and emitted (sum B a)
-// radiance are staged in LDS; TallyStage<PREC>::kSegs segments at a time they
-// are summed across the wavefront in a fixed order, weighted and added to the
-// cells' fixed-point accumulators (tally_flush).  The ray's entering and
-// escaped radiance over the chunk go the same way to the balance row.  PREC
-// selects the precision form: Planck values from the table, the degree-5
-// branch and FP64 partial sums.  Otherwise the Planck values of a lane's
-// points come from one exact value at its first point nu_a and the
-// second-order expansion of ln B:
-//   B(nu_a + d) = B_a (1 + g1 d + (g1^2 + g2) d^2 / 2),
-//   g1 = 3/nu - theta (1 + r),  g2 = -3/nu^2 + theta^2 r (1 + r),
-//   theta = c2 / T,  r = 1 / (exp(theta nu) - 1);
-// for d <= (kQ - 1) dnu the neglected terms are below 1e-9 relative.
+// radiance are staged in LDS; several segments at a time they are summed
+// across the wavefront in a fixed order, weighted and added to the cells'
+// fixed-point accumulators.  The ray's entering and escaped radiance over the
+// chunk go the same way to the balance row.
+//
+// The plain form (march_plain) takes kPlainQ contiguous points per lane, the
+// precision form (march_wave) kQ, Planck values from the table, the degree-5
+// branch and FP64 partial sums.
 struct MarchWave {
   const float* kappa;   // row c at kappa + c * ld, column j - col0
   const float* planck;  // same layout (precision form)
   int64_t ld;
   int64_t col0;
-  const double* theta;  // c2 / T per cell (plain form)
+  const double* theta;  // c2 / T per cell (plain form, general Planck values)
+  const float4* poly;   // Planck cubics (plain form): record c * n_poly + chunk
+  int64_t n_poly;
   const float* bwall;   // B(nu_j, T_wall), indexed by absolute j
   double nu0, dnu, c1, weight;
   unsigned long long* acc;  // accumulator rows, kAccRow words each
@@ -677,10 +663,32 @@ struct MarchWave {
   unsigned* ovf;            // set by acc_add for a value out of range
 };
 
-// Per-wavefront LDS staging of the per-segment partial sums: [kSegs][2][64].
-template <bool PREC>
-struct TallyStage {
-  static constexpr int kSegs = PREC ? 4 : 8;
+// Planck values of the plain form as one cubic per (cell, kMarchPoints-point
+// chunk), B(nu_j, T) = r.x + r.y u + r.z u^2 + r.w u^3 with u = j minus the
+// chunk's middle in points.  The host allows it (rt::planck_cubic_fits) where
+// the cubic through the Chebyshev nodes and its first-order expansion over a
+// lane's points are both within FP32 rounding of B; elsewhere a lane forms
+// its own value (planck_lane).
+constexpr int kMarchPoints = 64 * kPlainQ;
+constexpr double kCubicNodeA = 0.92387953251128674, kCubicNodeB = 0.38268343236508978;
+
+// Cubic through values at the nodes -a, -b, b, a of [-1, 1], for an argument
+// in points (half = points per unit).
+__host__ __device__ inline void planck_cubic(const double f[4], double half, double r[4]) {
+  const double a = kCubicNodeA, b = kCubicNodeB, den = a * a - b * b;
+  const double ea = 0.5 * (f[3] + f[0]), eb = 0.5 * (f[2] + f[1]);
+  const double oa = 0.5 * (f[3] - f[0]) / a, ob = 0.5 * (f[2] - f[1]) / b;
+  const double k2 = (ea - eb) / den, k3 = (oa - ob) / den;
+  r[0] = ea - k2 * a * a;
+  r[1] = (oa - k3 * a * a) / half;
+  r[2] = k2 / (half * half);
+  r[3] = k3 / (half * half * half);
+}
+
+// Per-wavefront LDS staging of the precision form's per-segment partial sums:
+// [kSegs][2][64].
+struct PrecStage {
+  static constexpr int kSegs = 4;
   static constexpr int kEntries = kSegs * 2 * 64;
 };
 
@@ -689,49 +697,41 @@ struct TallyStage {
 // (q = 0 absorbed or entering, 1 emitted or escaped) is summed by
 // 64 / (2 kSegs) lanes, each over a fixed run of the 64 partials, then across
 // those lanes with DPP: the same order every time.
-template <bool PREC>
-__device__ __forceinline__ void tally_flush(const MarchWave& a,
-                                            const typename Partial<PREC>::T* stage,
+__device__ __forceinline__ void tally_flush(const MarchWave& a, const double* stage,
                                             const int2* sg, int ns, int k0, int np, int lane,
                                             int64_t bal_row) {
-  using PT = typename Partial<PREC>::T;
-  constexpr int V = 2 * TallyStage<PREC>::kSegs;
+  constexpr int V = 2 * PrecStage::kSegs;
   constexpr int LPV = 64 / V;  // lanes per value
   constexpr int E = 64 / LPV;  // partials per lane
-  static_assert(LPV == 4 || LPV == 8, "flush layout");
+  static_assert(LPV == 8, "flush layout");
   __builtin_amdgcn_wave_barrier();
   // a flush runs once per kSegs segments: its lane-derived addresses are
   // formed here rather than hoisted and kept live across the march loop
   int ln = lane;
   asm volatile("" : "+v"(ln));
   const int v = ln / LPV, part = ln % LPV;
-  const PT* src = stage + v * 64 + part * E;
-  PT s = src[0];
+  const double* src = stage + v * 64 + part * E;
+  double s = src[0];
 #pragma unroll
   for (int i = 1; i < E; ++i) s += src[i];
-  s += dpp_pt<0xB1>(s);  // quad_perm [1,0,3,2]
-  s += dpp_pt<0x4E>(s);  // quad_perm [2,3,0,1]
-  if (LPV == 8) s += dpp_pt<0x141>(s);  // row_half_mirror: the two quads of 8 lanes
+  s += dpp_f64<0xB1>(s);   // quad_perm [1,0,3,2]
+  s += dpp_f64<0x4E>(s);   // quad_perm [2,3,0,1]
+  s += dpp_f64<0x141>(s);  // row_half_mirror: the two quads of 8 lanes
   __builtin_amdgcn_wave_barrier();
   const int seg = v >> 1;
   if (part == 0 && seg < np) {
     const int k = k0 + seg;
     const int64_t row = k < ns ? a.row0 + sg[k].x : bal_row;
-    acc_add(a.acc + row * kAccRow + (v & 1) * kAccDigits, (double)s * a.weight, a.ovf);
+    acc_add(a.acc + row * kAccRow + (v & 1) * kAccDigits, s * a.weight, a.ovf);
   }
 }
 
-// QUAD: keep the second-order term of the per-lane Planck expansion (plain
-// form); the host drops it when its relative size over a lane's span is
-// below FP32 unit roundoff for every cell temperature and wavenumber.
-// stage: this wavefront's TallyStage<PREC>::kEntries LDS entries; slot: the
-// ray's index in its launch, which picks its balance row.
-template <bool PREC, bool EXIT, bool QUAD = true>
+// Precision form.  stage: this wavefront's PrecStage::kEntries LDS entries;
+// slot: the ray's index in its launch, which picks its balance row.
+template <bool EXIT>
 __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, int ns, int64_t j,
-                                           int lane, float* exit_row,
-                                           typename Partial<PREC>::T* stage, int64_t slot) {
-  using PT = typename Partial<PREC>::T;
-  constexpr int kSegs = TallyStage<PREC>::kSegs;
+                                           int lane, float* exit_row, double* stage, int64_t slot) {
+  constexpr int kSegs = PrecStage::kSegs;
   const int64_t col = j - a.col0;
   float I[kQ];
 #pragma unroll
@@ -739,18 +739,9 @@ __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, i
     const float4 v = *reinterpret_cast<const float4*>(a.bwall + j + 4 * h);
     I[4 * h] = v.x; I[4 * h + 1] = v.y; I[4 * h + 2] = v.z; I[4 * h + 3] = v.w;
   }
-  double nu_a = 0.0;
-  float c1nu3 = 0.f, three_nu = 0.f, three_nu2 = 0.f;
-  const float dnu_f = (float)a.dnu;
-  if (!PREC) {
-    nu_a = a.nu0 + (double)j * a.dnu;
-    c1nu3 = (float)(a.c1 * nu_a * nu_a * nu_a);
-    three_nu = (float)(3.0 / nu_a);
-    three_nu2 = (float)(3.0 / (nu_a * nu_a));
-  }
-  PT enter = 0;
+  double enter = 0;
 #pragma unroll
-  for (int q = 0; q < kQ; ++q) enter += (PT)I[q];
+  for (int q = 0; q < kQ; ++q) enter += (double)I[q];
   const float nlog2e = -1.4426950408889634f;
   int np = 0, k0 = 0;  // staged entries, and the segment of the first
   for (int k = 0; k < ns; ++k) {
@@ -764,83 +755,24 @@ __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, i
       const float4 v = *reinterpret_cast<const float4*>(a.kappa + c * a.ld + col + 4 * h);
       kv[4 * h] = v.x; kv[4 * h + 1] = v.y; kv[4 * h + 2] = v.z; kv[4 * h + 3] = v.w;
     }
-    if (PREC) {
 #pragma unroll
-      for (int h = 0; h < kQ / 4; ++h) {
-        const float4 v = *reinterpret_cast<const float4*>(a.planck + c * a.ld + col + 4 * h);
-        bv[4 * h] = v.x; bv[4 * h + 1] = v.y; bv[4 * h + 2] = v.z; bv[4 * h + 3] = v.w;
-      }
-    } else {
-      const double th = a.theta[c];  // c2 / T
-      // exp(theta nu_a) with FP64 range reduction: 2^n 2^f, |f| <= 1/2
-      const double z = th * 1.4426950408889634074 * nu_a;
-      const double n = rint(z);
-      const float f = (float)(z - n);
-      const float e = ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
-      float em1 = e - 1.0f;
-      if (__ballot(z < 0.36)) {  // theta nu < 1/4: expm1 by its series
-        const float x = (float)(th * nu_a);
-        float p = fmaf(x, 1.0f / 720.0f, 1.0f / 120.0f);
-        p = fmaf(x, p, 1.0f / 24.0f);
-        p = fmaf(x, p, 1.0f / 6.0f);
-        p = fmaf(x, p, 0.5f);
-        p = fmaf(x, p, 1.0f);
-        if (z < 0.36) em1 = x * p;
-      }
-      const float r = __builtin_amdgcn_rcpf(em1);
-      const float B0 = c1nu3 * r;
-      const float thf = (float)th;
-      const float t1 = 1.0f + r;
-      const float g1 = fmaf(-thf, t1, three_nu);
-      const float g2 = fmaf(thf * thf, r * t1, -three_nu2);
-      const float K1 = B0 * g1 * dnu_f;
-      if (QUAD) {
-        const float K2 = 0.5f * B0 * fmaf(g1, g1, g2) * (dnu_f * dnu_f);
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) bv[q] = fmaf(fmaf(K2, (float)q, K1), (float)q, B0);
-      } else {
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) bv[q] = fmaf(K1, (float)q, B0);
-      }
+    for (int h = 0; h < kQ / 4; ++h) {
+      const float4 v = *reinterpret_cast<const float4*>(a.planck + c * a.ld + col + 4 * h);
+      bv[4 * h] = v.x; bv[4 * h + 1] = v.y; bv[4 * h + 2] = v.z; bv[4 * h + 3] = v.w;
     }
     // a = 1 - e^{-tau} per point
     float av[kQ];
-    if (PREC) {
-#pragma unroll
-      for (int q = 0; q < kQ; ++q) {
-        const float tau = kv[q] * l;
-        const float big = 1.0f - __builtin_amdgcn_exp2f(kv[q] * xs);
-        av[q] = tau < 0.25f ? poly5(tau) : big;
-      }
-    } else {
-      float kmin = kv[0];
-#pragma unroll
-      for (int q = 0; q < kQ; ++q) {
-        av[q] = 1.0f - __builtin_amdgcn_exp2f(kv[q] * xs);
-        kmin = fminf(kmin, kv[q]);
-      }
-      if (__ballot(kmin * l < 0.03125f)) {
-        // some lane has tau < 1/32: there a = tau - tau^2/2 + tau^3/6 written
-        // in x = -tau log2(e), i.e. a = -sum_k (x ln 2)^k / k!, k = 1..3
-        // (truncation below tau^3/24 = 1.3e-6 relative); at tau >= 1/32 the
-        // error of 1 - 2^x, about one unit in the last place of 2^x, is
-        // below 1.5e-6 relative to a
-        constexpr float L1 = -0.69314718055994531f, L2 = -0.24022650695910071f,
-                        L3 = -0.055504108664821576f;
-        constexpr float xlim = -0.03125f * 1.4426950408889634f;
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-          const float x = kv[q] * xs;
-          const float ser = x * fmaf(x, fmaf(x, L3, L2), L1);
-          av[q] = x > xlim ? ser : av[q];
-        }
-      }
-    }
-    PT ab = 0, em = 0;
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-      ab += (PT)(I[q] * av[q]);
-      em += (PT)(bv[q] * av[q]);
+      const float tau = kv[q] * l;
+      const float big = 1.0f - __builtin_amdgcn_exp2f(kv[q] * xs);
+      av[q] = tau < 0.25f ? poly5(tau) : big;
+    }
+    double ab = 0, em = 0;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      ab += (double)(I[q] * av[q]);
+      em += (double)(bv[q] * av[q]);
       I[q] = fmaf(-(I[q] - bv[q]), av[q], I[q]);
     }
     // the update of I is complete here, so a[] dies before the staging and
@@ -848,18 +780,18 @@ __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, i
     // them and keep a[] and B[] live across the flush)
 #pragma unroll
     for (int q = 0; q < kQ; ++q) asm volatile("" ::"v"(I[q]));
-    PT* st = stage + np * 128;
+    double* st = stage + np * 128;
     st[lane] = ab;
     st[64 + lane] = em;
     if (++np == kSegs) {
-      tally_flush<PREC>(a, stage, sg, ns, k0, np, lane, 0);
+      tally_flush(a, stage, sg, ns, k0, np, lane, 0);
       k0 += np;
       np = 0;
     }
   }
-  PT esc = 0;
+  double esc = 0;
 #pragma unroll
-  for (int q = 0; q < kQ; ++q) esc += (PT)I[q];
+  for (int q = 0; q < kQ; ++q) esc += (double)I[q];
   if (EXIT) {
 #pragma unroll
     for (int h = 0; h < kQ / 4; ++h)
@@ -867,10 +799,256 @@ __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, i
           make_float4(I[4 * h], I[4 * h + 1], I[4 * h + 2], I[4 * h + 3]);
   }
   // np < kSegs here: one more entry, the balance row's (entering, escaped)
-  PT* st = stage + np * 128;
+  double* st = stage + np * 128;
   st[lane] = enter;
   st[64 + lane] = esc;
-  tally_flush<PREC>(a, stage, sg, ns, k0, np + 1, lane, a.bal_row0 + (slot & a.bal_mask));
+  tally_flush(a, stage, sg, ns, k0, np + 1, lane, a.bal_row0 + (slot & a.bal_mask));
+}
+
+// ------------------------------------------------------- the plain form's march
+// Wave-uniform loads through the scalar cache: for data that no block of the
+// same launch writes (the persistent batched kernel, whose blocks write each
+// other's segments, loads the ordinary way and broadcasts).
+typedef int IntPair __attribute__((ext_vector_type(2)));
+typedef float FloatQuad __attribute__((ext_vector_type(4)));
+template <bool SCALAR>
+__device__ __forceinline__ IntPair load_seg(const int2* p) {
+  if (SCALAR)
+    return *reinterpret_cast<const __attribute__((address_space(4))) IntPair*>(
+        reinterpret_cast<uintptr_t>(p));
+  const int2 v = *p;
+  return IntPair{__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y)};
+}
+__device__ __forceinline__ FloatQuad load_quad(const float4* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) FloatQuad*>(
+      reinterpret_cast<uintptr_t>(p));
+}
+
+// Staging of the plain form: one float per lane and segment.  Lanes 2 i and
+// 2 i + 1 hold the pair's absorbed and emitted sums (one DPP add each and a
+// select), so 16 segments take the 4 KB that 8 took unpaired, and a flush,
+// whose cost is the fixed-point add whatever it carries, runs half as often.
+struct PlainStage {
+  static constexpr int kSegs = 16;
+  static constexpr int kEntries = kSegs * 64;
+};
+
+__device__ __forceinline__ void plain_stage(float* stage, int np, int lane, float ab, float em) {
+  const float a2 = ab + dpp_f32<0xB1>(ab);  // quad_perm [1,0,3,2]
+  const float e2 = em + dpp_f32<0xB1>(em);
+  stage[np * 64 + lane] = (lane & 1) ? e2 : a2;
+}
+
+// Adds np staged entries to the accumulators (entries as tally_flush).  Four
+// lanes per entry, each over 16 consecutive floats (8 absorbed, 8 emitted),
+// then across the four with DPP: the same order every time.
+__device__ __forceinline__ void plain_flush(const MarchWave& a, const float* stage, const int2* sg,
+                                            int ns, int k0, int np, int lane, int64_t bal_row) {
+  __builtin_amdgcn_wave_barrier();
+  int ln = lane;  // see tally_flush
+  asm volatile("" : "+v"(ln));
+  const int seg = ln >> 2;
+  const float4* src = reinterpret_cast<const float4*>(stage + ln * 16);
+  float ab = 0.f, em = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float4 v = src[i];
+    ab += v.x;
+    em += v.y;
+    ab += v.z;
+    em += v.w;
+  }
+  ab += dpp_f32<0xB1>(ab);
+  em += dpp_f32<0xB1>(em);
+  float s = (ln & 1) ? em : ab;
+  s += dpp_f32<0x4E>(s);  // quad_perm [2,3,0,1]
+  __builtin_amdgcn_wave_barrier();
+  if (!(ln & 2) && seg < np) {
+    const int k = k0 + seg;
+    const int64_t row = k < ns ? a.row0 + sg[k].x : bal_row;
+    acc_add(a.acc + row * kAccRow + (ln & 1) * kAccDigits, (double)s * a.weight, a.ovf);
+  }
+}
+
+// General Planck values of a lane (plain form, where the cubics do not fit):
+// one exact value at its first point nu_a and the second-order expansion of
+// ln B:
+//   B(nu_a + d) = B_a (1 + g1 d + (g1^2 + g2) d^2 / 2),
+//   g1 = 3/nu - theta (1 + r),  g2 = -3/nu^2 + theta^2 r (1 + r),
+//   theta = c2 / T,  r = 1 / (exp(theta nu) - 1).
+struct PlanckLane {
+  double nu_a;
+  float c1nu3, three_nu, three_nu2, dnu;
+};
+__device__ __forceinline__ void planck_lane(const PlanckLane& p, double th, float& B0, float& K1,
+                                            float& K2) {
+  // exp(theta nu_a) with FP64 range reduction: 2^n 2^f, |f| <= 1/2
+  const double z = th * 1.4426950408889634074 * p.nu_a;
+  const double n = rint(z);
+  const float f = (float)(z - n);
+  const float e = ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
+  float em1 = e - 1.0f;
+  if (__ballot(z < 0.36)) {  // theta nu < 1/4: expm1 by its series
+    const float x = (float)(th * p.nu_a);
+    float q = fmaf(x, 1.0f / 720.0f, 1.0f / 120.0f);
+    q = fmaf(x, q, 1.0f / 24.0f);
+    q = fmaf(x, q, 1.0f / 6.0f);
+    q = fmaf(x, q, 0.5f);
+    q = fmaf(x, q, 1.0f);
+    if (z < 0.36) em1 = x * q;
+  }
+  const float r = __builtin_amdgcn_rcpf(em1);
+  B0 = p.c1nu3 * r;
+  const float thf = (float)th;
+  const float t1 = 1.0f + r;
+  const float g1 = fmaf(-thf, t1, p.three_nu);
+  const float g2 = fmaf(thf * thf, r * t1, -p.three_nu2);
+  K1 = B0 * g1 * p.dnu;
+  K2 = 0.5f * B0 * fmaf(g1, g1, g2) * (p.dnu * p.dnu);
+}
+
+// One wavefront, one ray, the kMarchPoints points from the absolute index j0
+// (uniform), kPlainQ per lane.
+//
+// Issue-bound where rays are dense: a point takes its multiply, the
+// exponential, B, I - B, the update and two sums, 7 instructions, and a
+// segment 33 more (Planck cubic, tests, staging, flush, the ray's ends),
+// shared by the lane's kPlainQ points.  24 points per lane spread those best
+// but put 6 KB of each crossed cell's row in flight per wavefront, a whole
+// XCD's L2.  32^3 cells, 50,000 points, 2^20 rays: 9.7 instructions per
+// update and 2.5 TB past L2 in 498 ms at 12 points, 530 ms at 24, 526 ms at
+// 16, 655 ms at 8 (with sums over a per point, general Planck values and 24
+// points it was 11.6 instructions, 3.45 TB and 543 ms).  Where rays are sparse
+// (about 100 per cell) each row is read from beyond L2 for nearly every
+// crossing, at 7 TB/s, and fewer wavefronts in flight are better: the launches
+// pad the block's LDS to hold 6 or 7 per SIMD.
+//
+// The sums run over t = e^{-tau} itself: with W = sum I t and V = sum B t a
+// segment emits sum B - V and absorbs S - W, S = sum I being W + emitted of
+// the segment before, so that a = 1 - t is not formed per point.  These
+// differences lose at most a factor 1/a <= 32 of FP32 rounding, no more than
+// 1 - t loses at tau = 1/32, while every lane emits and absorbs at least 1/32
+// of its sums.  Where a lane does not, the segment's sums are formed again over
+// a = tau - tau^2/2 + tau^3/6, written in x = -tau log2(e) (truncation below
+// tau^3/24 = 1.3e-6 relative), or 1 - t from tau = 1/32 on.
+// CUBIC: Planck cubics, else planck_lane.  SCALAR: see load_seg.
+// stage: this wavefront's PlainStage::kEntries LDS floats; slot: the ray's
+// index in its launch, which picks its balance row.
+template <bool EXIT, bool CUBIC, bool SCALAR>
+__device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, int ns, int64_t j0,
+                                            int lane, float* exit_row, float* stage,
+                                            int64_t slot) {
+  constexpr int Q = kPlainQ;
+  constexpr float kThin = 0.03125f;
+  constexpr float nlog2e = -1.4426950408889634f;
+  const unsigned voff = (unsigned)lane * (Q * 4);            // bytes into the chunk's row
+  const char* kchunk = reinterpret_cast<const char*>(a.kappa + (j0 - a.col0));
+  const int64_t j = j0 + lane * Q;
+  float I[Q];
+#pragma unroll
+  for (int h = 0; h < Q / 4; ++h) {
+    const float4 v = *reinterpret_cast<const float4*>(a.bwall + j + 4 * h);
+    I[4 * h] = v.x; I[4 * h + 1] = v.y; I[4 * h + 2] = v.z; I[4 * h + 3] = v.w;
+  }
+  const float4* poly = nullptr;
+  float u0 = 0.f;  // the lane's first point from the chunk's middle
+  PlanckLane pl{};
+  if (CUBIC) {
+    poly = a.poly + j0 / kMarchPoints;
+    u0 = (float)(lane * Q) - 0.5f * (kMarchPoints - 1);
+  } else {
+    pl.nu_a = a.nu0 + (double)j * a.dnu;
+    pl.c1nu3 = (float)(a.c1 * pl.nu_a * pl.nu_a * pl.nu_a);
+    pl.three_nu = (float)(3.0 / pl.nu_a);
+    pl.three_nu2 = (float)(3.0 / (pl.nu_a * pl.nu_a));
+    pl.dnu = (float)a.dnu;
+  }
+  float S = 0.f;  // sum of I over the lane's points
+#pragma unroll
+  for (int q = 0; q < Q; ++q) S += I[q];
+  const float enter = S;
+  int np = 0, k0 = 0;  // staged entries, and the segment of the first
+  IntPair s = ns > 0 ? load_seg<SCALAR>(sg) : IntPair{0, 0};
+  for (int k = 0; k < ns; ++k) {
+    const int64_t c = s.x;
+    const float l = __int_as_float(s.y);
+    FloatQuad r{};
+    if (CUBIC) r = load_quad(poly + c * a.n_poly);
+    float kv[Q];
+    {
+      const char* row = kchunk + c * (a.ld * 4);
+      unsigned vo = voff;  // opaque: the row's address stays uniform, not per lane
+      asm("" : "+v"(vo));
+#pragma unroll
+      for (int h = 0; h < Q / 4; ++h) {
+        const float4 v = *reinterpret_cast<const float4*>(row + vo + 16 * h);
+        kv[4 * h] = v.x; kv[4 * h + 1] = v.y; kv[4 * h + 2] = v.z; kv[4 * h + 3] = v.w;
+      }
+    }
+    if (k + 1 < ns) s = load_seg<SCALAR>(sg + k + 1);  // the next segment's, early
+    const float xs = l * nlog2e;
+    float B0, K1, K2 = 0.f;
+    if (CUBIC) {
+      const float e2 = fmaf(r.w, u0, r.z);
+      const float e1 = fmaf(e2, u0, r.y);
+      B0 = fmaf(e1, u0, r.x);
+      K1 = fmaf(fmaf(r.w, u0, e2), u0, e1);  // the derivative at u0
+    } else {
+      planck_lane(pl, a.theta[c], B0, K1, K2);
+    }
+    float x[Q], t[Q], B[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      x[q] = kv[q] * xs;
+      t[q] = __builtin_amdgcn_exp2f(x[q]);
+      B[q] = q == 0 ? B0 : fmaf(CUBIC ? K1 : fmaf(K2, (float)q, K1), (float)q, B0);
+    }
+    float W = I[0] * t[0], V = B[0] * t[0];
+#pragma unroll
+    for (int q = 1; q < Q; ++q) {
+      W = fmaf(I[q], t[q], W);
+      V = fmaf(B[q], t[q], V);
+    }
+    constexpr float s1 = 0.5f * Q * (Q - 1), s2 = Q * (Q - 1) * (2 * Q - 1) / 6.0f;
+    float sumB = fmaf(K1, s1, B0 * (float)Q);
+    if (!CUBIC) sumB = fmaf(K2, s2, sumB);
+    float em = sumB - V, ab = S - W;
+    if (__ballot(!(fminf(fmaf(-kThin, sumB, em), fmaf(-kThin, S, ab)) >= 0.f))) {
+      constexpr float L1 = -0.69314718055994531f, L2 = -0.24022650695910071f,
+                      L3 = -0.055504108664821576f;
+      constexpr float xlim = kThin * nlog2e;
+      ab = 0.f;
+      em = 0.f;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const float ser = x[q] * fmaf(x[q], fmaf(x[q], L3, L2), L1);
+        const float av = x[q] > xlim ? ser : 1.0f - t[q];
+        ab = fmaf(I[q], av, ab);
+        em = fmaf(B[q], av, em);
+      }
+    }
+    S = W + em;
+    // I = (I - B) t + B in the three-address form: the compiler would add into
+    // B's register and copy the Q results back around the loop
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(I[q]) : "v"(I[q] - B[q]), "v"(t[q]), "v"(B[q]));
+    plain_stage(stage, np, lane, ab, em);
+    if (++np == PlainStage::kSegs) {
+      plain_flush(a, stage, sg, ns, k0, np, lane, 0);
+      k0 += np;
+      np = 0;
+    }
+  }
+  if (EXIT) {
+#pragma unroll
+    for (int h = 0; h < Q / 4; ++h)
+      *reinterpret_cast<float4*>(exit_row + (j - a.col0) + 4 * h) =
+          make_float4(I[4 * h], I[4 * h + 1], I[4 * h + 2], I[4 * h + 3]);
+  }
+  // np < kSegs here: one more entry, the balance row's (entering, escaped)
+  plain_stage(stage, np, lane, enter, S);
+  plain_flush(a, stage, sg, ns, k0, np + 1, lane, a.bal_row0 + (slot & a.bal_mask));
 }
 
 }  // namespace dev

@@ -137,6 +137,27 @@ __global__ void wall_table_kernel(float2 theta_wall, int n_nu, int64_t ld, float
   bw[j] = v;
 }
 
+// Planck cubics of the plain march: one thread per (cell, chunk of
+// kMarchPoints points), B at the four Chebyshev nodes in FP64.
+__global__ void planck_cubics_kernel(const double* __restrict__ theta, int64_t n, int64_t n_chunks,
+                                     double nu0, double dnu, double c1,
+                                     float4* __restrict__ poly) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n * n_chunks) return;
+  const double th = theta[i / n_chunks];
+  const double half = 0.5 * kMarchPoints;
+  const double mid = nu0 + ((double)(i % n_chunks) * kMarchPoints + 0.5 * (kMarchPoints - 1)) * dnu;
+  const double x[4] = {-kCubicNodeA, -kCubicNodeB, kCubicNodeB, kCubicNodeA};
+  double f[4], r[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double nu = mid + x[k] * half * dnu;
+    f[k] = c1 * nu * nu * nu / expm1(th * nu);
+  }
+  planck_cubic(f, half, r);
+  poly[i] = make_float4((float)r[0], (float)r[1], (float)r[2], (float)r[3]);
+}
+
 // The paper's own formulation of Eq. (2) (Section 3 and its listing): line i
 // contributes u S_i s_i(T) f_i(j) at the 16 grid points j = m_i - 7 .. m_i + 8,
 // f_i the reference-state Lorentz shape tabulated once per line (prof16);
@@ -362,6 +383,15 @@ hipError_t launch_kappa_tiles_fine(rt_ctx c, const KappaTile& t, int64_t n_cell_
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL((kappa_linesum_kernel<false, false, 1>), dim3((unsigned)blocks),
                      dim3(kKappaThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_planck_cubics(rt_ctx c, const double* theta, int64_t n, float4* poly,
+                                hipStream_t s) {
+  const int64_t chunks = plain_chunks(c->n_nu), blocks = (n * chunks + 255) / 256;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(planck_cubics_kernel, dim3((unsigned)blocks), dim3(256), 0, s, theta, n,
+                     chunks, c->nu0, c->dnu, first_radiation_wavenumber(), poly);
   return hipGetLastError();
 }
 

@@ -14,6 +14,8 @@
 //                balance from exact sums of the accumulators
 #include "device_common.h"
 
+#include <cmath>
+
 namespace rt {
 namespace {
 
@@ -101,7 +103,6 @@ __global__ void raygen_dda_kernel(uint64_t seed, uint64_t begin, int64_t count, 
 
 struct MarchArgs {
   MarchWave w;
-  int n_chunks;
   int64_t ray_blocks_x;  // ray blocks per XCD
   const int2* segs;
   const int32_t* counts;
@@ -111,40 +112,44 @@ struct MarchArgs {
 };
 
 // Block = 4 wavefronts = 4 consecutive rays (batch slots) on one spectral
-// chunk.  Workgroups are dispatched to the 8 XCDs round-robin, so block b
-// runs on XCD b % 8; that XCD is given a contiguous range of ray blocks,
-// chunk-major, so the waves in flight on it march neighbouring rays of the
-// coherent order through one chunk and share kappa rows in its L2.
-template <bool PREC, bool EXIT, bool QUAD>
-__device__ __forceinline__ void march_block(const MarchArgs& a,
-                                            typename Partial<PREC>::T (*stage)[TallyStage<PREC>::kEntries]) {
-  const int64_t b = blockIdx.x;
-  const int64_t xcd = b & 7, local = b >> 3;
-  const int chunk = (int)(local / a.ray_blocks_x);
-  const int64_t rb = xcd * a.ray_blocks_x + local % a.ray_blocks_x;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int64_t ray = rb * 4 + wave;
-  if (ray >= a.n_rays) return;
-  const int64_t j = (int64_t)chunk * kChunk + lane * kQ;
-  march_wave<PREC, EXIT, QUAD>(a.w, a.segs + ray * a.max_segs, a.counts[ray], j, lane,
-                               EXIT ? a.exit_I + ray * a.w.ld : nullptr, stage[wave], ray);
+// chunk (blockIdx.y).  Workgroups are dispatched to the 8 XCDs round-robin, so
+// block b of a chunk runs on XCD b % 8 (a chunk's blocks are a multiple of 8);
+// that XCD is given a contiguous range of ray blocks, chunk-major, so the
+// waves in flight on it march neighbouring rays of the coherent order through
+// one chunk and share kappa rows in its L2.
+__device__ __forceinline__ bool march_place(const MarchArgs& a, int64_t& ray, int& wave,
+                                            int& lane) {
+  const unsigned b = blockIdx.x;
+  const int64_t rb = (int64_t)(b & 7) * a.ray_blocks_x + (b >> 3);
+  wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  lane = threadIdx.x & 63;
+  ray = rb * 4 + wave;
+  return ray < a.n_rays;
 }
 
-// Plain form.  Five wavefronts per SIMD (at most 96 VGPRs): the kappa rows
-// of the next segments are in flight while other wavefronts compute.
-template <bool EXIT, bool QUAD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void march_kernel(
+// Plain form (see march_plain).
+template <bool EXIT, bool CUBIC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void march_kernel(
     MarchArgs a) {
-  __shared__ float stage[4][TallyStage<false>::kEntries];
-  march_block<false, EXIT, QUAD>(a, stage);
+  __shared__ float stage[4][PlainStage::kEntries];
+  int64_t ray;
+  int wave, lane;
+  if (!march_place(a, ray, wave, lane)) return;
+  march_plain<EXIT, CUBIC, true>(a.w, a.segs + ray * a.max_segs, a.counts[ray],
+                                 (int64_t)blockIdx.y * kMarchPoints, lane,
+                                 EXIT ? a.exit_I + ray * a.w.ld : nullptr, stage[wave], ray);
 }
 
 // Precision form (Planck table, FP64 partial sums).
 template <bool EXIT>
 __global__ __launch_bounds__(256) void march_prec_kernel(MarchArgs a) {
-  __shared__ double stage[4][TallyStage<true>::kEntries];
-  march_block<true, EXIT, true>(a, stage);
+  __shared__ double stage[4][PrecStage::kEntries];
+  int64_t ray;
+  int wave, lane;
+  if (!march_place(a, ray, wave, lane)) return;
+  march_wave<EXIT>(a.w, a.segs + ray * a.max_segs, a.counts[ray],
+                   (int64_t)blockIdx.y * kChunk + lane * kQ, lane,
+                   EXIT ? a.exit_I + ray * a.w.ld : nullptr, stage[wave], ray);
 }
 
 // Carries of every accumulator row (rows x 2 digit groups).
@@ -256,28 +261,36 @@ hipError_t launch_raygen(rt_ctx c, const RayScratch& s, uint64_t seed, uint64_t 
   return hipGetLastError();
 }
 
-// The plain march expands B(nu_a + s) = B0 (1 + g1 s + (g1^2 + g2) s^2 / 2
-// + ...) about a lane's first point nu_a, s <= (kQ - 1) dnu, with
-// g1 = d ln B / d nu = 3/nu - theta (1 + r), g2 = d g1 / d nu
-// = -3/nu^2 + theta^2 r (1 + r), theta = c2/T, r = 1/(exp(theta nu) - 1).
-// The second-order term is needed unless its relative size stays below FP32
-// unit roundoff (2^-24) over the grid's temperatures and wavenumbers
-// (checked at the extremes and midpoints of both ranges).
-bool planck_needs_quadratic(double T_min, double T_max, double nu0, double dnu, int n_nu) {
+int64_t plain_chunks(int64_t n_nu) { return (n_nu + kMarchPoints - 1) / kMarchPoints; }
+
+// The Planck cubics serve a grid where, over its temperatures and wavenumbers
+// (checked at the extremes and midpoints of both ranges), a chunk's cubic is
+// within 2^-25 of B and the first-order expansion over a lane's kPlainQ points
+// within 2^-24 (FP32 unit roundoff) of it: at 300 K and 1000 cm^-1 up to
+// dnu of about 0.03 cm^-1.  A cubic costs the march 7 instructions per
+// segment against 17 for the general value, and 16 bytes per row of 3 KB.
+bool planck_cubic_fits(double T_min, double T_max, double nu0, double dnu, int n_nu) {
   const double c2 = second_radiation_cm_K();
-  const double span = (kQ - 1) * dnu;
-  const double nu_lo = nu0, nu_hi = nu0 + (n_nu - 1) * dnu;
-  const double Ts[3] = {T_min, T_max, std::sqrt(T_min * T_max)};
-  const double nus[3] = {nu_lo, nu_hi, 0.5 * (nu_lo + nu_hi)};
-  double worst = 0;
-  for (double T : Ts)
-    for (double nu : nus) {
-      const double th = c2 / T, r = 1.0 / std::expm1(th * nu);
-      const double g1 = 3.0 / nu - th * (1.0 + r);
-      const double g2 = -3.0 / (nu * nu) + th * th * r * (1.0 + r);
-      worst = std::max(worst, 0.5 * std::fabs(g1 * g1 + g2) * span * span);
+  const double half = 0.5 * kMarchPoints;
+  auto B = [&](double nu, double T) { return nu * nu * nu / std::expm1(c2 * nu / T); };
+  const double mid0 = nu0 + 0.5 * (kMarchPoints - 1) * dnu;
+  const double last = (double)(plain_chunks(n_nu) - 1) * kMarchPoints * dnu;
+  const double u[5] = {-1.0, -0.7071, 0.0, 0.7071, 1.0};
+  for (double T : {T_min, T_max, std::sqrt(T_min * T_max)})
+    for (double m : {mid0, mid0 + 0.5 * last, mid0 + last}) {
+      const double x[4] = {-kCubicNodeA, -kCubicNodeB, kCubicNodeB, kCubicNodeA};
+      double f[4], r[4];
+      for (int i = 0; i < 4; ++i) f[i] = B(m + x[i] * half * dnu, T);
+      planck_cubic(f, half, r);
+      for (double v : u) {
+        const double p = v * half, ref = B(m + p * dnu, T);
+        const double fit = r[0] + p * (r[1] + p * (r[2] + p * r[3]));
+        if (!(std::fabs(fit - ref) <= std::ldexp(ref, -25))) return false;
+        const double d2 = 0.5 * std::fabs(2.0 * r[2] + 6.0 * r[3] * p) * (kPlainQ - 1) * (kPlainQ - 1);
+        if (!(d2 < std::ldexp(ref, -24))) return false;
+      }
     }
-  return !(worst < std::ldexp(1.0, -24));
+  return true;
 }
 
 hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double weight, bool prec,
@@ -288,6 +301,8 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
   a.w.ld = c->ld;
   a.w.col0 = 0;
   a.w.theta = c->cells.theta;
+  a.w.poly = c->d_poly;
+  a.w.n_poly = plain_chunks(c->n_nu);
   a.w.bwall = c->d_bwall;
   a.w.nu0 = c->nu0;
   a.w.dnu = c->dnu;
@@ -298,25 +313,28 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
   a.w.bal_row0 = c->n_cells;
   a.w.bal_mask = kBalRows - 1;
   a.w.ovf = c->d_ovf;
-  a.n_chunks = (int)(c->ld / kChunk);
   a.ray_blocks_x = ((count + 3) / 4 + 7) / 8;
   a.segs = s.segs;
   a.counts = s.counts;
   a.max_segs = s.max_segs;
   a.n_rays = count;
   a.exit_I = exit_dev;
-  const int64_t blocks = 8 * a.ray_blocks_x * a.n_chunks;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 g((unsigned)blocks), t(256);
+  // the columns past n_nu hold zeros and add nothing: the plain form stops at
+  // the last chunk that holds a point
+  const int64_t n_chunks = prec ? c->ld / kChunk : plain_chunks(c->n_nu);
+  // x: at most 2^21 rays a batch, 2^19 blocks; y: n_nu < 2^24 points, 2^15 chunks
+  const dim3 g((unsigned)(8 * a.ray_blocks_x), (unsigned)n_chunks), t(256);
+  // seven wavefronts per SIMD instead of eight: 32^3 workload 498 -> 496 ms
+  const unsigned pad = 6000;
   if (prec) {
     if (exit_dev) hipLaunchKernelGGL((march_prec_kernel<true>), g, t, 0, c->stream, a);
     else hipLaunchKernelGGL((march_prec_kernel<false>), g, t, 0, c->stream, a);
-  } else if (planck_needs_quadratic(c->T_min, c->T_max, c->nu0, c->dnu, c->n_nu)) {
-    if (exit_dev) hipLaunchKernelGGL((march_kernel<true, true>), g, t, 0, c->stream, a);
-    else hipLaunchKernelGGL((march_kernel<false, true>), g, t, 0, c->stream, a);
+  } else if (c->planck_cubic) {
+    if (exit_dev) hipLaunchKernelGGL((march_kernel<true, true>), g, t, pad, c->stream, a);
+    else hipLaunchKernelGGL((march_kernel<false, true>), g, t, pad, c->stream, a);
   } else {
-    if (exit_dev) hipLaunchKernelGGL((march_kernel<true, false>), g, t, 0, c->stream, a);
-    else hipLaunchKernelGGL((march_kernel<false, false>), g, t, 0, c->stream, a);
+    if (exit_dev) hipLaunchKernelGGL((march_kernel<true, false>), g, t, pad, c->stream, a);
+    else hipLaunchKernelGGL((march_kernel<false, false>), g, t, pad, c->stream, a);
   }
   const int64_t groups = 2 * (c->n_cells + kBalRows);
   hipLaunchKernelGGL(acc_normalize_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0,

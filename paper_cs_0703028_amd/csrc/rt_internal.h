@@ -195,6 +195,13 @@ struct rt_ctx_s {
   int64_t ld = 0;
   float* d_bwall = nullptr; // B(nu_j, T_wall), ld floats (owned)
   int64_t bwall_len = 0;
+  // the plain march's Planck cubics, [cells][chunks of the march], behind the
+  // walls' row in its allocation, formed once per grid and line list like the
+  // cell factors; planck_cubic: whether they fit this grid and spectrum (else
+  // the march forms its values)
+  float4* d_poly = nullptr;
+  int64_t poly_cap = 0;
+  bool planck_cubic = false;
 
   // tallies (owned): fixed-point accumulator rows [n_cells + kBalRows][2][kAccDigits]
   // (rows from n_cells: entering, escaped) followed by the overflow flag; the
@@ -273,8 +280,12 @@ hipError_t launch_raygen(rt_ctx c, const RayScratch& s, uint64_t seed, uint64_t 
                          const uint32_t* perm);
 hipError_t launch_order(rt_ctx c, const RayScratch& s, uint64_t seed, uint64_t begin,
                         int64_t count);
-// whether the plain march needs the second-order term of its Planck expansion
-bool planck_needs_quadratic(double T_min, double T_max, double nu0, double dnu, int n_nu);
+// march chunks of the plain form in n_nu points, and its Planck cubics: whether
+// they serve a grid's temperatures and spectrum, and their table for n cells
+int64_t plain_chunks(int64_t n_nu);
+bool planck_cubic_fits(double T_min, double T_max, double nu0, double dnu, int n_nu);
+hipError_t launch_planck_cubics(rt_ctx c, const double* theta, int64_t n, float4* poly,
+                                hipStream_t s);
 // FP32 arithmetic characterisation (arith.hip): operands each op reads (0 for
 // an unknown op) and the element-wise launch.
 int arith_operands(int op);

@@ -1,0 +1,59 @@
+"""The plain march where its forms meet: spectra that end at, before and after
+its 768-point chunk and the 1536-point table pitch, the Planck cubics and the
+general Planck values (wide point spacings), and gas from
+transparent (the segment sums over a) to thick (the sums over t), per cell
+against the FP64 oracle.  The tolerance is the repository's 1e-5 per cell.
+"""
+import numpy as np
+import pytest
+
+from paper_cs_0703028_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+REL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def rt():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_cs_0703028_amd import rtlbl
+    return rtlbl
+
+
+@pytest.fixture(scope="module")
+def O():
+    from oracle import oracle
+    oracle.build()
+    return oracle
+
+
+def _run(rt, w):
+    t = rt.Tracer(0)
+    t.setup_workload(w)
+    t.compute_kappa(rt.KAPPA_PLAIN)
+    t.trace_rays(w.seed, w.n_rays, 0, w.n_rays, rt.TALLY_F32)
+    out = t.tally()
+    t.close()
+    return out
+
+
+def _check(got, ref):
+    for g, o in zip(got, (ref["absorbed"], ref["emitted"], ref["balance"])):
+        nz = o != 0
+        assert (g[~nz] == 0).all()
+        assert (np.abs(g[nz] - o[nz]) <= REL * np.abs(o[nz])).all()
+
+
+@pytest.mark.parametrize("n_nu,dnu,x,T_wall", [
+    (1, 0.01, 0.1, 900.0), (767, 0.01, 0.1, 0.0), (768, 0.01, 0.1, 900.0),
+    (769, 0.01, 0.3, 0.0), (1535, 0.01, 1e-3, 900.0), (1537, 0.01, 1e-5, 900.0),
+    (2304, 0.02, 1.0, 0.0), (1600, 0.05, 0.1, 900.0), (1600, 0.25, 1e-4, 900.0),
+])
+def test_chunk_ends_planck_forms_and_optical_depths(rt, O, n_nu, dnu, x, T_wall):
+    g = I.linear_T_grid(4, 0.1, ny=3, nz=5, T_lo=300.0, T_hi=1800.0, x=x, p=1.1, T_wall=T_wall)
+    L = I.line_list(300, 999.0, 1001.0 + n_nu * dnu, seed=4, dnu=dnu, n_nu=n_nu)
+    w = I.Workload("edges", g, L, 300, 6)
+    print(f"n_nu {n_nu} dnu {dnu} x {x}", flush=True)
+    _check(_run(rt, w), O.run(g, L, w.n_rays, seed=w.seed))
