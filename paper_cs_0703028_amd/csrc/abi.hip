@@ -126,16 +126,8 @@ bool finite_all(const double* a, int64_t n) {
 }
 
 void free_lineset(rt::LineSet& L) {
-  dev_free(L.m); dev_free(L.phi); dev_free(L.wlo); dev_free(L.whi); dev_free(L.S);
-  dev_free(L.E2); dev_free(L.nu); dev_free(L.gamma); dev_free(L.nexp); dev_free(L.prof16);
-  dev_free(L.tile16);
-  dev_free(L.span4);
-  dev_free(L.r64); dev_free(L.S64); dev_free(L.g64); dev_free(L.n64);
-  dev_free(L.aE); dev_free(L.rN);
-  dev_free(L.E2p); dev_free(L.nup);
-  L.n = 0;
-  L.n_tiles16 = 0;
-  L.n_spans = 0;
+  dev_free(L.block);
+  L = rt::LineSet();
 }
 
 void free_lines(rt_ctx c) { free_lineset(c->lines); }
@@ -485,27 +477,6 @@ rt_status build_lines(rt_ctx c, const char* who, int n_lines, const double* nu, 
     haE[k] = E ? -c2 * E[i] : 0.0;
     hrN[k] = 1.0 / std::expm1(-c2 * nu[i] / T_ref);
   }
-  RT_HIP(c, dev_alloc(&L.m, nl));
-  RT_HIP(c, dev_alloc(&L.phi, nl));
-  RT_HIP(c, dev_alloc(&L.wlo, nl));
-  RT_HIP(c, dev_alloc(&L.whi, nl));
-  RT_HIP(c, dev_alloc(&L.S, nl));
-  RT_HIP(c, dev_alloc(&L.E2, nl));
-  RT_HIP(c, dev_alloc(&L.nu, nl));
-  RT_HIP(c, dev_alloc(&L.gamma, nl));
-  RT_HIP(c, dev_alloc(&L.nexp, nl));
-  RT_HIP(c, dev_alloc(&L.prof16, (size_t)nl * 16));
-  RT_HIP(c, dev_alloc(&L.E2p, nl));
-  RT_HIP(c, dev_alloc(&L.nup, nl));
-  {
-    double** d64[6] = {&L.r64, &L.S64, &L.g64, &L.n64, &L.aE, &L.rN};
-    const std::vector<double>* h64[6] = {&hr64, &hS64, &hg64, &hn64, &haE, &hrN};
-    for (int k = 0; k < 6; ++k) {
-      RT_HIP(c, dev_alloc(d64[k], nl));
-      if (nl > 0)
-        RT_HIP(c, hipMemcpy(*d64[k], h64[k]->data(), nl * sizeof(double), hipMemcpyHostToDevice));
-    }
-  }
   // per 256-point tile, the lines with m in [256 t - 8, 256 t + 255 + 7]
   const int n_t16 = (n_nu + 255) / 256;
   std::vector<int2> ht16(n_t16);
@@ -515,41 +486,73 @@ rt_status build_lines(rt_ctx c, const char* who, int n_lines, const double* nu, 
     while (hi < nl && hm[hi] <= 256 * t + 262) ++hi;
     ht16[t] = make_int2(lo, hi);
   }
-  RT_HIP(c, dev_alloc(&L.tile16, (size_t)n_t16));
-  RT_HIP(c, hipMemcpy(L.tile16, ht16.data(), (size_t)n_t16 * sizeof(int2), hipMemcpyHostToDevice));
-  L.n_tiles16 = n_t16;
   // per 64-point span, the four line-range bounds of LineSet::span4 (the
   // window bounds are non-decreasing along the sorted list)
   const int n_sp = (nl > 0 ? std::max(0, hwhi[nl - 1]) : 0) / 64 + 2;
-  std::vector<int4> hsp(n_sp);
-  for (int b = 0; b < n_sp; ++b) {
-    const int v0 = 64 * b, v1 = 64 * b + 63;
-    auto ge = [&](const std::vector<int32_t>& a, int v) {
-      return (int)(std::lower_bound(a.begin(), a.end(), v) - a.begin());
+  std::vector<int4> hsp(3 * (size_t)n_sp);
+  {
+    // one pass: every bound moves forward with the span
+    int p[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    auto advance = [&](int& k, const std::vector<int32_t>& a, int v) {  // first with a >= v
+      while (k < nl && a[k] < v) ++k;
+      return k;
     };
-    auto gt = [&](const std::vector<int32_t>& a, int v) {
-      return (int)(std::upper_bound(a.begin(), a.end(), v) - a.begin());
-    };
-    hsp[b] = make_int4(ge(hwhi, v0), gt(hwlo, v1), ge(hwhi, v1), gt(hwlo, v0));
+    for (int b = 0; b < n_sp; ++b) {
+      const int v0 = 64 * b;
+      hsp[b] = make_int4(advance(p[0], hwhi, v0), advance(p[1], hwlo, v0 + 64),
+                         advance(p[2], hwhi, v0 + 63), advance(p[3], hwlo, v0 + 1));
+      hsp[n_sp + b] = make_int4(advance(p[4], hm, v0 - rt::kFarBelow + 1),
+                                advance(p[5], hm, v0 + rt::kFarAbove),
+                                advance(p[6], hwhi, v0 + 32), advance(p[7], hwlo, v0 + 32));
+      hsp[2 * n_sp + b] = make_int4(advance(p[8], hm, 2 * v0 - rt::kPairBelow + 1),
+                                    advance(p[9], hm, 2 * v0 + rt::kPairAbove), 0, 0);
+    }
   }
-  RT_HIP(c, dev_alloc(&L.span4, (size_t)n_sp));
-  RT_HIP(c, hipMemcpy(L.span4, hsp.data(), (size_t)n_sp * sizeof(int4), hipMemcpyHostToDevice));
+  // every array in one allocation
+  struct Place {
+    void** dst;
+    const void* src;
+    size_t bytes, off;
+  };
+  std::vector<Place> place;
+  size_t total = 0;
+  auto put = [&](auto*& dst, const void* src, size_t bytes) {
+    place.push_back({reinterpret_cast<void**>(&dst), src, bytes, total});
+    total += (bytes + 255) / 256 * 256;
+  };
+  put(L.data, nullptr, nl * sizeof(rt::LineData));  // gathered on the device, below
+  put(L.m, hm.data(), nl * sizeof(int32_t));
+  put(L.phi, hphi.data(), nl * sizeof(float));
+  put(L.wlo, hwlo.data(), nl * sizeof(int32_t));
+  put(L.whi, hwhi.data(), nl * sizeof(int32_t));
+  put(L.S, hS.data(), nl * sizeof(float));
+  put(L.E2, hE2.data(), nl * sizeof(double));
+  put(L.nu, hnu.data(), nl * sizeof(double));
+  put(L.gamma, hg.data(), nl * sizeof(float));
+  put(L.nexp, hn.data(), nl * sizeof(float));
+  put(L.prof16, hprof.data(), (size_t)nl * 16 * sizeof(float));
+  put(L.E2p, hE2p.data(), nl * sizeof(float2));
+  put(L.nup, hnup.data(), nl * sizeof(float2));
+  put(L.r64, hr64.data(), nl * sizeof(double));
+  put(L.S64, hS64.data(), nl * sizeof(double));
+  put(L.g64, hg64.data(), nl * sizeof(double));
+  put(L.n64, hn64.data(), nl * sizeof(double));
+  put(L.aE, haE.data(), nl * sizeof(double));
+  put(L.rN, hrN.data(), nl * sizeof(double));
+  put(L.tile16, ht16.data(), ht16.size() * sizeof(int2));
+  put(L.span4, hsp.data(), hsp.size() * sizeof(int4));
+  RT_HIP(c, dev_alloc(&L.block, total));
+  for (const Place& q : place) {
+    *q.dst = L.block + q.off;
+    if (q.src && q.bytes)
+      RT_HIP(c, hipMemcpy(L.block + q.off, q.src, q.bytes, hipMemcpyHostToDevice));
+  }
+  L.span_far = L.span4 + n_sp;
+  L.span_pair = L.span_far + n_sp;
+  L.n_tiles16 = n_t16;
   L.n_spans = n_sp;
-  if (nl > 0) {
-    RT_HIP(c, hipMemcpy(L.prof16, hprof.data(), (size_t)nl * 16 * sizeof(float), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.m, hm.data(), nl * sizeof(int32_t), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.phi, hphi.data(), nl * sizeof(float), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.wlo, hwlo.data(), nl * sizeof(int32_t), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.whi, hwhi.data(), nl * sizeof(int32_t), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.S, hS.data(), nl * sizeof(float), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.E2, hE2.data(), nl * sizeof(double), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.nu, hnu.data(), nl * sizeof(double), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.gamma, hg.data(), nl * sizeof(float), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.nexp, hn.data(), nl * sizeof(float), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.E2p, hE2p.data(), nl * sizeof(float2), hipMemcpyHostToDevice));
-    RT_HIP(c, hipMemcpy(L.nup, hnup.data(), nl * sizeof(float2), hipMemcpyHostToDevice));
-  }
   L.n = nl;
+  RT_HIP(c, rt::launch_line_data(c, L));
   return RT_OK;
 }
 

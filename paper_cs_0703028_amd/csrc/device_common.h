@@ -137,6 +137,20 @@ __device__ __forceinline__ void two_sum_acc(float& s, float& comp, float x) {
   comp += err;
 }
 
+// ---------------------------------------------------- wavefront reductions
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int2 h = *reinterpret_cast<int2*>(&v);
+  int2 r;
+  r.x = __builtin_amdgcn_update_dpp(0, h.x, CTRL, ROW_MASK, 0xf, false);
+  r.y = __builtin_amdgcn_update_dpp(0, h.y, CTRL, ROW_MASK, 0xf, false);
+  return *reinterpret_cast<double*>(&r);
+}
+
 // ------------------------------------------------------------ line records
 // A staged line: (m, phi, lo, hi) -- the integer centre, the fraction, and
 // the first and last offsets from m of the points the line contributes to
@@ -145,17 +159,29 @@ __device__ __forceinline__ void two_sum_acc(float& s, float& comp, float x) {
 // adds A / ((j - m - phi)^2 + g2) at point j.
 constexpr int kLineRec = 4 + 2 * kKappaCells;  // floats per staged line
 
-// The per-cell part of a record for line i and cell `cell` (Eqs. (1)-(2)).
-__device__ __forceinline__ void line_cell_params(const LineSet& L, const CellSet& C, int i,
-                                                 int64_t cell, int have_E, float& amp, float& g2) {
-  const float gp = L.gamma[i] * C.P[cell] * fast_exp2(L.nexp[i] * C.lam2[cell]);
-  float a = C.G[cell] * L.S[i] * gp;
+// The per-cell part of a record (Eqs. (1)-(2)) from a line's data and a
+// cell's factors.
+struct CellFactors {
+  double beta, theta;
+  float G, P, lam2;
+};
+__device__ __forceinline__ void line_cell_params(const LineData& d, const CellFactors& c,
+                                                 int have_E, float& amp, float& g2) {
+  const float gp = d.gamma * c.P * fast_exp2(d.nexp * c.lam2);
+  float a = c.G * d.S * gp;
   if (have_E) {
-    a *= exp_split(L.E2[i] * C.beta[cell]);
-    a *= one_minus_exp_neg_d(L.nu[i] * C.theta[cell]);
+    a *= exp_split(d.E2 * c.beta);
+    a *= one_minus_exp_neg_d(d.nu * c.theta);
   }
   amp = a;
   g2 = gp * gp;
+}
+__device__ __forceinline__ void line_cell_params(const LineSet& L, const CellSet& C, int i,
+                                                 int64_t cell, int have_E, float& amp, float& g2) {
+  line_cell_params(LineData{0.f, 0.f, 0.f, L.S[i], L.gamma[i], L.nexp[i], 0.f, 0.f,
+                            have_E ? L.E2[i] : 0.0, have_E ? L.nu[i] : 0.0},
+                   CellFactors{C.beta[cell], C.theta[cell], C.G[cell], C.P[cell], C.lam2[cell]},
+                   have_E, amp, g2);
 }
 
 // The same record in FP32 only (the precision form): the Eq. (1) factors from
@@ -205,7 +231,7 @@ __device__ __forceinline__ void add_line_terms(const float* rec, const float (&j
 }
 
 // ------------------------------------------------------------ line sum tile
-// Eq. (2) with the Eq. (1) strength ratio for one block: nu points
+// The compensated sum.  Eq. (2) with the Eq. (1) strength ratio for one block: nu points
 // [j0, j0 + 512) x kKappaCells cells starting at cell0.  Wave w owns the
 // points j0 + 128 w + 64 p + lane (p < 2).  Lines whose window meets the
 // block's points are staged kLineTile at a time as line records (m, phi,
@@ -254,14 +280,11 @@ struct TileGate {
   int n_chunks = 0;
 };
 
-// F32: line records from line_cell_params_f32 (the precision form).
-// active (uniform over the wavefront): false leaves this wavefront's points
-// untouched; it still stages line records with the others.  P: points per
-// lane (the tile is 256 P points); every point's sum runs over the same
-// lines in the same order whatever P is, so the values do not depend on it.
-template <bool COMP, bool F32 = false, int P = kKappaPoints>
-__device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds,
-                           bool active = true) {
+// Compensated: blocks of 16 lines are summed plainly and folded in with
+// TwoSum.  F32: line records from line_cell_params_f32 (the precision form).
+template <bool F32>
+__device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds) {
+  constexpr int P = kKappaPoints;
   constexpr int C = kKappaCells;
   constexpr int REC = kLineRec;
   const int tid = threadIdx.x;
@@ -276,13 +299,8 @@ __device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds
   auto bound = [&](int b, int k) {  // field k of span b (all n past the table)
     return b < a.L.n_spans ? reinterpret_cast<const int*>(a.L.span4)[4 * b + k] : nl;
   };
-  int blk_first = bound(j0 / 64, 0);
-  int blk_end = bound((j0 + kKappaThreads * P - 1) / 64, 1);
-  if (a.line_parts > 1) {
-    const int share = (blk_end - blk_first + a.line_parts - 1) / a.line_parts;
-    blk_first = min(blk_end, blk_first + a.line_part * share);
-    blk_end = min(blk_end, blk_first + share);
-  }
+  const int blk_first = bound(j0 / 64, 0);
+  const int blk_end = bound((j0 + kKappaThreads * P - 1) / 64, 1);
   const int wb0 = wj0 / 64, wb1 = (wj0 + span - 1) / 64;
   const int w_first = bound(wb0, 0);
   const int w_end = bound(wb1, 1);
@@ -305,25 +323,21 @@ __device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds
 
   // Adds lines [l0, l1) of the staged tile starting at line `base`.  FULL:
   // every point is inside the window.  Otherwise a point outside it gets an
-  // infinite offset, whose reciprocal term is 0.  COMP: blocks of 16 lines
-  // are summed plainly and folded into (acc, cmp) with TwoSum.
+  // infinite offset, whose reciprocal term is 0.
   auto sum_lines = [&](auto full_tag, int base, int l0, int l1) {
     constexpr bool FULL = decltype(full_tag)::value;
     for (int s0 = l0; s0 < l1;) {
-      const int s1 = COMP ? min(s0 + 16, l1) : l1;
+      const int s1 = min(s0 + 16, l1);
       float part[P][C];
 #pragma unroll
       for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int c = 0; c < C; ++c) part[p][c] = COMP ? 0.f : acc[p][c];
+        for (int c = 0; c < C; ++c) part[p][c] = 0.f;
       for (int l = s0; l < s1; ++l) add_line_terms<FULL, P>(lds + (l - base) * REC, jf, part);
 #pragma unroll
       for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-          if (COMP) two_sum_acc(acc[p][c], cmp[p][c], part[p][c]);
-          else acc[p][c] = part[p][c];
-        }
+        for (int c = 0; c < C; ++c) two_sum_acc(acc[p][c], cmp[p][c], part[p][c]);
       s0 = s1;
     }
   };
@@ -351,7 +365,6 @@ __device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds
     }
     __syncthreads();
 
-    if (!active) continue;
     const int lb = max(base, w_first), le = min(base + nt, w_end);
     // lines [f_first, f_end) cover all of the wave's points: no membership test
     const int fb = min(le, max(lb, f_first)), fe = max(fb, min(le, f_end));
@@ -359,7 +372,6 @@ __device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds
     sum_lines(std::true_type(), base, fb, fe);
     sum_lines(std::false_type(), base, fe, le);
   }
-  if (!active) return;
 
 #pragma unroll
   for (int c = 0; c < C; ++c) {
@@ -370,11 +382,397 @@ __device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds
     for (int p = 0; p < P; ++p) {
       const int64_t j = wj0 + 64 * p + lane;
       if (j >= a.col0 && j < a.col_end) {
-        const float v = COMP ? acc[p][c] + cmp[p][c] : acc[p][c];
+        const float v = acc[p][c] + cmp[p][c];
         float* o = a.out + cell * a.ld_out + (j - a.col0);
         *o = (j < a.n_nu) ? (a.accumulate ? *o + v : v) : 0.f;
       }
     }
+  }
+}
+
+// ------------------------------------------- line sum tile with far nodes
+// The plain form's line sum.  Over a span of the grid a line whose window
+// covers the span and whose centre lies far enough from the span's middle is
+// smooth: it is evaluated at kFarNodes Chebyshev nodes of the span instead of
+// at its points, and the nodes' sum over all such lines is interpolated once.
+// Two levels: pairs of spans (128 points, centres at least 170.5 points from
+// the middle) and spans (64 points, 84.5 points).  A pair's nodes are
+// interpolated to the nodes of its two spans, theirs to the points.  With 12
+// nodes of half width 31.6 (63.7) the interpolant of any A / (d^2 + g^2) is
+// within 1.1e-7 of its value at the reach (poles at distance g from the real
+// axis only help) and falls by a factor 10 per 12 points beyond it: below the
+// reciprocal's rounding that every direct term carries.  Lines nearer, and
+// those whose window ends inside the span, are summed point by point.
+//
+// Instructions per line and span of 8 cells: 28 point by point, 7 at a span's
+// nodes, 3.5 at a pair's.  In a window of 1,001 points (cutoff 5 cm^-1 at
+// 0.01) 16% of the lines that meet a span are near, 12% end inside it, 22%
+// are at its nodes and 50% at the pair's.
+//
+// Issue-bound, as the sum at every point was, on 0.96 of the SIMD cycles.
+// 24^3 cells, 20,000 points, 5,000 lines: 7.86 -> 3.38 ms, error against 64
+// bits 3.1e-7 -> 1.5e-7 (fewer, shorter FP32 sums); 8^3 cells, 10,000 points,
+// 20,000 lines: 1.85 -> 0.76 ms, 2.7e-6 -> 5.4e-7.  With the spans' level
+// alone 3.80 and 0.94 ms.
+constexpr int kFarNodes = 12;
+
+struct FarTables {
+  float node[2][kFarNodes];                       // offsets from the middle: span, pair
+  alignas(16) float weight[64][kFarNodes];        // span's nodes -> its points
+  alignas(16) float down[2][kFarNodes][kFarNodes];  // pair's nodes -> each span's nodes
+};
+constexpr FarTables make_far_tables() {
+  // cos((2 k + 1) pi / 24)
+  constexpr double c[6] = {0.99144486137381041, 0.92387953251128674, 0.79335334029123517,
+                           0.60876142900872064, 0.38268343236508978, 0.13052619222005159};
+  FarTables t{};
+  double x[2][kFarNodes] = {};
+  for (int v = 0; v < 2; ++v)
+    for (int k = 0; k < 6; ++k) {
+      x[v][k] = -(v ? 63.7 : 31.6) * c[k];
+      x[v][kFarNodes - 1 - k] = (v ? 63.7 : 31.6) * c[k];
+    }
+  for (int v = 0; v < 2; ++v)
+    for (int i = 0; i < kFarNodes; ++i) t.node[v][i] = (float)x[v][i];
+  for (int i = 0; i < kFarNodes; ++i) {
+    for (int j = 0; j < 64; ++j) {
+      double w = 1.0;
+      for (int k = 0; k < kFarNodes; ++k)
+        if (k != i) w *= ((double)j - 31.5 - x[0][k]) / (x[0][i] - x[0][k]);
+      t.weight[j][i] = (float)w;
+    }
+    for (int h = 0; h < 2; ++h)
+      for (int j = 0; j < kFarNodes; ++j) {
+        double w = 1.0;
+        for (int k = 0; k < kFarNodes; ++k)
+          if (k != i) w *= (x[0][j] + (h ? 32.0 : -32.0) - x[1][k]) / (x[1][i] - x[1][k]);
+        t.down[h][j][i] = (float)w;
+      }
+  }
+  return t;
+}
+static __device__ const FarTables far_tables = make_far_tables();
+constexpr int kFarRef = kFarNodes / 2;  // the node the others are taken relative to
+constexpr int kFarValues = kFarNodes * kKappaCells;
+constexpr int kFarEntries = 2 * kFarValues + kKappaCells;  // LDS floats per wavefront
+
+__device__ __forceinline__ void half_swap(float& a, float& b) {  // a's upper and b's lower half
+  typedef unsigned U2 __attribute__((ext_vector_type(2)));
+  const U2 r = __builtin_amdgcn_permlane32_swap((unsigned)__float_as_int(a),
+                                                (unsigned)__float_as_int(b), false, false);
+  a = __int_as_float((int)r.x);
+  b = __int_as_float((int)r.y);
+}
+__device__ __forceinline__ void row_swap(float& a, float& b) {   // a's odd and b's even rows
+  typedef unsigned U2 __attribute__((ext_vector_type(2)));
+  const U2 r = __builtin_amdgcn_permlane16_swap((unsigned)__float_as_int(a),
+                                                (unsigned)__float_as_int(b), false, false);
+  a = __int_as_float((int)r.x);
+  b = __int_as_float((int)r.y);
+}
+
+// Lane (s, c) = (lane >> 3, lane & 7) holds chain s of cell c for every node.
+// Adds the eight chains, two nodes at a time, halving the registers at each
+// step: lo gets node lane >> 3 of cell c, hi node 8 + (lane >> 3 & 3).
+__device__ __forceinline__ void far_reduce(const float (&F)[kFarNodes], int lane, float& lo,
+                                           float& hi) {
+  float g[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    const float a = F[2 * i] + dpp_f32<0x128>(F[2 * i]);  // row_ror:8
+    const float b = F[2 * i + 1] + dpp_f32<0x128>(F[2 * i + 1]);
+    g[i] = (lane & 8) ? b : a;
+  }
+  float s[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    row_swap(g[2 * i], g[2 * i + 1]);
+    s[i] = g[2 * i] + g[2 * i + 1];
+  }
+  half_swap(s[0], s[1]);
+  lo = s[0] + s[1];
+  float t = s[2];
+  half_swap(s[2], t);
+  hi = s[2] + t;
+}
+
+// What a half of a span takes of a line: nothing, every point, the points
+// from the window's first, up to its last, or within it.
+constexpr int kNone = 0, kAll = 1, kFrom = 2, kUpTo = 3, kWithin = 4;
+template <int M>
+using Take = std::integral_constant<int, M>;
+
+// As kappa_tile for the plain form: points [j0, j0 + 256 SP) x kKappaCells
+// cells; each wavefront owns SP spans of 64 points.  Point by point a lane
+// takes points pt and pt + 32 of a span for 4 of the cells (2 LDS reads of
+// parameters per line, where one point of 8 cells would take 4 and leave the
+// LDS the bound); at the nodes it takes every eighth line for one cell.  A
+// point's sum runs over the same lines in the same order, and a node's over
+// the same lines in the same eight chains (by line index modulo 8), whatever
+// SP and the staging are, so the values do not depend on them.
+// lds: kLineTile * kLineRec floats; fx: this wavefront's kFarEntries floats.
+// active (uniform over the wavefront): false leaves this wavefront's points
+// untouched; it still stages line records with the others.
+template <int SP>
+__device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float* lds, float* fx,
+                               bool active = true) {
+  constexpr int C = kKappaCells;
+  static_assert(kLineRec == 4 + 2 * C && 64 == 8 * C, "headers, then parameters of 8 cells");
+  static_assert(SP == 1 || SP % 2 == 0, "a wavefront's spans are one of a pair, or whole pairs");
+  constexpr FarTables tab = make_far_tables();
+  constexpr int NP = (SP + 1) / 2;  // pairs a wavefront's spans lie in
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int pt = lane & 31, cg = lane >> 5;
+  const int nl = a.L.n;
+  auto bound = [&](const int4* table, int b, int k) {  // a scalar load: b is uniform
+    return b < a.L.n_spans ? reinterpret_cast<const __attribute__((address_space(4))) int*>(
+                                 reinterpret_cast<uintptr_t>(table))[4 * b + k]
+                           : nl;
+  };
+  int blk_first = bound(a.L.span4, j0 / 64, 0);
+  int blk_end = bound(a.L.span4, (j0 + kKappaThreads * SP - 1) / 64, 1);
+  if (a.line_parts > 1) {
+    const int share = (blk_end - blk_first + a.line_parts - 1) / a.line_parts;
+    blk_first = min(blk_end, blk_first + a.line_part * share);
+    blk_end = min(blk_end, blk_first + share);
+  }
+  // cuts of the sorted list.  Per pair: the lines at its nodes, [p0, p1) below
+  // and [p2, p3) above.  Per span: lines ending inside it [x, c0), of which
+  // [x, h0) meet its lower half only and [x, s0) also start at or before it
+  // (all, but for windows narrower than the span); covering ones [c0, c1), of
+  // which [m0, m1) are near; starting inside it [c1, y), of which [h1, y) meet
+  // its upper half only
+  struct Pair4 {
+    int p0, p1, p2, p3;
+  } pair[NP];
+  struct Cuts {
+    int x, h0, s0, c0, m0, m1, c1, h1, y;
+  } cut[SP];
+  const int wj0 = j0 + wave * 64 * SP;
+#pragma unroll
+  for (int v = 0; v < NP; ++v) {
+    const int b = (wj0 / 128 + v) * 2;
+    Pair4 q;
+    q.p1 = bound(a.L.span_pair, b / 2, 0);
+    q.p0 = min(bound(a.L.span4, b + 1, 2), q.p1);
+    q.p2 = bound(a.L.span_pair, b / 2, 1);
+    q.p3 = max(bound(a.L.span4, b, 3), q.p2);
+    pair[v] = q;
+  }
+#pragma unroll
+  for (int p = 0; p < SP; ++p) {
+    const int b = wj0 / 64 + p;
+    Cuts q;
+    q.x = bound(a.L.span4, b, 0);
+    q.y = bound(a.L.span4, b, 1);
+    q.c0 = min(max(bound(a.L.span4, b, 2), q.x), q.y);
+    q.c1 = max(q.c0, min(bound(a.L.span4, b, 3), q.y));
+    q.m0 = min(max(bound(a.L.span_far, b, 0), q.c0), q.c1);
+    q.m1 = min(max(bound(a.L.span_far, b, 1), q.m0), q.c1);
+    q.s0 = min(max(bound(a.L.span4, b, 3), q.x), q.c0);
+    q.h0 = min(max(bound(a.L.span_far, b, 2), q.x), q.s0);
+    q.h1 = min(max(bound(a.L.span_far, b, 3), q.c1), q.y);
+    cut[p] = q;
+  }
+
+  float acc[SP][2][4];
+  float F[SP][kFarNodes], F2[NP][kFarNodes];
+#pragma unroll
+  for (int p = 0; p < SP; ++p) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[p][h][c] = 0.f;
+#pragma unroll
+    for (int n = 0; n < kFarNodes; ++n) F[p][n] = 0.f;
+  }
+#pragma unroll
+  for (int v = 0; v < NP; ++v)
+#pragma unroll
+    for (int n = 0; n < kFarNodes; ++n) F2[v][n] = 0.f;
+
+  // staging: a thread forms the parameters of every 32nd line for one cell,
+  // whose factors it keeps; headers (m, phi, lo, hi) and parameters lie apart,
+  // so that eight lines' parameters of eight cells are 512 contiguous bytes
+  float4* hdr = reinterpret_cast<float4*>(lds);
+  float2* par = reinterpret_cast<float2*>(lds + 4 * kLineTile);
+  const int cc = tid % C;
+  CellFactors cf;
+  {
+    int64_t scell = cell0 + cc;
+    if (scell >= a.n_cells) scell = a.n_cells - 1;
+    if (a.cell_list) scell = a.cell_list[scell];
+    cf = CellFactors{a.C.beta[scell], a.C.theta[scell], a.C.G[scell], a.C.P[scell],
+                     a.C.lam2[scell]};
+  }
+
+  for (int base = blk_first & ~7; base < blk_end; base += kLineTile) {
+    const int nt = min(kLineTile, blk_end - base);
+    __syncthreads();
+#pragma unroll 2
+    for (int li = tid / C; li < nt; li += kKappaThreads / C) {
+      const LineData d = a.L.data[base + li];
+      if (cc == 0) hdr[li] = make_float4(d.m, d.phi, d.lo, (float)a.K);
+      float amp, g2;
+      line_cell_params(d, cf, a.have_E, amp, g2);
+      par[li * C + cc] = make_float2(amp, g2);
+    }
+    __syncthreads();
+    if (!active) continue;
+    const int first = max(base, blk_first), end = base + nt;
+    // lines [l0, l1) at the nodes `node` about the point v0 + mid
+    auto far = [&](float (&f)[kFarNodes], const float (&node)[kFarNodes], float v0, float mid,
+                   int l0, int l1) {
+      l0 = __builtin_amdgcn_readfirstlane(max(l0, first) - base);
+      l1 = __builtin_amdgcn_readfirstlane(min(l1, end) - base);
+      for (int l8 = l0 & ~7; l8 < l1; l8 += 8) {  // base: a multiple of 8
+        const int l = l8 + (lane >> 3);
+        if (l >= l0 && l < l1) {
+          const float2 h = *reinterpret_cast<const float2*>(hdr + l);
+          const float2 ag = par[l8 * C + lane];
+          const float e = ((h.x - v0) - mid) + h.y;  // the centre from the middle
+#pragma unroll
+          for (int n = 0; n < kFarNodes; ++n) {
+            const float d = node[n] - e;
+            f[n] = fmaf(ag.x, fast_rcp(fmaf(d, d, ag.y)), f[n]);
+          }
+        }
+      }
+    };
+#pragma unroll
+    for (int v = 0; v < NP; ++v) {
+      const float v0 = (float)((wj0 / 128 + v) * 128);
+      far(F2[v], tab.node[1], v0, 63.5f, pair[v].p0, pair[v].p1);
+      far(F2[v], tab.node[1], v0, 63.5f, pair[v].p2, pair[v].p3);
+    }
+#pragma unroll
+    for (int p = 0; p < SP; ++p) {
+      const float v0 = (float)(wj0 + 64 * p);
+      const float jl = v0 + (float)pt, ju = jl + 32.f;
+      // lines [l0, l1) point by point: what the lower and the upper half take
+      // of them
+      auto direct = [&](auto lower, auto upper, int l0, int l1) {
+        l0 = __builtin_amdgcn_readfirstlane(max(l0, first) - base);
+        l1 = __builtin_amdgcn_readfirstlane(min(l1, end) - base);
+        for (int l = l0; l < l1; ++l) {
+          const float4 h = hdr[l];
+          const float4* g = reinterpret_cast<const float4*>(par + l * C + 4 * cg);
+          const float4 g0 = g[0], g1 = g[1];
+          auto add = [&](auto take, float j, float (&s)[4]) {
+            constexpr int M = decltype(take)::value;
+            if constexpr (M == kNone) return;
+            const float t = j - h.x;
+            float d = t - h.y;
+            if (M == kFrom) d = t >= h.z ? d : __builtin_inff();
+            if (M == kUpTo) d = t <= h.w ? d : __builtin_inff();
+            if (M == kWithin) d = ((t >= h.z) & (t <= h.w)) ? d : __builtin_inff();
+            s[0] = fmaf(g0.x, fast_rcp(fmaf(d, d, g0.y)), s[0]);
+            s[1] = fmaf(g0.z, fast_rcp(fmaf(d, d, g0.w)), s[1]);
+            s[2] = fmaf(g1.x, fast_rcp(fmaf(d, d, g1.y)), s[2]);
+            s[3] = fmaf(g1.z, fast_rcp(fmaf(d, d, g1.w)), s[3]);
+          };
+          add(lower, jl, acc[p][0]);
+          add(upper, ju, acc[p][1]);
+        }
+      };
+      const Cuts& q = cut[p];
+      const Pair4& r = pair[p / 2];
+      direct(Take<kUpTo>(), Take<kNone>(), q.x, q.h0);
+      direct(Take<kAll>(), Take<kUpTo>(), q.h0, q.s0);
+      direct(Take<kWithin>(), Take<kWithin>(), q.s0, q.c0);
+      far(F[p], tab.node[0], v0, 31.5f, q.c0, min(r.p0, q.m0));
+      far(F[p], tab.node[0], v0, 31.5f, max(r.p1, q.c0), q.m0);
+      direct(Take<kAll>(), Take<kAll>(), q.m0, q.m1);
+      far(F[p], tab.node[0], v0, 31.5f, q.m1, min(r.p2, q.c1));
+      far(F[p], tab.node[0], v0, 31.5f, max(r.p3, q.m1), q.c1);
+      direct(Take<kFrom>(), Take<kAll>(), q.c1, q.h1);
+      direct(Take<kNone>(), Take<kFrom>(), q.h1, q.y);
+    }
+  }
+  if (!active) return;
+
+  const int n_hi = 8 + ((lane >> 3) & 3);  // the node of far_reduce's hi
+#pragma unroll
+  for (int p = 0; p < SP; ++p) {
+    const Pair4& r = pair[p / 2];
+    const bool paired = r.p1 - r.p0 + r.p3 - r.p2 > 0;
+    if (!paired && cut[p].m0 - cut[p].c0 + cut[p].c1 - cut[p].m1 == 0) continue;  // no far line
+    if (paired && p % 2 == 0) {  // the pair's node sums, for both of its spans
+      float lo, hi;
+      far_reduce(F2[p / 2], lane, lo, hi);
+      __builtin_amdgcn_wave_barrier();
+      fx[kFarValues + lane] = lo;
+      if (lane < 32) fx[kFarValues + 64 + lane] = hi;
+      __builtin_amdgcn_wave_barrier();
+    }
+    float lo, hi;
+    far_reduce(F[p], lane, lo, hi);
+    if (paired) {
+      const int half = (wj0 / 64 + p) & 1;
+      const float* dl = far_tables.down[half][lane >> 3];
+      const float* dh = far_tables.down[half][n_hi];
+#pragma unroll
+      for (int k = 0; k < kFarNodes; ++k) {
+        const float f = fx[kFarValues + k * C + (lane & 7)];
+        lo = fmaf(dl[k], f, lo);
+        hi = fmaf(dh[k], f, hi);
+      }
+    }
+    // the nodes relative to one of them: the interpolation's rounding then
+    // scales with their differences
+    const float ref = __int_as_float(__builtin_amdgcn_ds_bpermute(
+        4 * (8 * kFarRef + (lane & 7)), __float_as_int(lo)));
+    __builtin_amdgcn_wave_barrier();
+    fx[lane] = lo - ref;
+    if (lane < 32) fx[64 + lane] = hi - ref;
+    if (lane < C) fx[2 * kFarValues + lane] = ref;
+    __builtin_amdgcn_wave_barrier();
+    float v[2][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[0][c] = v[1][c] = 0.f;
+#pragma unroll
+    for (int g = 0; g < kFarNodes / 4; ++g) {
+      const float4 wl = *reinterpret_cast<const float4*>(&far_tables.weight[pt][4 * g]);
+      const float4 wu = *reinterpret_cast<const float4*>(&far_tables.weight[pt + 32][4 * g]);
+      const float l4[4] = {wl.x, wl.y, wl.z, wl.w}, u4[4] = {wu.x, wu.y, wu.z, wu.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 f = *reinterpret_cast<const float4*>(fx + (4 * g + k) * C + 4 * cg);
+        const float f4[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          v[0][c] = fmaf(l4[k], f4[c], v[0][c]);
+          v[1][c] = fmaf(u4[k], f4[c], v[1][c]);
+        }
+      }
+    }
+    const float4 rf = *reinterpret_cast<const float4*>(fx + 2 * kFarValues + 4 * cg);
+    const float r4[4] = {rf.x, rf.y, rf.z, rf.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      acc[p][0][c] += r4[c] + v[0][c];
+      acc[p][1][c] += r4[c] + v[1][c];
+    }
+  }
+
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    int64_t cell = cell0 + 4 * cg + c;
+    if (cell >= a.n_cells) break;
+    if (a.cell_list && !a.compact_rows) cell = a.cell_list[cell];
+#pragma unroll
+    for (int p = 0; p < SP; ++p)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int64_t j = wj0 + 64 * p + 32 * h + pt;
+        if (j >= a.col0 && j < a.col_end) {
+          float* o = a.out + cell * a.ld_out + (j - a.col0);
+          const float v = acc[p][h][c];
+          *o = (j < a.n_nu) ? (a.accumulate ? *o + v : v) : 0.f;
+        }
+      }
   }
 }
 
@@ -537,20 +935,6 @@ __device__ inline uint32_t order_key(const int64_t O[3], const int64_t D[3], int
   const uint32_t q2 = (uint32_t)fmin(63.0, fmax(0.0, p2));
   const uint32_t dir = (uint32_t)((ax * 2 + (D[ax] > 0)) * 9 + b1 * 3 + b2);
   return dir * 4096u + (spread6(q1) | (spread6(q2) << 1));
-}
-
-// ---------------------------------------------------- wavefront reductions
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ float dpp_f32(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
-}
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int2 h = *reinterpret_cast<int2*>(&v);
-  int2 r;
-  r.x = __builtin_amdgcn_update_dpp(0, h.x, CTRL, ROW_MASK, 0xf, false);
-  r.y = __builtin_amdgcn_update_dpp(0, h.y, CTRL, ROW_MASK, 0xf, false);
-  return *reinterpret_cast<double*>(&r);
 }
 
 // a = 1 - e^{-tau} for tau >= 0, two accuracy levels.

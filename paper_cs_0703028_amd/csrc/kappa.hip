@@ -2,8 +2,8 @@
 //
 //   cell_params   : per-cell gas state -> FP32/FP64 factors (FP64 arithmetic)
 //   kappa_linesum : Eq. (2) with the Eq. (1) strength ratio (line tiles staged
-//                   in LDS, each lane owns 2 nu points of 8 cells, kappa
-//                   written coalesced along nu; see dev::kappa_tile)
+//                   in LDS, kappa written coalesced along nu): plain
+//                   (dev::kappa_tile_far) and compensated (dev::kappa_tile)
 //   planck_table  : Eq. (4), wavenumber form, per (cell, nu) and for the walls,
 //                   evaluated in FP32 (pair arguments, exp_pair/expm1_pair)
 #include "batch_plan.h"
@@ -40,6 +40,14 @@ __global__ void cell_params_kernel(int64_t n, const double* __restrict__ T,
   P[c] = (float)(p[c] / dnu);
 }
 
+// The plain line sum's records of a line list, from its arrays.
+__global__ void line_data_kernel(LineSet L) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= L.n) return;
+  L.data[i] = LineData{(float)L.m[i], L.phi[i], (float)(L.wlo[i] - L.m[i]), L.S[i], L.gamma[i],
+                       L.nexp[i], 0.f, 0.f, L.E2[i], L.nu[i]};
+}
+
 // The precision form's Gq = u q / (pi dnu) per cell, in FP32: u/(pi dnu) and
 // log2(T_ref/T) come from the host, q = 2^(1.5 log2(T_ref/T)) with energies
 // (the partition ratio of Eq. (1)), 1 without.
@@ -68,12 +76,20 @@ struct KappaArgs {
   int64_t part_stride = 0;   // floats between the shares' outputs
 };
 
-// The plain sum is held to 64 registers (eight wavefronts per SIMD), the
-// compensated one needs more.
 template <bool COMP, bool F32 = false, int P = kKappaPoints>
 __global__ __launch_bounds__(kKappaThreads)
-__attribute__((amdgpu_waves_per_eu(COMP ? 1 : 8))) void kappa_linesum_kernel(KappaArgs a) {
-  __shared__ float4 lds4[kLineTile * (4 + 2 * kKappaCells) / 4];
+__attribute__((amdgpu_waves_per_eu(COMP ? 1 : 5))) void kappa_linesum_kernel(KappaArgs a) {
+  __shared__ float4 lds4[kLineTile * kLineRec / 4];
+  __shared__ float4 fx4[COMP ? 1 : kKappaThreads / 64 * kFarEntries / 4];
+  auto sum_tile = [&](const KappaTile& t, int j0, int64_t cell0, bool on) {
+    float* lds = reinterpret_cast<float*>(lds4);
+    if constexpr (COMP) {
+      kappa_tile<F32>(t, j0, cell0, lds);
+    } else {
+      const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      kappa_tile_far<P>(t, j0, cell0, lds, reinterpret_cast<float*>(fx4) + wave * kFarEntries, on);
+    }
+  };
   const int part = (int)(blockIdx.x % (unsigned)a.parts);
   const int64_t tb = blockIdx.x / (unsigned)a.parts;
   const int tile = (int)(tb % a.n_tiles);
@@ -106,10 +122,10 @@ __attribute__((amdgpu_waves_per_eu(COMP ? 1 : 8))) void kappa_linesum_kernel(Kap
     t.line_parts = a.parts;
     t.line_part = part;
     t.out += part * a.part_stride;
-    kappa_tile<COMP, F32, P>(t, j0, cg * kKappaCells, reinterpret_cast<float*>(lds4), wave_on);
+    sum_tile(t, j0, cg * kKappaCells, wave_on);
     return;
   }
-  kappa_tile<COMP, F32, P>(a.t, j0, cg * kKappaCells, reinterpret_cast<float*>(lds4), wave_on);
+  sum_tile(a.t, j0, cg * kKappaCells, wave_on);
 }
 
 // Planck table: one block per (cell, 256-point segment of the row).
@@ -260,6 +276,13 @@ hipError_t launch_kappa_table16(rt_ctx c) {
   return e;
 }
 
+hipError_t launch_line_data(rt_ctx c, const LineSet& L) {
+  if (L.n > 0)
+    hipLaunchKernelGGL(line_data_kernel, dim3((unsigned)((L.n + 255) / 256)), dim3(256), 0,
+                       c->stream, L);
+  return hipGetLastError();
+}
+
 hipError_t launch_cell_params(rt_ctx c) {
   const int64_t n = c->n_cells;
   const int threads = 256;
@@ -303,6 +326,29 @@ hipError_t launch_gas_factor(rt_ctx c, int g) {
   return hipGetLastError();
 }
 
+// The plain line sum of a.n_tiles tiles of kKappaTilePoints points for
+// `groups` groups of cells.  A block's latency sets the time of a launch that
+// fills the chip little more than once (five blocks fit a CU): below 6 blocks
+// per CU it is cut into tiles of half the points, with the same values bit for
+// bit (6^3 cells, 3,037 points, 162 blocks: 36 -> 30 us; 8^3, 10,000 points,
+// 1,344 blocks: 110 -> 104 us at 25 lines per cm^-1, 932 -> 753 us at 200,
+// 42 us either way at 5; 10^3, 2,625 blocks: 173 us against 176).
+static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
+  const int64_t blocks = groups * a.n_tiles * a.parts;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (blocks == 0) return hipSuccess;
+  if (blocks < 6 * 256) {
+    a.n_tiles *= 2;
+    a.tile_begin *= 2;
+    hipLaunchKernelGGL((kappa_linesum_kernel<false, false, 1>), dim3((unsigned)(2 * blocks)),
+                       dim3(kKappaThreads), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((kappa_linesum_kernel<false>), dim3((unsigned)blocks), dim3(kKappaThreads),
+                       0, s, a);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_kappa(rt_ctx c, bool compensated) {
   KappaArgs a;
   a.t.L = c->lines;
@@ -321,12 +367,10 @@ hipError_t launch_kappa(rt_ctx c, bool compensated) {
   const int64_t blocks = groups * a.n_tiles;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   auto launch = [&]() {
-    if (compensated)  // the precision form: FP32 line parameters
-      hipLaunchKernelGGL((kappa_linesum_kernel<true, true>), dim3((unsigned)blocks),
-                         dim3(kKappaThreads), 0, c->stream, a);
-    else
-      hipLaunchKernelGGL((kappa_linesum_kernel<false>), dim3((unsigned)blocks),
-                         dim3(kKappaThreads), 0, c->stream, a);
+    if (!compensated) return launch_plain(a, groups, c->stream);
+    // the precision form: FP32 line parameters
+    hipLaunchKernelGGL((kappa_linesum_kernel<true, true>), dim3((unsigned)blocks),
+                       dim3(kKappaThreads), 0, c->stream, a);
     return hipGetLastError();
   };
   hipError_t e = launch();
@@ -354,19 +398,16 @@ hipError_t launch_kappa_tiles(rt_ctx c, const KappaTile& t, int64_t n_cell_group
   a.tile_begin = tile_begin;
   a.parts = parts < 1 ? 1 : parts;
   a.part_stride = part_stride;
-  const int64_t blocks = n_cell_groups * n_tiles * a.parts;
+  if (!comp) return launch_plain(a, n_cell_groups, s);
+  const int64_t blocks = n_cell_groups * n_tiles;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
-  if (comp)
-    hipLaunchKernelGGL((kappa_linesum_kernel<true>), dim3((unsigned)blocks), dim3(kKappaThreads),
-                       0, s, a);
-  else
-    hipLaunchKernelGGL((kappa_linesum_kernel<false>), dim3((unsigned)blocks), dim3(kKappaThreads),
-                       0, s, a);
+  hipLaunchKernelGGL((kappa_linesum_kernel<true>), dim3((unsigned)blocks), dim3(kKappaThreads), 0,
+                     s, a);
   return hipGetLastError();
 }
 
-// The plain line sum in 256-point tiles of one point per lane: twice the
+// The plain line sum in 256-point tiles (one span per wavefront): twice the
 // blocks of launch_kappa_tiles, each with half its work, for launches that
 // cover only part of the table (the learned form's fallback), where the
 // latency of one block rather than the total work sets the time.  The

@@ -30,9 +30,25 @@ constexpr double kAtm = 101325.0;
 inline double second_radiation_cm_K() { return kPlanckH * kLightC / kBoltzmann * 100.0; }
 inline double first_radiation_wavenumber() { return 2.0 * kPlanckH * kLightC * kLightC * 1e8; }
 
+// Reach of the plain line sum's far nodes (dev::kappa_tile_far) about a
+// 64-point span of first point v0, 84.5 points from its middle v0 + 31.5:
+// lines with m <= v0 - kFarBelow or m >= v0 + kFarAbove (the centre lies in
+// [m, m + 1)); about a pair of spans, 170.5 points from v0 + 63.5, likewise
+constexpr int kFarBelow = 54, kFarAbove = 116;
+constexpr int kPairBelow = 108, kPairAbove = 234;
+
+// What the plain line sum stages of a line, in three 16-byte loads: centre
+// m + phi, the window's first offset from m, and the Eq. (1)-(2) inputs.
+struct alignas(16) LineData {
+  float m, phi, lo, S;
+  float gamma, nexp, pad0, pad1;
+  double E2, nu;
+};
+
 // Per-line data after sorting by centre (device, structure of arrays).
 struct LineSet {
   int n = 0;              // lines kept (window meets the grid)
+  char* block = nullptr;  // the allocation that holds every array below
   int32_t* m = nullptr;   // floor((nu - nu0)/dnu)
   float* phi = nullptr;   // (nu - nu0)/dnu - m, rounded to float
   int32_t* wlo = nullptr; // first grid point of the window: m - K + [phi > 0]
@@ -59,6 +75,14 @@ struct LineSet {
   // Spans from n_spans on lie past every window: (n, n, n, n).
   int4* span4 = nullptr;
   int n_spans = 0;
+  // per span, for the plain form's far nodes (dev::kappa_tile_far): x the
+  // first line with m > 64 b - kFarBelow and y with m >= 64 b + kFarAbove (the
+  // near lines), z the first with whi >= 64 b + 32 and w with
+  // wlo >= 64 b + 32 (the lines that end in the lower half, start in the upper)
+  int4* span_far = nullptr;
+  // per pair of spans (first point v0 = 128 b, n_spans entries): x the first
+  // line with m > v0 - kPairBelow, y with m >= v0 + kPairAbove
+  int4* span_pair = nullptr;
   // binary64 line data for the adaptive windows: r = (nu - nu0)/dnu,
   // S_ref, gamma_ref, n_T, a = -c2 E and 1/expm1(-c2 nu / T_ref)
   double* r64 = nullptr;
@@ -71,6 +95,7 @@ struct LineSet {
   // nu, each split on the host into an FP32 pair hi + lo
   float2* E2p = nullptr;
   float2* nup = nullptr;
+  LineData* data = nullptr;  // the plain line sum's inputs, one record per line
 };
 
 // Per-cell derived parameters (device), from FP64 on the device.
@@ -257,6 +282,7 @@ constexpr int kOrderBuckets = 6 * 9 * 4096;
 constexpr int64_t kOrderMinRays = int64_t(1) << 15;
 
 // kernel launchers (defined in the .hip files)
+hipError_t launch_line_data(rt_ctx c, const LineSet& L);  // fills L.data
 hipError_t launch_cell_params(rt_ctx c);
 // per-cell factor G of extra gas g (after launch_cell_params' other tables)
 hipError_t launch_gas_factor(rt_ctx c, int g);

@@ -404,8 +404,9 @@ struct FusedArgs {
 // Points per lane of the exact rows computed beside the network (tiles of
 // 256 kExactPoints points): few, long blocks, one per free CU.
 constexpr int kExactPoints = 4;
-static_assert(sizeof(bf16) * 64 * kLdsRow >= sizeof(float) * dev::kLineTile * dev::kLineRec,
-              "the line-sum blocks stage their line records in the activations' LDS");
+static_assert(sizeof(bf16) * 64 * kLdsRow >=
+                  sizeof(float) * (dev::kLineTile * dev::kLineRec + 4 * dev::kFarEntries),
+              "the line-sum blocks stage their line records and nodes in the activations' LDS");
 
 // The transposed product of one layer, Z^T += W^T H^T over K = 512, for RT
 // row tiles x NT column tiles: the weights are the MFMA's A operand, the
@@ -568,13 +569,13 @@ __global__ __launch_bounds__(kFuseThreads) void mlp_fused_kernel(FusedArgs a) {
     // records staged in H
     if (wave >= dev::kKappaThreads / 64) return;
     float* lds = reinterpret_cast<float*>(H);
+    float* fx = lds + dev::kLineTile * dev::kLineRec + wave * dev::kFarEntries;
     if (xb < a.x_blocks) {
       const int tile = (int)(xb % a.x_tiles);
-      dev::kappa_tile<false, false, kExactPoints>(a.xt, tile * dev::kKappaThreads * kExactPoints,
-                                                  (xb / a.x_tiles) * dev::kKappaCells, lds);
+      dev::kappa_tile_far<kExactPoints>(a.xt, tile * dev::kKappaThreads * kExactPoints,
+                                        (xb / a.x_tiles) * dev::kKappaCells, lds, fx);
     } else {
-      dev::kappa_tile<false, false, 1>(a.tt, a.tail_j0, (xb - a.x_blocks) * dev::kKappaCells,
-                                       lds);
+      dev::kappa_tile_far<1>(a.tt, a.tail_j0, (xb - a.x_blocks) * dev::kKappaCells, lds, fx);
     }
     return;
   }
