@@ -352,8 +352,10 @@ rt_status rt_setup_grid(rt_ctx c, int nx, int ny, int nz, double cell_m, const d
   RT_HIP(c, dev_alloc(&c->d_abs, n));
   RT_HIP(c, dev_alloc(&c->d_emi, n));
   // accumulator rows of the cells and the balance, then the overflow flag
-  RT_HIP(c, dev_alloc(&c->d_acc, (size_t)((n + rt::kBalRows) * rt::kAccRow + 1)));
-  c->d_ovf = reinterpret_cast<unsigned*>(c->d_acc + (n + rt::kBalRows) * rt::kAccRow);
+  c->acc_rows = n * rt::acc_copies(n);
+  const int64_t words = (c->acc_rows + rt::kBalRows) * rt::kAccRow;
+  RT_HIP(c, dev_alloc(&c->d_acc, (size_t)(words + 1)));
+  c->d_ovf = reinterpret_cast<unsigned*>(c->d_acc + words);
   RT_HIP(c, dev_alloc(&c->cells.G, n));
   RT_HIP(c, dev_alloc(&c->cells.beta, n));
   RT_HIP(c, dev_alloc(&c->cells.theta, n));

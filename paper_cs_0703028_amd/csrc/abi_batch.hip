@@ -101,7 +101,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   pl.n_chunks = (int)((n_nu + t.chunk_points - 1) / t.chunk_points);
   pl.bwall_ld = (int64_t)pl.n_chunks * t.chunk_points;
   pl.cases.assign(n_cases, BatchCase());
-  int64_t cell_off = 0, seg_off = 0, ray_off = 0, blk_off = 0, max_cells = 0;
+  int64_t cell_off = 0, seg_off = 0, ray_off = 0, blk_off = 0, max_cells = 0, row_off = 0;
   double evals = 0;
   for (int k = 0; k < n_cases; ++k) {
     const rt_case& q = cases[k];
@@ -114,6 +114,9 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
     b.max_segs = q.nx + q.ny + q.nz;
     b.n_cells = (int64_t)q.nx * q.ny * q.nz;
     b.cell_off = cell_off;
+    b.copies = acc_copies(b.n_cells);
+    b.row_off = row_off;
+    row_off += b.copies * b.n_cells + kCaseBalRows;
     b.n_rays = (int64_t)q.n_rays;
     // one launch adds up to rays x spectral chunks terms to a case's
     // accumulator words, which hold kAccMaxTerms until normalised
@@ -143,6 +146,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
     evals += c->line_evals_per_cell * (double)b.n_cells;
   }
   pl.total_cells = cell_off;
+  pl.total_rows = row_off;
   pl.total_rays = ray_off;
   pl.ray_blocks = blk_off;
   if (pl.chunked && 8 * blk_off > 0x7fffffffLL)
@@ -216,7 +220,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   int64_t o_G = take(nc * 4), o_beta = take(nc * 8), o_theta = take(nc * 8), o_lam2 = take(nc * 4),
           o_P = take(nc * 4);
   int64_t o_abs = take(nc * 8), o_emi = take(nc * 8);
-  int64_t o_acc = take(((nc + (int64_t)n_cases * kCaseBalRows) * kAccRow + 1) * 8), o_bal = take((int64_t)n_cases * 4 * 8);
+  int64_t o_acc = take((row_off * kAccRow + 1) * 8), o_bal = take((int64_t)n_cases * 4 * 8);
   int64_t o_bw = take((int64_t)n_cases * pl.bwall_ld * 4);
   int64_t o_poly = take(nc * plain_chunks(c->n_nu) * 16);
   int64_t o_segs = take(seg_off * 8), o_cnt = take(ray_off * 4);
@@ -472,8 +476,7 @@ rt_status rt_batch_results(rt_ctx c, double* absorbed, double* emitted, double* 
   RT_BHIP(c, hipStreamSynchronize(c->stream));
   unsigned err = 0, ovf = 0;
   RT_BHIP(c, hipMemcpy(&err, pl.d_counters + 2, sizeof(unsigned), hipMemcpyDeviceToHost));
-  RT_BHIP(c, hipMemcpy(&ovf, pl.d_acc + (pl.total_cells + (int64_t)pl.n_cases * kCaseBalRows) * kAccRow, sizeof(unsigned),
-                       hipMemcpyDeviceToHost));
+  RT_BHIP(c, hipMemcpy(&ovf, pl.d_acc + pl.total_rows * kAccRow, sizeof(unsigned), hipMemcpyDeviceToHost));
   if (ovf)
     return bfail(c, RT_EDEVICE, "rt_batch_results: a tallied power was negative, not finite or not below 2^80 W");
   if (absorbed)

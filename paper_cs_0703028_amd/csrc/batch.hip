@@ -219,8 +219,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     w.c1 = a.c1;
     w.weight = cs.weight;
     w.acc = a.acc;
-    w.row0 = cs.cell_off + (int64_t)st.cas * kCaseBalRows;
-    w.bal_row0 = w.row0 + cs.n_cells;
+    w.row0 = cs.row_off;
+    w.rep_rows = cs.n_cells;
+    w.rep_mask = cs.copies - 1;
+    w.bal_row0 = cs.row_off + cs.copies * cs.n_cells;
     w.bal_mask = kCaseBalRows - 1;
     w.ovf = a.ovf;
     float* stage = lds + wave * PlainStage::kEntries;
@@ -285,15 +287,16 @@ __global__ __launch_bounds__(256) void case_tally_kernel(const BatchCase* cases,
                                                          double* balance) {
   __shared__ unsigned long long red[kAccRow][256];
   const BatchCase cs = cases[blockIdx.x];
-  const int64_t row0 = cs.cell_off + (int64_t)blockIdx.x * kCaseBalRows;
   for (int64_t c = threadIdx.x; c < cs.n_cells; c += 256) {
-    const unsigned long long* r = acc + (row0 + c) * kAccRow;
-    abs_[cs.cell_off + c] = acc_value(r);
-    emi[cs.cell_off + c] = acc_value(r + kAccDigits);
+    unsigned long long d[kAccRow];
+    acc_sum_copies(acc, cs.row_off + c, cs.n_cells, cs.copies, d);
+    abs_[cs.cell_off + c] = acc_value(d);
+    emi[cs.cell_off + c] = acc_value(d + kAccDigits);
   }
   unsigned long long cells[kAccRow], bal[kAccRow];
-  case_rows_sum(acc, row0, cs.n_cells, red, cells);
-  case_rows_sum(acc, row0 + cs.n_cells, kCaseBalRows, red, bal);
+  const int64_t rows = cs.copies * cs.n_cells;
+  case_rows_sum(acc, cs.row_off, rows, red, cells);
+  case_rows_sum(acc, cs.row_off + rows, kCaseBalRows, red, bal);
   if (threadIdx.x == 0) {
     double* b = balance + 4 * blockIdx.x;
     b[0] = acc_value(bal);
@@ -446,8 +449,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
   w.c1 = a.c1;
   w.weight = cs.weight;
   w.acc = a.acc;
-  w.row0 = cs.cell_off + (int64_t)k * kCaseBalRows;
-  w.bal_row0 = w.row0 + cs.n_cells;
+  w.row0 = cs.row_off;
+  w.rep_rows = cs.n_cells;
+  w.rep_mask = cs.copies - 1;
+  w.bal_row0 = cs.row_off + cs.copies * cs.n_cells;
   w.bal_mask = kCaseBalRows - 1;
   w.ovf = a.ovf;
   march_plain<false, CUBIC, true>(w, a.segs + cs.seg_off + r * cs.max_segs,
@@ -514,7 +519,7 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
                      pl.d_hist);
   hipLaunchKernelGGL(batch_order_scatter_kernel, dim3(ray_blocks), dim3(256), 0, s, pl.d_cases,
                      pl.n_cases, pl.total_rays, pl.d_keys, pl.d_hist, pl.d_perm);
-  const int64_t acc_words = (pl.total_cells + (int64_t)pl.n_cases * kCaseBalRows) * kAccRow;
+  const int64_t acc_words = pl.total_rows * kAccRow;
   fill_d(reinterpret_cast<double*>(pl.d_acc), acc_words + 1);  // + overflow flag
   unsigned* ovf = reinterpret_cast<unsigned*>(pl.d_acc + acc_words);
   const int64_t groups = acc_words / kAccDigits;

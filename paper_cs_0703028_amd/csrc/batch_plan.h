@@ -28,6 +28,9 @@ struct BatchCase {
   int nx, ny, nz, max_segs;
   int64_t n_cells, cell_off, n_rays, seg_off, ray_off;
   int64_t blk_off;  // chunked mode: first row of 8 march blocks of the case
+  int64_t row_off;  // first accumulator row: copies of the cells' rows, then
+                    // kCaseBalRows balance rows
+  int copies;       // acc_copies of the case's cells
   int cubic;        // the march's Planck cubics fit the case (planck_cubic_fits)
   uint64_t seed;
   double weight, unit_cm;
@@ -40,6 +43,7 @@ struct BatchPlan {
   bool chunked = true;      // tuning.mode == RT_BATCH_CHUNKED
   bool any_cubic = false, any_general = false;  // over the cases' `cubic`
   int n_cases = 0, n_chunks = 0, n_pairs = 0, n_stages = 0;
+  int64_t total_rows = 0;  // accumulator rows of all cases
   int64_t total_items = 0, total_cells = 0, total_rays = 0, max_cells = 0;
   int64_t ray_blocks = 0;  // chunked mode: rows of 8 march blocks over all cases
   int64_t grid_blocks = 0;
@@ -51,9 +55,9 @@ struct BatchPlan {
   // device pointers into the caller's workspace
   double *d_T = nullptr, *d_x = nullptr, *d_p = nullptr, *d_T_wall = nullptr;
   CellSet cells;
-  // fixed-point accumulator rows: case k's cells from cell_off + k kCaseBalRows,
-  // then its kCaseBalRows balance rows (entering, escaped); the overflow flag
-  // after the last row
+  // fixed-point accumulator rows: case k's from its row_off (the copies of its
+  // cells' rows, then its kCaseBalRows balance rows: entering, escaped); the
+  // overflow flag after the last row
   unsigned long long* d_acc = nullptr;
   double *d_abs = nullptr, *d_emi = nullptr, *d_balance = nullptr;
   float* d_bwall = nullptr;

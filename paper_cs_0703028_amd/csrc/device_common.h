@@ -1009,6 +1009,20 @@ __device__ __forceinline__ void acc_normalize(unsigned long long* d) {
   d[kAccDigits - 1] += carry;
 }
 
+// Digit sums of the copies (rows row, row + step, ...) of one accumulator
+// row, normalised: the exact sum of the copies.
+__device__ __forceinline__ void acc_sum_copies(const unsigned long long* acc, int64_t row,
+                                               int64_t step, int copies,
+                                               unsigned long long* d) {
+#pragma unroll
+  for (int k = 0; k < kAccRow; ++k) d[k] = 0;
+  for (int r = 0; r < copies; ++r)
+#pragma unroll
+    for (int k = 0; k < kAccRow; ++k) d[k] += acc[(row + r * step) * kAccRow + k];
+  acc_normalize(d);
+  acc_normalize(d + kAccDigits);
+}
+
 // The value of normalised digits, summed from the top digit down.
 __device__ __forceinline__ double acc_value(const unsigned long long* d) {
   double v = 0.0;
@@ -1041,6 +1055,10 @@ struct MarchWave {
   double nu0, dnu, c1, weight;
   unsigned long long* acc;  // accumulator rows, kAccRow words each
   int64_t row0;             // row of cell 0
+  // copies of the cells' rows, rep_rows apart (a power of two of them): a ray
+  // adds to copy (its slot & rep_mask), see acc_copies
+  int64_t rep_rows;
+  int rep_mask;
   int64_t bal_row0;         // first of the balance rows (entering, escaped)
   int bal_mask;             // balance rows - 1 (a power of two): a ray adds to
                             // row bal_row0 + (its slot & bal_mask)
@@ -1083,7 +1101,7 @@ struct PrecStage {
 // those lanes with DPP: the same order every time.
 __device__ __forceinline__ void tally_flush(const MarchWave& a, const double* stage,
                                             const int2* sg, int ns, int k0, int np, int lane,
-                                            int64_t bal_row) {
+                                            int64_t row0, int64_t bal_row) {
   constexpr int V = 2 * PrecStage::kSegs;
   constexpr int LPV = 64 / V;  // lanes per value
   constexpr int E = 64 / LPV;  // partials per lane
@@ -1105,7 +1123,7 @@ __device__ __forceinline__ void tally_flush(const MarchWave& a, const double* st
   const int seg = v >> 1;
   if (part == 0 && seg < np) {
     const int k = k0 + seg;
-    const int64_t row = k < ns ? a.row0 + sg[k].x : bal_row;
+    const int64_t row = k < ns ? row0 + sg[k].x : bal_row;
     acc_add(a.acc + row * kAccRow + (v & 1) * kAccDigits, s * a.weight, a.ovf);
   }
 }
@@ -1116,6 +1134,7 @@ template <bool EXIT>
 __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, int ns, int64_t j,
                                            int lane, float* exit_row, double* stage, int64_t slot) {
   constexpr int kSegs = PrecStage::kSegs;
+  const int64_t row0 = a.row0 + (slot & a.rep_mask) * a.rep_rows;
   const int64_t col = j - a.col0;
   float I[kQ];
 #pragma unroll
@@ -1168,7 +1187,7 @@ __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, i
     st[lane] = ab;
     st[64 + lane] = em;
     if (++np == kSegs) {
-      tally_flush(a, stage, sg, ns, k0, np, lane, 0);
+      tally_flush(a, stage, sg, ns, k0, np, lane, row0, 0);
       k0 += np;
       np = 0;
     }
@@ -1186,7 +1205,7 @@ __device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, i
   double* st = stage + np * 128;
   st[lane] = enter;
   st[64 + lane] = esc;
-  tally_flush(a, stage, sg, ns, k0, np + 1, lane, a.bal_row0 + (slot & a.bal_mask));
+  tally_flush(a, stage, sg, ns, k0, np + 1, lane, row0, a.bal_row0 + (slot & a.bal_mask));
 }
 
 // ------------------------------------------------------- the plain form's march
@@ -1227,7 +1246,8 @@ __device__ __forceinline__ void plain_stage(float* stage, int np, int lane, floa
 // lanes per entry, each over 16 consecutive floats (8 absorbed, 8 emitted),
 // then across the four with DPP: the same order every time.
 __device__ __forceinline__ void plain_flush(const MarchWave& a, const float* stage, const int2* sg,
-                                            int ns, int k0, int np, int lane, int64_t bal_row) {
+                                            int ns, int k0, int np, int lane, int64_t row0,
+                                            int64_t bal_row) {
   __builtin_amdgcn_wave_barrier();
   int ln = lane;  // see tally_flush
   asm volatile("" : "+v"(ln));
@@ -1249,7 +1269,7 @@ __device__ __forceinline__ void plain_flush(const MarchWave& a, const float* sta
   __builtin_amdgcn_wave_barrier();
   if (!(ln & 2) && seg < np) {
     const int k = k0 + seg;
-    const int64_t row = k < ns ? a.row0 + sg[k].x : bal_row;
+    const int64_t row = k < ns ? row0 + sg[k].x : bal_row;
     acc_add(a.acc + row * kAccRow + (ln & 1) * kAccDigits, (double)s * a.weight, a.ovf);
   }
 }
@@ -1323,6 +1343,7 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
                                             int lane, float* exit_row, float* stage,
                                             int64_t slot) {
   constexpr int Q = kPlainQ;
+  const int64_t row0 = a.row0 + (slot & a.rep_mask) * a.rep_rows;
   constexpr float kThin = 0.03125f;
   constexpr float nlog2e = -1.4426950408889634f;
   const unsigned voff = (unsigned)lane * (Q * 4);            // bytes into the chunk's row
@@ -1419,7 +1440,7 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
       asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(I[q]) : "v"(I[q] - B[q]), "v"(t[q]), "v"(B[q]));
     plain_stage(stage, np, lane, ab, em);
     if (++np == PlainStage::kSegs) {
-      plain_flush(a, stage, sg, ns, k0, np, lane, 0);
+      plain_flush(a, stage, sg, ns, k0, np, lane, row0, 0);
       k0 += np;
       np = 0;
     }
@@ -1432,7 +1453,7 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
   }
   // np < kSegs here: one more entry, the balance row's (entering, escaped)
   plain_stage(stage, np, lane, enter, S);
-  plain_flush(a, stage, sg, ns, k0, np + 1, lane, a.bal_row0 + (slot & a.bal_mask));
+  plain_flush(a, stage, sg, ns, k0, np + 1, lane, row0, a.bal_row0 + (slot & a.bal_mask));
 }
 
 }  // namespace dev

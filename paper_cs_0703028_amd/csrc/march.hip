@@ -160,11 +160,13 @@ __global__ void acc_normalize_kernel(unsigned long long* acc, int64_t groups) {
 
 // Per-cell powers from the normalised accumulators.
 __global__ void acc_cells_kernel(const unsigned long long* __restrict__ acc, int64_t n_cells,
-                                 double* abs_, double* emi) {
+                                 int copies, double* abs_, double* emi) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n_cells) return;
-  abs_[c] = acc_value(acc + c * kAccRow);
-  emi[c] = acc_value(acc + c * kAccRow + kAccDigits);
+  unsigned long long d[kAccRow];
+  acc_sum_copies(acc, c, n_cells, copies, d);
+  abs_[c] = acc_value(d);
+  emi[c] = acc_value(d + kAccDigits);
 }
 
 // The exact sum of accumulator rows [first, first + n): each digit is summed
@@ -201,11 +203,11 @@ __device__ void acc_rows_sum(const unsigned long long* __restrict__ acc, int64_t
 // balance = {entering, sum emitted, sum absorbed, escaped}, each from the
 // exact sum of its accumulators (cells, or the balance rows), converted once.
 __global__ __launch_bounds__(256) void tally_kernel(const unsigned long long* __restrict__ acc,
-                                                    int64_t n_cells, double* balance) {
+                                                    int64_t rows, double* balance) {
   __shared__ unsigned long long red[kAccRow][256];
   unsigned long long cells[kAccRow], bal[kAccRow];
-  acc_rows_sum(acc, 0, n_cells, red, cells);
-  acc_rows_sum(acc, n_cells, kBalRows, red, bal);
+  acc_rows_sum(acc, 0, rows, red, cells);
+  acc_rows_sum(acc, rows, kBalRows, red, bal);
   if (threadIdx.x == 0) {
     balance[0] = acc_value(bal);
     balance[1] = acc_value(cells + kAccDigits);
@@ -310,7 +312,9 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
   a.w.weight = weight;
   a.w.acc = c->d_acc;
   a.w.row0 = 0;
-  a.w.bal_row0 = c->n_cells;
+  a.w.rep_rows = c->n_cells;
+  a.w.rep_mask = acc_copies(c->n_cells) - 1;
+  a.w.bal_row0 = c->acc_rows;
   a.w.bal_mask = kBalRows - 1;
   a.w.ovf = c->d_ovf;
   a.ray_blocks_x = ((count + 3) / 4 + 7) / 8;
@@ -336,7 +340,7 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
     if (exit_dev) hipLaunchKernelGGL((march_kernel<true, false>), g, t, pad, c->stream, a);
     else hipLaunchKernelGGL((march_kernel<false, false>), g, t, pad, c->stream, a);
   }
-  const int64_t groups = 2 * (c->n_cells + kBalRows);
+  const int64_t groups = 2 * (c->acc_rows + kBalRows);
   hipLaunchKernelGGL(acc_normalize_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0,
                      c->stream, c->d_acc, groups);
   return hipGetLastError();
@@ -344,8 +348,8 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
 
 hipError_t launch_tally(rt_ctx c) {
   hipLaunchKernelGGL(acc_cells_kernel, dim3((unsigned)((c->n_cells + 255) / 256)), dim3(256), 0,
-                     c->stream, c->d_acc, c->n_cells, c->d_abs, c->d_emi);
-  hipLaunchKernelGGL(tally_kernel, dim3(1), dim3(256), 0, c->stream, c->d_acc, c->n_cells,
+                     c->stream, c->d_acc, c->n_cells, acc_copies(c->n_cells), c->d_abs, c->d_emi);
+  hipLaunchKernelGGL(tally_kernel, dim3(1), dim3(256), 0, c->stream, c->d_acc, c->acc_rows,
                      c->d_balance);
   return hipGetLastError();
 }
@@ -357,7 +361,7 @@ hipError_t launch_zero(rt_ctx c) {
   };
   z(c->d_abs, c->n_cells);
   z(c->d_emi, c->n_cells);
-  z(reinterpret_cast<double*>(c->d_acc), (c->n_cells + kBalRows) * kAccRow + 1);  // + overflow flag
+  z(reinterpret_cast<double*>(c->d_acc), (c->acc_rows + kBalRows) * kAccRow + 1);  // + overflow flag
   z(c->d_balance, 4);
   z(reinterpret_cast<double*>(c->d_segcount), 1);
   return hipGetLastError();

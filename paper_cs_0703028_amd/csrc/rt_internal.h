@@ -228,9 +228,11 @@ struct rt_ctx_s {
   int64_t poly_cap = 0;
   bool planck_cubic = false;
 
-  // tallies (owned): fixed-point accumulator rows [n_cells + kBalRows][2][kAccDigits]
-  // (rows from n_cells: entering, escaped) followed by the overflow flag; the
-  // per-cell powers and the balance converted from them by rt_tally
+  // tallies (owned): fixed-point accumulator rows
+  // [acc_copies n_cells + kBalRows][2][kAccDigits] (the last kBalRows: entering,
+  // escaped) followed by the overflow flag; the per-cell powers and the balance
+  // converted from them by rt_tally
+  int64_t acc_rows = 0;  // cell rows, all copies
   unsigned long long* d_acc = nullptr;
   unsigned* d_ovf = nullptr;
   double* d_abs = nullptr;
@@ -275,6 +277,18 @@ constexpr int64_t kAccMaxTerms = int64_t(1) << 35;
 // Balance rows (entering, escaped) per grid: rays spread over them so that
 // their additions do not all meet in one accumulator.
 constexpr int kBalRows = 1024;
+// Copies of a grid's cell rows: the integer atomics of different rays meet in
+// a cell's row, and on few cells they bound the march (5^3 cells, 6,380
+// points, 54,553 rays: 1,497 -> 1,033 us a call; one cell, 10,000 points, 4,096
+// rays: 1,405 -> 60 us; no difference from 12^3 on; 8,192 rows gain 2% more on
+// 8^3 and cost the tally as much), so small grids spread them over up to 2,048
+// rows.  Copies are summed as integers, exactly.
+constexpr int64_t kAccCopyRows = 2048;
+inline int acc_copies(int64_t n_cells) {
+  int r = 1;
+  while (r < 64 && 2 * r * n_cells <= kAccCopyRows) r *= 2;
+  return r;
+}
 // Coherent ray order: 6 dominant directions x 3 x 3 transverse direction
 // bins x 64 x 64 positions on the mid-plane; used for batches of at least
 // kOrderMinRays rays.
