@@ -238,7 +238,7 @@ rt_status rt_set_line_tolerance(rt_ctx ctx, double eps);
  * absorbed/emitted power and to the energy balance; ranges may be traced in
  * any order and any split (tallies add).  tally_prec: rt_tally_prec.
  * The rays of a call are traced in batches of up to about 1 GiB of segment
- * scratch (owned by the handle); a batch of 2^15 rays or more is marched in
+ * scratch (owned by the handle); a batch of 12,288 rays or more is marched in
  * a coherent order (rays sorted by direction and position), which changes
  * only the order of the floating-point additions.
  * Requires rt_compute_kappa. */

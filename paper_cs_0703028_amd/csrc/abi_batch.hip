@@ -226,6 +226,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   int64_t o_segs = take(seg_off * 8), o_cnt = take(ray_off * 4);
   int64_t o_keys = take(ray_off * 4), o_perm = take(ray_off * 4);
   int64_t o_hist = take((int64_t)n_cases * kOrderBuckets * 4);
+  int64_t o_hsum = take((int64_t)n_cases * kOrderTiles * 4);
   int64_t o_slab = take((int64_t)n_slabs * pl.slab_stride * 4);
   int64_t o_ctr = take(pl.n_counters * 4);
   int64_t o_st = take((int64_t)pl.n_stages * sizeof(BatchStage));
@@ -252,6 +253,7 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   pl.d_keys = reinterpret_cast<uint32_t*>(o_keys);
   pl.d_perm = reinterpret_cast<uint32_t*>(o_perm);
   pl.d_hist = reinterpret_cast<uint32_t*>(o_hist);
+  pl.d_hist_sums = reinterpret_cast<uint32_t*>(o_hsum);
   pl.d_slabs = reinterpret_cast<float*>(o_slab);
   pl.d_counters = reinterpret_cast<unsigned*>(o_ctr);
   pl.d_stages = reinterpret_cast<BatchStage*>(o_st);
@@ -270,6 +272,7 @@ void carve(BatchPlan& pl, void* ws) {
   rebase(pl.d_abs, b); rebase(pl.d_emi, b); rebase(pl.d_acc, b); rebase(pl.d_balance, b);
   rebase(pl.d_bwall, b); rebase(pl.d_poly, b); rebase(pl.d_segs, b); rebase(pl.d_counts, b); rebase(pl.d_slabs, b);
   rebase(pl.d_keys, b); rebase(pl.d_perm, b); rebase(pl.d_hist, b);
+  rebase(pl.d_hist_sums, b);
   rebase(pl.d_counters, b); rebase(pl.d_stages, b); rebase(pl.d_cases, b);
 }
 

@@ -330,31 +330,6 @@ __global__ void batch_order_key_kernel(const BatchCase* __restrict__ cases, int 
   atomicAdd(hist + (int64_t)k * kOrderBuckets + key, 1u);
 }
 
-// one block of 1024 threads per case: exclusive prefix sum of its histogram
-__global__ __launch_bounds__(1024) void batch_order_scan_kernel(uint32_t* hist) {
-  __shared__ uint32_t part[1024];
-  uint32_t* h = hist + (int64_t)blockIdx.x * kOrderBuckets;
-  const int t = threadIdx.x;
-  constexpr int run = (kOrderBuckets + 1023) / 1024;
-  const int lo = min(kOrderBuckets, t * run), hi = min(kOrderBuckets, lo + run);
-  uint32_t s = 0;
-  for (int i = lo; i < hi; ++i) s += h[i];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const uint32_t v = t >= off ? part[t - off] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  uint32_t acc = part[t] - s;
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t v = h[i];
-    h[i] = acc;
-    acc += v;
-  }
-}
-
 __global__ void batch_order_scatter_kernel(const BatchCase* __restrict__ cases, int n_cases,
                                            int64_t total_rays, const uint32_t* __restrict__ keys,
                                            uint32_t* hist, uint32_t* perm) {
@@ -515,8 +490,8 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
   const unsigned ray_blocks = (unsigned)((pl.total_rays + 255) / 256);
   hipLaunchKernelGGL(batch_order_key_kernel, dim3(ray_blocks), dim3(256), 0, s, pl.d_cases,
                      pl.n_cases, pl.total_rays, pl.d_keys, pl.d_hist);
-  hipLaunchKernelGGL(batch_order_scan_kernel, dim3((unsigned)pl.n_cases), dim3(1024), 0, s,
-                     pl.d_hist);
+  hipError_t oe = launch_order_scan(pl.d_hist, pl.d_hist_sums, pl.n_cases, s);
+  if (oe != hipSuccess) return oe;
   hipLaunchKernelGGL(batch_order_scatter_kernel, dim3(ray_blocks), dim3(256), 0, s, pl.d_cases,
                      pl.n_cases, pl.total_rays, pl.d_keys, pl.d_hist, pl.d_perm);
   const int64_t acc_words = pl.total_rows * kAccRow;

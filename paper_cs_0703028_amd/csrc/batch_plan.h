@@ -67,6 +67,7 @@ struct BatchPlan {
   uint32_t* d_keys = nullptr;  // coherent-order key per ray (all cases)
   uint32_t* d_perm = nullptr;  // case-local slot -> case-local ray index
   uint32_t* d_hist = nullptr;  // [n_cases][kOrderBuckets] counts, then offsets
+  uint32_t* d_hist_sums = nullptr;  // [n_cases][kOrderTiles] for their scan
   float* d_slabs = nullptr;
   unsigned* d_counters = nullptr;  // [queue lo, queue hi, error, pad, rg_done..., k_done..., m_done...]
   BatchStage* d_stages = nullptr;

@@ -32,31 +32,6 @@ __global__ void order_key_kernel(uint64_t seed, uint64_t begin, int64_t count, i
   atomicAdd(hist + k, 1u);
 }
 
-// Exclusive prefix sum of hist[0..n) in place; one block of 1024 threads,
-// each owning a contiguous run.
-__global__ __launch_bounds__(1024) void order_scan_kernel(uint32_t* hist, int n) {
-  __shared__ uint32_t part[1024];
-  const int t = threadIdx.x;
-  const int run = (n + 1023) / 1024;
-  const int lo = min(n, t * run), hi = min(n, lo + run);
-  uint32_t s = 0;
-  for (int i = lo; i < hi; ++i) s += hist[i];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const uint32_t v = t >= off ? part[t - off] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  uint32_t acc = part[t] - s;  // exclusive
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t v = hist[i];
-    hist[i] = acc;
-    acc += v;
-  }
-}
-
 __global__ void order_scatter_kernel(const uint32_t* __restrict__ keys, int64_t count,
                                      uint32_t* offsets, uint32_t* perm) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -221,7 +196,60 @@ __global__ void zero_f64_kernel(double* p, int64_t n) {
   if (i < n) p[i] = 0.0;
 }
 
+// Exclusive prefix sums of n histograms in place.  A histogram is
+// kOrderTiles tiles of 1024 buckets: first the tiles' sums, then every tile's
+// block adds the sums before its own.  Both are launches of a few
+// microseconds (4.3 and 4.4 us; one block per histogram, each thread over a
+// run of 216 buckets at a stride that no two lanes share a line of, took 360).
+__global__ __launch_bounds__(256) void order_sums_kernel(const uint32_t* __restrict__ hist,
+                                                         uint32_t* sums) {
+  __shared__ uint32_t part[4];
+  const int64_t h = blockIdx.y;
+  const uint4 v =
+      reinterpret_cast<const uint4*>(hist + h * kOrderBuckets)[blockIdx.x * 256 + threadIdx.x];
+  uint32_t s = v.x + v.y + v.z + v.w;
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) sums[h * kOrderTiles + blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+__global__ __launch_bounds__(256) void order_scan_kernel(uint32_t* hist,
+                                                         const uint32_t* __restrict__ sums) {
+  __shared__ uint32_t part[8];
+  const int64_t h = blockIdx.y;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // the tiles before this one (kOrderTiles <= 256: one per thread)
+  uint32_t before = t < (int)blockIdx.x ? sums[h * kOrderTiles + t] : 0u;
+  for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+  uint4* p = reinterpret_cast<uint4*>(hist + h * kOrderBuckets) + blockIdx.x * 256 + t;
+  const uint4 v = *p;
+  const uint32_t own = v.x + v.y + v.z + v.w;
+  uint32_t incl = own;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t u = __shfl_up(incl, off);
+    if (lane >= off) incl += u;
+  }
+  if (lane == 0) part[wave] = before;
+  if (lane == 63) part[4 + wave] = incl;
+  __syncthreads();
+  uint32_t base = part[0] + part[1] + part[2] + part[3] + incl - own;
+  for (int w = 0; w < wave; ++w) base += part[4 + w];
+  *p = make_uint4(base, base + v.x, base + v.x + v.y, base + v.x + v.y + v.z);
+}
+
 }  // namespace
+
+hipError_t launch_order_scan(uint32_t* hist, uint32_t* sums, int n, hipStream_t s) {
+  for (int h = 0; h < n; h += 32768) {  // a grid's y ends at 65,535
+    const dim3 grid(kOrderTiles, (unsigned)std::min(n - h, 32768));
+    uint32_t* const hh = hist + (int64_t)h * kOrderBuckets;
+    uint32_t* const hs = sums + (int64_t)h * kOrderTiles;
+    hipLaunchKernelGGL(order_sums_kernel, grid, dim3(256), 0, s, hh, hs);
+    hipLaunchKernelGGL(order_scan_kernel, grid, dim3(256), 0, s, hh, hs);
+  }
+  return hipGetLastError();
+}
 
 RayScratch owned_rays(rt_ctx c) {
   RayScratch s;
@@ -243,8 +271,8 @@ hipError_t launch_order(rt_ctx c, const RayScratch& s, uint64_t seed, uint64_t b
                      0, c->stream, s.hist, (int64_t)kOrderBuckets);
   hipLaunchKernelGGL(order_key_kernel, dim3(blocks), dim3(threads), 0, c->stream, seed, begin,
                      count, c->nx, c->ny, c->nz, s.keys, s.hist);
-  hipLaunchKernelGGL(order_scan_kernel, dim3(1), dim3(1024), 0, c->stream, s.hist,
-                     kOrderBuckets);
+  hipError_t e = launch_order_scan(s.hist, s.perm, 1, c->stream);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(order_scatter_kernel, dim3(blocks), dim3(threads), 0, c->stream, s.keys,
                      count, s.hist, s.perm);
   return hipGetLastError();

@@ -293,7 +293,14 @@ inline int acc_copies(int64_t n_cells) {
 // bins x 64 x 64 positions on the mid-plane; used for batches of at least
 // kOrderMinRays rays.
 constexpr int kOrderBuckets = 6 * 9 * 4096;
-constexpr int64_t kOrderMinRays = int64_t(1) << 15;
+constexpr int kOrderTiles = kOrderBuckets / 1024;
+static_assert(kOrderTiles * 1024 == kOrderBuckets && kOrderTiles <= 256, "tiles of the scan");
+// The order costs 25 us a batch and pays by what the rays of a block then share
+// of their cells' rows: at 8192 rays it costs 2% of an 8^3 plain trace and saves
+// 2-8% on 16^3 to 32^3 cells, from 12,000 rays on it saves 2% (8^3 and 32^3),
+// 11% (16^3) and 4% (24^3), at 30,000 rays 3%, 20%, 11% and 6%.
+constexpr int64_t kOrderMinRays = 3 * (int64_t(1) << 12);
+static_assert(kOrderMinRays >= kOrderTiles, "the permutation holds the tiles' sums");
 
 // kernel launchers (defined in the .hip files)
 hipError_t launch_line_data(rt_ctx c, const LineSet& L);  // fills L.data
@@ -318,6 +325,10 @@ RayScratch owned_rays(rt_ctx c);
 hipError_t launch_raygen(rt_ctx c, const RayScratch& s, uint64_t seed, uint64_t begin,
                          int64_t count, bool explicit_rays, int64_t* rays_out, bool count_work,
                          const uint32_t* perm);
+// exclusive prefix sums of n histograms in place; sums: kOrderTiles words of
+// scratch for each (a batch's permutation, not yet written, serves: it is at
+// least kOrderMinRays long)
+hipError_t launch_order_scan(uint32_t* hist, uint32_t* sums, int n, hipStream_t s);
 hipError_t launch_order(rt_ctx c, const RayScratch& s, uint64_t seed, uint64_t begin,
                         int64_t count);
 // march chunks of the plain form in n_nu points, and its Planck cubics: whether

@@ -57,3 +57,23 @@ def test_chunk_ends_planck_forms_and_optical_depths(rt, O, n_nu, dnu, x, T_wall)
     w = I.Workload("edges", g, L, 300, 6)
     print(f"n_nu {n_nu} dnu {dnu} x {x}", flush=True)
     _check(_run(rt, w), O.run(g, L, w.n_rays, seed=w.seed))
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("n", [12287, 12288, 12289, 20001])
+def test_coherent_order_starts_at_12288_rays(rt, n, prec):
+    """One call of n rays against pieces of it below the order's first batch
+    size: the tallies are exact sums of the same values."""
+    t = rt.Tracer(0)
+    t.setup_workload(I.small_ragged())
+    t.compute_kappa(rt.KAPPA_COMPENSATED)  # with the Planck table, which both forms take
+    print(f"{n} rays, {prec}", flush=True)
+    p = rt.TALLY_F64 if prec == "f64" else rt.TALLY_F32
+    t.trace_rays(7, n, 0, n, p)
+    one = t.tally()
+    t.reset_tally()
+    for b in range(0, n, 5000):
+        t.trace_rays(7, n, b, min(5000, n - b), p)
+    for a, b in zip(one, t.tally()):
+        assert np.array_equal(a, b)
+    t.close()
