@@ -105,3 +105,33 @@ def test_table16_full_size_32cube_sampled_rows(rt, O):
     print(f"table16 32^3 sampled rows: rel err max {r.max():.3e} median {np.median(r):.3e}",
           flush=True)
     assert r.max() <= REL
+
+
+@pytest.mark.parametrize("cells,n_nu,n_lines,huge", [
+    ((1, 1, 1), 1, 3, 0), ((7, 3, 3), 255, 40, 0), ((4, 4, 4), 256, 63, 0),
+    ((5, 13, 1), 257, 64, 0), ((8, 8, 2), 545, 200, 0), ((3, 3, 3), 800, 900, 0),
+    ((9, 5, 3), 1600, 0, 0), ((5, 13, 1), 700, 100, 3),
+])
+def test_table16_tile_edges(rt, O, cells, n_nu, n_lines, huge):
+    """Grids around a tile's 64 cells, spectra around its 256 points and 32-point
+    parts, staged runs of up to, at and beyond 64 lines.  huge: lines whose
+    amplitude is beyond float reach their own 16 points and no others."""
+    nx, ny, nz = cells
+    g = I.linear_T_grid(nx, 0.1, ny=ny, nz=nz, x=0.2)
+    L = I.line_list(n_lines, 999.9, 1000.1 + n_nu * 0.01, seed=n_nu, dnu=0.01, n_nu=n_nu)
+    for k in range(huge):
+        L.S[7 + 30 * k] = 1e300
+    t = rt.Tracer(0)
+    t.setup_grid(g)
+    t.setup_lines(L)
+    print(f"table16 edges {cells} {n_nu} points {n_lines} lines", flush=True)
+    kap, _ = t.compute_kappa(rt.KAPPA_TABLE16)
+    kg = kap.cpu().numpy().astype(np.float64)
+    t.close()
+    ko = O.kappa_table16(g, L)
+    assert (kg[:, n_nu:] == 0).all()
+    fits = ko < 1e30
+    assert fits.all() == (huge == 0)
+    assert not np.isfinite(kg[:, :n_nu][~fits]).any()
+    r = _rel(np.where(fits, kg[:, :n_nu], 0), np.where(fits, ko, 0))
+    assert r.size == 0 or r.max() <= REL
