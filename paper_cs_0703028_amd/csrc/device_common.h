@@ -851,50 +851,64 @@ __device__ inline void sample_ray(uint64_t seed, uint64_t r, int nx, int ny, int
 }
 
 // Incremental traversal with exact integer comparisons.  The parameter of
-// the next plane along axis k is tnum_k / tden_k (tden_k = |D_k|); the
-// smallest one is found by cross-multiplication, every axis reaching it
-// steps at once (edges and corners are crossed in one step), and the
-// segment length is the exact integer numerator of t_next - t_prev over
-// its denominator, times |D| h / 2^21, rounded once to FP32.
+// the next plane along axis k is tnum_k / tden_k (tden_k = |D_k| <= 2^21,
+// tnum_k <= 2^41); the smallest one is found by cross-multiplication, every
+// axis reaching it steps at once (edges and corners are crossed in one step),
+// and the segment length is the exact integer numerator of t_next - t_prev
+// over its denominator, times |D| h / 2^21, rounded once to FP32.  An axis the
+// ray does not move along keeps 1 / 0, later than every plane.
+//
+// The chain of a step is what it costs, a wavefront having few others beside
+// it: the three pairs are compared once, for the smallest and for the ties
+// alike, in products of 64 by 32 bits.  Ray generation and traversal of 1024
+// rays, 8^3 cells: 10.1 us, 4096 rays, 24^3 cells: 25.5, 2^20 rays, 32^3 cells:
+// 259 (two passes over the axes with 64 by 64 products: 15.5, 42.8 and 319).
 __device__ inline int traverse(int nx, int ny, int nz, double unit_cm, const int64_t O[3],
                                const int64_t D[3], int max_segs, int2* out) {
-  const int64_t n[3] = {nx, ny, nz};
-  int64_t idx[3], tnum[3], tden[3];
-  bool live[3];
+  const unsigned n[3] = {(unsigned)nx, (unsigned)ny, (unsigned)nz};
+  unsigned idx[3], den[3];
+  uint64_t num[3];
   for (int k = 0; k < 3; ++k) {
     const int64_t q = O[k] / kCellUnits;  // O >= 0
     const bool on_plane = (O[k] % kCellUnits) == 0;
-    idx[k] = (on_plane && D[k] < 0) ? q - 1 : q;
-    live[k] = D[k] != 0;
-    tden[k] = D[k] < 0 ? -D[k] : D[k];
-    if (D[k] > 0) tnum[k] = (idx[k] + 1) * kCellUnits - O[k];
-    else if (D[k] < 0) tnum[k] = O[k] - idx[k] * kCellUnits;
-    else tnum[k] = 0;
+    const int64_t i = (on_plane && D[k] < 0) ? q - 1 : q;
+    idx[k] = (unsigned)i;  // -1: beyond every n
+    den[k] = (unsigned)(D[k] < 0 ? -D[k] : D[k]);
+    if (D[k] > 0) num[k] = (uint64_t)((i + 1) * kCellUnits - O[k]);
+    else if (D[k] < 0) num[k] = (uint64_t)(O[k] - i * kCellUnits);
+    else num[k] = 1;
   }
+  const unsigned d0 = den[0], d1 = den[1], d2 = den[2];
+  const unsigned step0 = D[0] > 0 ? 1u : ~0u, step1 = D[1] > 0 ? 1u : ~0u, step2 = D[2] > 0 ? 1u : ~0u;
+  unsigned i0 = idx[0], i1 = idx[1], i2 = idx[2];
+  uint64_t t0 = num[0], t1 = num[1], t2 = num[2];
   const double dlen = sqrt((double)D[0] * (double)D[0] + (double)D[1] * (double)D[1] +
                            (double)D[2] * (double)D[2]);
-  int64_t pnum = 0, pden = 1;
+  uint64_t pnum = 0;
+  unsigned pden = 1;
   int count = 0;
-  while (idx[0] >= 0 && idx[0] < n[0] && idx[1] >= 0 && idx[1] < n[1] && idx[2] >= 0 &&
-         idx[2] < n[2] && count < max_segs) {
-    int m = -1;
-    for (int k = 0; k < 3; ++k) {
-      if (!live[k]) continue;
-      if (m < 0 || tnum[k] * tden[m] < tnum[m] * tden[k]) m = k;
-    }
-    const int64_t mnum = tnum[m], mden = tden[m];
-    const int64_t dnum = mnum * pden - pnum * mden;
-    const int64_t dden = mden * pden;
+  while (i0 < n[0] && i1 < n[1] && i2 < n[2] && count < max_segs) {
+    const uint64_t a01 = t0 * d1, b01 = t1 * d0, a02 = t0 * d2, b02 = t2 * d0, a12 = t1 * d2,
+                   b12 = t2 * d1;
+    // the first of the axes with the smallest parameter, and those it ties with
+    const bool m0 = a01 <= b01 && a02 <= b02;
+    const bool m1 = !m0 && a12 <= b12;
+    const bool go1 = m0 ? a01 == b01 : m1;
+    const bool go2 = m0 ? a02 == b02 : (m1 ? a12 == b12 : true);
+    const uint64_t mnum = m0 ? t0 : (m1 ? t1 : t2);
+    const unsigned mden = m0 ? d0 : (m1 ? d1 : d2);
+    const int64_t dnum = (int64_t)(mnum * pden - pnum * mden);
+    const int64_t dden = (int64_t)((uint64_t)mden * pden);
     const double len = ((double)dnum / (double)dden) * dlen * unit_cm;
-    const int cell = (int)(idx[0] + n[0] * (idx[1] + n[1] * idx[2]));
+    const int cell = (int)(i0 + n[0] * (i1 + n[1] * i2));
     out[count] = make_int2(cell, __float_as_int((float)len));
     ++count;
-    for (int k = 0; k < 3; ++k) {
-      if (live[k] && tnum[k] * mden == mnum * tden[k]) {
-        idx[k] += D[k] > 0 ? 1 : -1;
-        tnum[k] += kCellUnits;
-      }
-    }
+    i0 += m0 ? step0 : 0u;
+    t0 += m0 ? (uint64_t)kCellUnits : 0;
+    i1 += go1 ? step1 : 0u;
+    t1 += go1 ? (uint64_t)kCellUnits : 0;
+    i2 += go2 ? step2 : 0u;
+    t2 += go2 ? (uint64_t)kCellUnits : 0;
     pnum = mnum;
     pden = mden;
   }

@@ -77,3 +77,31 @@ def test_coherent_order_starts_at_12288_rays(rt, n, prec):
     for a, b in zip(one, t.tally()):
         assert np.array_equal(a, b)
     t.close()
+
+
+U = 1 << 21  # one cell width
+
+
+@pytest.mark.parametrize("o,d", [
+    ((0, 0, 0), (1, 1, 1)), ((0, 0, 0), (1, 1, 0)), ((0, 0, 0), (0, 1, 1)),
+    ((0, 0, 0), (2, 1, 2)), ((0, U, 0), (1, 0, 1)), ((4 * U, 3 * U, 5 * U), (-1, -1, -1)),
+    ((4 * U, U // 2, U), (-2, 1, 1)), ((0, U, 2 * U), (1, 0, 0)), ((U, 3 * U, 5 * U - 1), (0, -1, 0)),
+    ((3 * U, 0, U), (-1, 1, 1)), ((1, 3 * U, 4 * U), (1, -1, -1)),
+])
+def test_rays_through_edges_and_corners(rt, O, o, d):
+    """Rays that reach two or three planes at once, and rays along an axis or
+    in a plane: every cell's power against the oracle's own traversal."""
+    g = I.linear_T_grid(4, 0.1, ny=3, nz=5, T_lo=400.0, T_hi=1500.0, x=0.1, T_wall=900.0)
+    L = I.line_list(200, 999.0, 1011.0, seed=3, dnu=0.01, n_nu=1000)
+    o = np.array([o], np.int64)
+    d = np.array([d], np.int64) << 19
+    t = rt.Tracer(0)
+    t.setup_grid(g)
+    t.setup_lines(L)
+    t.compute_kappa(rt.KAPPA_PLAIN)
+    print(f"ray {o[0]} {d[0]}", flush=True)
+    t.trace_explicit(o, d, 1.0)
+    got = t.tally()
+    t.close()
+    a, e, b, _ = O.march(g, L, o, d, 1.0, O.kappa(g, L), O.planck_rows(g, L))
+    _check(got, {"absorbed": a, "emitted": e, "balance": b})
