@@ -150,11 +150,66 @@ void free_gases(rt_ctx c) {
   }
 }
 
-void free_cells(rt_ctx c) {
-  rt::CellSet& C = c->cells;
-  dev_free(C.G); dev_free(C.beta); dev_free(C.theta); dev_free(C.lam2); dev_free(C.P);
-  dev_free(C.uf); dev_free(C.lamf); dev_free(C.Pf); dev_free(C.beta2); dev_free(C.theta2);
-  dev_free(C.Gq);
+// Host memory for rt_tally's results.  A handle has its own while it lives and
+// leaves it for the next one: making and freeing it costs 50 us, as much as the
+// rest of a small grid's setup.  At most kSpareHost pieces wait, and they are
+// freed with the last handle that holds one.
+constexpr size_t kSpareHost = 4;
+struct HostSpare {
+  std::mutex m;
+  std::vector<std::pair<double*, int64_t>> spare;  // memory, doubles
+  int held = 0;
+  HostSpare() { spare.reserve(kSpareHost + 1); }  // nothing below allocates
+};
+HostSpare& host_spare() {
+  static HostSpare* p = new HostSpare;  // never destroyed: handles may be, at exit
+  return *p;
+}
+
+void take_host(rt_ctx c, int64_t doubles) {
+  HostSpare& h = host_spare();
+  std::lock_guard<std::mutex> lock(h.m);
+  for (size_t i = 0; i < h.spare.size(); ++i) {
+    if (h.spare[i].second < doubles) continue;
+    c->h_tally = h.spare[i].first;
+    c->h_tally_cap = h.spare[i].second;
+    h.spare.erase(h.spare.begin() + i);
+    h.held += 1;
+    return;
+  }
+  const int64_t cap = std::max<int64_t>(doubles, 1 << 13);  // 64 KB, 4093 cells
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_tally), cap * sizeof(double),
+                    hipHostMallocPortable) == hipSuccess) {
+    c->h_tally_cap = cap;
+    h.held += 1;
+  } else {
+    c->h_tally = nullptr;
+    (void)hipGetLastError();
+  }
+}
+
+void give_host(rt_ctx c) {
+  if (!c->h_tally) return;
+  HostSpare& h = host_spare();
+  std::lock_guard<std::mutex> lock(h.m);
+  h.spare.emplace_back(c->h_tally, c->h_tally_cap);
+  c->h_tally = nullptr;
+  c->h_tally_cap = 0;
+  h.held -= 1;
+  while (h.spare.size() > (h.held > 0 ? kSpareHost : 0)) {
+    (void)hipHostFree(h.spare.front().first);
+    h.spare.erase(h.spare.begin());
+  }
+}
+
+// The grid's arrays, all in one allocation.
+void free_grid(rt_ctx c) {
+  dev_free(c->grid_block);
+  c->cells = rt::CellSet();
+  c->d_T = c->d_x = c->d_p = nullptr;
+  c->d_acc = nullptr;
+  c->d_ovf = nullptr;
+  c->d_tally = nullptr;
 }
 
 void free_events(std::vector<std::pair<hipEvent_t, hipEvent_t>>& v) {
@@ -162,13 +217,29 @@ void free_events(std::vector<std::pair<hipEvent_t, hipEvent_t>>& v) {
   v.clear();
 }
 
+// The pairs of v, for the next record_begin (a pair may still be pending: the
+// next record replaces it).
+constexpr size_t kSpareEvents = 16;
+void recycle_events(rt_ctx c, std::vector<std::pair<hipEvent_t, hipEvent_t>>& v) {
+  while (!v.empty() && c->spare_events.size() < kSpareEvents) {
+    c->spare_events.push_back(v.back());
+    v.pop_back();
+  }
+  free_events(v);
+}
+
 rt_status record_begin(rt_ctx c, std::vector<std::pair<hipEvent_t, hipEvent_t>>& v) {
-  hipEvent_t a, b;
-  RT_HIP(c, hipEventCreate(&a));
-  hipError_t e = hipEventCreate(&b);
-  if (e != hipSuccess) { (void)hipEventDestroy(a); return hip_fail(c, e, "hipEventCreate"); }
-  v.emplace_back(a, b);
-  RT_HIP(c, hipEventRecord(a, c->stream));
+  if (!c->spare_events.empty()) {
+    v.push_back(c->spare_events.back());
+    c->spare_events.pop_back();
+  } else {
+    hipEvent_t a, b;
+    RT_HIP(c, hipEventCreate(&a));
+    hipError_t e = hipEventCreate(&b);
+    if (e != hipSuccess) { (void)hipEventDestroy(a); return hip_fail(c, e, "hipEventCreate"); }
+    v.emplace_back(a, b);
+  }
+  RT_HIP(c, hipEventRecord(v.back().first, c->stream));
   return RT_OK;
 }
 
@@ -186,7 +257,7 @@ rt_status drain_events(rt_ctx c, std::vector<std::pair<hipEvent_t, hipEvent_t>>&
     RT_HIP(c, hipEventElapsedTime(&f, e.first, e.second));
     t += f;
   }
-  free_events(v);
+  recycle_events(c, v);
   *ms += t;
   return RT_OK;
 }
@@ -263,10 +334,12 @@ rt_status rt_create(rt_ctx* out, int hip_device, void* hip_stream) {
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   e = hipSetDevice(hip_device);
   if (e == hipSuccess) e = scratch_address(hip_device, n, &c->noalloc_scratch);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_balance), 4 * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_segcount), sizeof(unsigned long long));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_adapt_evals), sizeof(unsigned long long));
-  if (e == hipSuccess) e = hipMemset(c->d_adapt_evals, 0, sizeof(unsigned long long));
+  // tally sums and ticket, segment count, kept evaluations
+  const size_t counters = (rt::kAccRow + 3) * sizeof(unsigned long long);
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_tally_sums), counters);
+  if (e == hipSuccess) e = hipMemset(c->d_tally_sums, 0, counters);
+  c->d_segcount = c->d_tally_sums ? c->d_tally_sums + rt::kAccRow + 1 : nullptr;
+  c->d_adapt_evals = c->d_tally_sums ? c->d_tally_sums + rt::kAccRow + 2 : nullptr;
   if (e != hipSuccess) {
     (void)hipGetLastError();  // not left for the next launch check
     rt_destroy(c);
@@ -286,16 +359,16 @@ rt_status rt_destroy(rt_ctx c) {
   (void)hipStreamSynchronize(c->stream);
   free_lines(c);
   free_gases(c);
-  free_cells(c);
-  dev_free(c->d_T); dev_free(c->d_x); dev_free(c->d_p);
+  free_grid(c);
   dev_free(c->d_bwall);
-  dev_free(c->d_abs); dev_free(c->d_emi); dev_free(c->d_acc); dev_free(c->d_balance);
-  dev_free(c->d_segcount);
-  dev_free(c->d_sbar); dev_free(c->d_win); dev_free(c->d_adapt_evals); dev_free(c->d_und);
+  dev_free(c->d_tally_sums);
+  give_host(c);
+  dev_free(c->d_sbar); dev_free(c->d_win); dev_free(c->d_und);
   dev_free(c->d_segs); dev_free(c->d_counts); dev_free(c->d_rays_explicit); dev_free(c->d_exit);
   dev_free(c->d_keys); dev_free(c->d_perm); dev_free(c->d_hist);
   free_events(c->trace_events); free_events(c->march_events); free_events(c->kappa_events);
   free_events(c->batch_events);
+  free_events(c->spare_events);
   rt::destroy_batch(c);
   rt::free_surrogate(c);
   delete c;
@@ -337,36 +410,39 @@ rt_status rt_setup_grid(rt_ctx c, int nx, int ny, int nz, double cell_m, const d
   }
   if (rt_status s = set_device(c)) return s;
   RT_HIP(c, hipStreamSynchronize(c->stream));
-  dev_free(c->d_T); dev_free(c->d_x); dev_free(c->d_p);
-  dev_free(c->d_abs); dev_free(c->d_emi); dev_free(c->d_acc);
-  c->d_ovf = nullptr;
-  free_cells(c);
+  free_grid(c);
   free_gases(c);
   c->have_grid = false;
   c->have_kappa = false;
   c->cells_valid = false;
   c->cells32_valid = false;
-  RT_HIP(c, dev_alloc(&c->d_T, n));
-  RT_HIP(c, dev_alloc(&c->d_x, n));
-  RT_HIP(c, dev_alloc(&c->d_p, n));
-  RT_HIP(c, dev_alloc(&c->d_abs, n));
-  RT_HIP(c, dev_alloc(&c->d_emi, n));
   // accumulator rows of the cells and the balance, then the overflow flag
   c->acc_rows = n * rt::acc_copies(n);
   const int64_t words = (c->acc_rows + rt::kBalRows) * rt::kAccRow;
-  RT_HIP(c, dev_alloc(&c->d_acc, (size_t)(words + 1)));
+  size_t total = 0;
+  auto take = [&](auto*& dst, int64_t count) {  // twice: offsets, then addresses
+    using E = std::remove_reference_t<decltype(*dst)>;
+    dst = reinterpret_cast<E*>(reinterpret_cast<uintptr_t>(c->grid_block) + total);
+    total += ((size_t)count * sizeof(E) + 255) / 256 * 256;
+  };
+  auto carve = [&] {
+    total = 0;
+    rt::CellSet& C = c->cells;
+    take(c->d_T, n); take(c->d_x, n); take(c->d_p, n);
+    take(c->d_acc, words + 1);
+    take(c->d_tally, 2 * n + 5);
+    take(C.G, n); take(C.beta, n); take(C.theta, n); take(C.lam2, n); take(C.P, n);
+    take(C.uf, n); take(C.lamf, n); take(C.Pf, n); take(C.beta2, n); take(C.theta2, n);
+    take(C.Gq, n);
+  };
+  carve();
+  const hipError_t e = dev_alloc(&c->grid_block, total);
+  if (e != hipSuccess) {
+    free_grid(c);
+    return hip_fail(c, e, "rt_setup_grid: device memory for the grid");
+  }
+  carve();
   c->d_ovf = reinterpret_cast<unsigned*>(c->d_acc + words);
-  RT_HIP(c, dev_alloc(&c->cells.G, n));
-  RT_HIP(c, dev_alloc(&c->cells.beta, n));
-  RT_HIP(c, dev_alloc(&c->cells.theta, n));
-  RT_HIP(c, dev_alloc(&c->cells.lam2, n));
-  RT_HIP(c, dev_alloc(&c->cells.P, n));
-  RT_HIP(c, dev_alloc(&c->cells.uf, n));
-  RT_HIP(c, dev_alloc(&c->cells.lamf, n));
-  RT_HIP(c, dev_alloc(&c->cells.Pf, n));
-  RT_HIP(c, dev_alloc(&c->cells.beta2, n));
-  RT_HIP(c, dev_alloc(&c->cells.theta2, n));
-  RT_HIP(c, dev_alloc(&c->cells.Gq, n));
   RT_HIP(c, hipMemcpyAsync(c->d_T, T, n * sizeof(double), hipMemcpyHostToDevice, c->stream));
   RT_HIP(c, hipMemcpyAsync(c->d_x, x, n * sizeof(double), hipMemcpyHostToDevice, c->stream));
   RT_HIP(c, hipMemcpyAsync(c->d_p, p, n * sizeof(double), hipMemcpyHostToDevice, c->stream));
@@ -385,7 +461,7 @@ rt_status rt_setup_grid(rt_ctx c, int nx, int ny, int nz, double cell_m, const d
   c->grid_epoch += 1;
   c->have_grid = true;
   c->stats = rt::Stats();
-  RT_HIP(c, rt::launch_zero(c));
+  RT_HIP(c, rt::launch_zero(c, false));
   return RT_OK;
 }
 
@@ -1015,19 +1091,31 @@ rt_status rt_tally(rt_ctx c, double* absorbed, double* emitted, double* balance)
   if (!c) return fail(c, RT_EINVAL, "rt_tally: NULL handle");
   if (!c->have_grid) return fail(c, RT_ESTATE, "rt_tally: call rt_setup_grid first");
   if (rt_status s = set_device(c)) return s;
-  RT_HIP(c, rt::launch_tally(c));
-  if (absorbed)
-    RT_HIP(c, hipMemcpyAsync(absorbed, c->d_abs, c->n_cells * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  if (emitted)
-    RT_HIP(c, hipMemcpyAsync(emitted, c->d_emi, c->n_cells * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  double bal[4];
-  unsigned ovf = 0;
-  RT_HIP(c, hipMemcpyAsync(bal, c->d_balance, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  RT_HIP(c, hipMemcpyAsync(&ovf, c->d_ovf, sizeof(ovf), hipMemcpyDeviceToHost, c->stream));
-  RT_HIP(c, hipStreamSynchronize(c->stream));
-  if (ovf)
+  const size_t n = (size_t)c->n_cells;
+  const int64_t results = 2 * c->n_cells + 5;
+  if (c->n_cells <= rt::kHostTallyCells && c->h_tally_cap < results) {
+    give_host(c);
+    take_host(c, results);  // or none: d_tally serves as well
+  }
+  const bool host = c->h_tally_cap >= results && c->n_cells <= rt::kHostTallyCells;
+  RT_HIP(c, rt::launch_tally(c, host ? c->h_tally : c->d_tally));
+  double tail[5];  // balance, overflow
+  if (host) {
+    RT_HIP(c, hipStreamSynchronize(c->stream));
+    if (absorbed) std::memcpy(absorbed, c->h_tally, n * sizeof(double));
+    if (emitted) std::memcpy(emitted, c->h_tally + n, n * sizeof(double));
+    std::memcpy(tail, c->h_tally + 2 * n, sizeof(tail));
+  } else {
+    if (absorbed)
+      RT_HIP(c, hipMemcpyAsync(absorbed, c->d_tally, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    if (emitted)
+      RT_HIP(c, hipMemcpyAsync(emitted, c->d_tally + n, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    RT_HIP(c, hipMemcpyAsync(tail, c->d_tally + 2 * n, sizeof(tail), hipMemcpyDeviceToHost, c->stream));
+    RT_HIP(c, hipStreamSynchronize(c->stream));
+  }
+  if (tail[4] != 0.0)
     return fail(c, RT_EDEVICE, "rt_tally: a tallied power was negative, not finite or not below 2^80 W");
-  if (balance) std::memcpy(balance, bal, sizeof(bal));
+  if (balance) std::memcpy(balance, tail, 4 * sizeof(double));
   return RT_OK;
 }
 
@@ -1035,12 +1123,11 @@ rt_status rt_reset_tally(rt_ctx c) {
   if (!c) return fail(c, RT_EINVAL, "rt_reset_tally: NULL handle");
   if (!c->have_grid) return fail(c, RT_ESTATE, "rt_reset_tally: call rt_setup_grid first");
   if (rt_status s = set_device(c)) return s;
-  RT_HIP(c, rt::launch_zero(c));
-  RT_HIP(c, hipMemsetAsync(c->d_adapt_evals, 0, sizeof(unsigned long long), c->stream));
-  double tmp = 0;
-  if (rt_status s = drain_events(c, c->trace_events, &tmp)) return s;
-  if (rt_status s = drain_events(c, c->march_events, &tmp)) return s;
-  if (rt_status s = drain_events(c, c->kappa_events, &tmp)) return s;
+  RT_HIP(c, rt::launch_zero(c, true));
+  // their times are dropped, so nothing waits for them
+  recycle_events(c, c->trace_events);
+  recycle_events(c, c->march_events);
+  recycle_events(c, c->kappa_events);
   c->stats.kappa_ms = 0;
   c->stats.line_evals = 0;
   c->stats.trace_ms = 0;

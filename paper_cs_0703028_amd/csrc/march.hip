@@ -133,67 +133,92 @@ __global__ void acc_normalize_kernel(unsigned long long* acc, int64_t groups) {
   if (i < groups) acc_normalize(acc + i * kAccDigits);
 }
 
-// Per-cell powers from the normalised accumulators.
-__global__ void acc_cells_kernel(const unsigned long long* __restrict__ acc, int64_t n_cells,
-                                 int copies, double* abs_, double* emi) {
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n_cells) return;
-  unsigned long long d[kAccRow];
-  acc_sum_copies(acc, c, n_cells, copies, d);
-  abs_[c] = acc_value(d);
-  emi[c] = acc_value(d + kAccDigits);
+// Digit sums of a block's 256 rows in thread 0: in the wavefront by lane
+// exchanges, then over the four wavefronts.
+__device__ void acc_block_sum(unsigned long long (&d)[kAccRow]) {
+  __shared__ unsigned long long red[3][kAccRow];
+#pragma unroll
+  for (int k = 0; k < kAccRow; ++k)
+    for (int off = 32; off > 0; off >>= 1) d[k] += __shfl_xor(d[k], off);
+  const int wave = threadIdx.x >> 6;
+  __syncthreads();  // an earlier sum's rows read
+  if (wave > 0 && (threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < kAccRow; ++k) red[wave - 1][k] = d[k];
+  __syncthreads();
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int k = 0; k < kAccRow; ++k) d[k] += red[0][k] + red[1][k] + red[2][k];
 }
 
-// The exact sum of accumulator rows [first, first + n): each digit is summed
-// over the rows as an integer (normalised digits are below 2^28 and there are
-// fewer than 2^31 rows), in a fixed-order tree over the block's 256 threads;
-// thread 0 gets the normalised digits in d.
-__device__ void acc_rows_sum(const unsigned long long* __restrict__ acc, int64_t first, int64_t n,
-                             unsigned long long (*red)[256], unsigned long long* d) {
-  const int t = threadIdx.x;
-  unsigned long long s[kAccRow];
+// Per-cell powers from the normalised accumulators, and balance = {entering,
+// sum emitted, sum absorbed, escaped}, each from the exact sum of its
+// accumulators (cells, or the balance rows), converted once.  A block adds its
+// cells' digits to the handle's sums (normalised digits are below 2^28 and
+// there are fewer than 2^31 cells); the last block to do so, which leaves them
+// and the ticket cleared, converts them.  out: absorbed[n], emitted[n],
+// balance[4], overflow flag.  13 us at 512 cells, where a launch over the cells
+// and one of a single block over all rows took 4 and 11 with a gap of 5, and 57
+// against 73 a call at 32^3 cells.
+__global__ __launch_bounds__(256) void tally_kernel(const unsigned long long* __restrict__ acc,
+                                                    int64_t n_cells, int copies, int64_t rows,
+                                                    unsigned long long* sums, double* out) {
+  __shared__ bool last;
+  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  unsigned long long d[kAccRow];
+  if (c < n_cells) {
+    acc_sum_copies(acc, c, n_cells, copies, d);
+    out[c] = acc_value(d);
+    out[n_cells + c] = acc_value(d + kAccDigits);
+  } else {
 #pragma unroll
-  for (int k = 0; k < kAccRow; ++k) s[k] = 0;
-  for (int64_t r = first + t; r < first + n; r += 256)
-#pragma unroll
-    for (int k = 0; k < kAccRow; ++k) s[k] += acc[r * kAccRow + k];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kAccRow; ++k) red[k][t] = s[k];
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (t < off)
-#pragma unroll
-      for (int k = 0; k < kAccRow; ++k) red[k][t] += red[k][t + off];
-    __syncthreads();
+    for (int k = 0; k < kAccRow; ++k) d[k] = 0;
   }
-  if (t == 0) {
+  acc_block_sum(d);
+  if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < kAccRow; ++k) d[k] = red[k][0];
+    for (int k = 0; k < kAccRow; ++k) atomicAdd(sums + k, d[k]);
+    __threadfence();
+    last = atomicAdd(sums + kAccRow, 1ull) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  // the balance rows
+#pragma unroll
+  for (int k = 0; k < kAccRow; ++k) d[k] = 0;
+  for (int64_t r = rows + threadIdx.x; r < rows + kBalRows; r += 256)
+#pragma unroll
+    for (int k = 0; k < kAccRow; ++k) d[k] += acc[r * kAccRow + k];
+  acc_block_sum(d);
+  if (threadIdx.x == 0) {
+    unsigned long long cells[kAccRow];
+#pragma unroll
+    for (int k = 0; k < kAccRow; ++k) cells[k] = atomicExch(sums + k, 0ull);
+    atomicExch(sums + kAccRow, 0ull);
     acc_normalize(d);
     acc_normalize(d + kAccDigits);
-  }
-}
-
-// balance = {entering, sum emitted, sum absorbed, escaped}, each from the
-// exact sum of its accumulators (cells, or the balance rows), converted once.
-__global__ __launch_bounds__(256) void tally_kernel(const unsigned long long* __restrict__ acc,
-                                                    int64_t rows, double* balance) {
-  __shared__ unsigned long long red[kAccRow][256];
-  unsigned long long cells[kAccRow], bal[kAccRow];
-  acc_rows_sum(acc, 0, rows, red, cells);
-  acc_rows_sum(acc, rows, kBalRows, red, bal);
-  if (threadIdx.x == 0) {
-    balance[0] = acc_value(bal);
+    acc_normalize(cells);
+    acc_normalize(cells + kAccDigits);
+    double* balance = out + 2 * n_cells;
+    balance[0] = acc_value(d);
     balance[1] = acc_value(cells + kAccDigits);
     balance[2] = acc_value(cells);
-    balance[3] = acc_value(bal + kAccDigits);
+    balance[3] = acc_value(d + kAccDigits);
+    // the flag behind the balance rows
+    balance[4] = *reinterpret_cast<const unsigned*>(acc + (rows + kBalRows) * kAccRow) ? 1.0 : 0.0;
   }
 }
 
-__global__ void zero_f64_kernel(double* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.0;
+// Clears the accumulators (and the overflow flag behind them), the segment
+// count and, where given, the kept evaluations.
+__global__ void zero_tally_kernel(unsigned long long* acc, int64_t n, unsigned long long* segs,
+                                  unsigned long long* evals) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) acc[i] = 0;
+  if (i == 0) {
+    *segs = 0;
+    if (evals) *evals = 0;
+  }
 }
 
 // Exclusive prefix sums of n histograms in place.  A histogram is
@@ -374,24 +399,17 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
   return hipGetLastError();
 }
 
-hipError_t launch_tally(rt_ctx c) {
-  hipLaunchKernelGGL(acc_cells_kernel, dim3((unsigned)((c->n_cells + 255) / 256)), dim3(256), 0,
-                     c->stream, c->d_acc, c->n_cells, acc_copies(c->n_cells), c->d_abs, c->d_emi);
-  hipLaunchKernelGGL(tally_kernel, dim3(1), dim3(256), 0, c->stream, c->d_acc, c->acc_rows,
-                     c->d_balance);
+hipError_t launch_tally(rt_ctx c, double* out) {
+  hipLaunchKernelGGL(tally_kernel, dim3((unsigned)((c->n_cells + 255) / 256)), dim3(256), 0,
+                     c->stream, c->d_acc, c->n_cells, acc_copies(c->n_cells), c->acc_rows,
+                     c->d_tally_sums, out);
   return hipGetLastError();
 }
 
-hipError_t launch_zero(rt_ctx c) {
-  auto z = [&](double* p, int64_t n) {
-    hipLaunchKernelGGL(zero_f64_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       c->stream, p, n);
-  };
-  z(c->d_abs, c->n_cells);
-  z(c->d_emi, c->n_cells);
-  z(reinterpret_cast<double*>(c->d_acc), (c->acc_rows + kBalRows) * kAccRow + 1);  // + overflow flag
-  z(c->d_balance, 4);
-  z(reinterpret_cast<double*>(c->d_segcount), 1);
+hipError_t launch_zero(rt_ctx c, bool evals) {
+  const int64_t n = (c->acc_rows + kBalRows) * kAccRow + 1;
+  hipLaunchKernelGGL(zero_tally_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream,
+                     c->d_acc, n, c->d_segcount, evals ? c->d_adapt_evals : nullptr);
   return hipGetLastError();
 }
 

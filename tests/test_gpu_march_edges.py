@@ -105,3 +105,26 @@ def test_rays_through_edges_and_corners(rt, O, o, d):
     t.close()
     a, e, b, _ = O.march(g, L, o, d, 1.0, O.kappa(g, L), O.planck_rows(g, L))
     _check(got, {"absorbed": a, "emitted": e, "balance": b})
+
+
+def test_tally_grid_sizes_and_repeats(rt, O):
+    """One handle over grids of one cell, around a block's 256 cells and around
+    the 2^16 cells up to which results come through host memory: powers against
+    the oracle, and a second tally the same bits."""
+    t = rt.Tracer(0)
+    for cells in [(1, 1, 1), (64, 2, 2), (257, 1, 1), (3, 4, 5), (256, 256, 1), (257, 256, 1), (5, 5, 5)]:
+        g = I.linear_T_grid(cells[0], 0.02, ny=cells[1], nz=cells[2], T_lo=500.0, T_hi=1500.0, x=0.1,
+                            T_wall=800.0)
+        L = I.line_list(40, 999.9, 1001.1, seed=5, dnu=0.01, n_nu=100)
+        print(f"tally {cells}", flush=True)
+        t.setup_grid(g)
+        t.setup_lines(L)
+        t.compute_kappa(rt.KAPPA_PLAIN)
+        t.trace_rays(3, 200)
+        one = t.tally()
+        for a, b in zip(one, t.tally()):
+            assert np.array_equal(a, b)
+        _check(one, O.run(g, L, 200, seed=3))
+        t.reset_tally()
+        assert all((a == 0).all() for a in t.tally())
+    t.close()
