@@ -907,13 +907,13 @@ rt_status rt_compute_kappa(rt_ctx c, int mode, float* kappa_dev, float* planck_d
 // rs.  timed: record the HIP events rt_get_stats reads (the entry point that
 // allocates nothing records none).
 static rt_status trace_with(rt_ctx c, const rt::RayScratch& rs, uint64_t seed, uint64_t begin,
-                            uint64_t count, double weight, bool f64, bool explicit_rays,
+                            uint64_t count, double weight, int prec_q, bool explicit_rays,
                             float* exit_dev, bool timed) {
   if (timed)
     if (rt_status s = record_begin(c, c->trace_events)) return s;
   // A launch adds at most (rays x chunks) terms to one accumulator word
   // (a ray crosses a cell once); the words are normalised after every launch.
-  const int64_t n_chunks = f64 ? std::max<int64_t>(1, c->ld / rt::kChunk) : rt::plain_chunks(c->n_nu);
+  const int64_t n_chunks = rt::march_chunks(c->n_nu, prec_q);
   const int64_t per_launch =
       std::max<int64_t>(1, std::min<int64_t>(rs.cap, rt::kAccMaxTerms / n_chunks));
   for (uint64_t off = 0; off < count; off += (uint64_t)per_launch) {
@@ -925,7 +925,7 @@ static rt_status trace_with(rt_ctx c, const rt::RayScratch& rs, uint64_t seed, u
                                 order ? rs.perm : nullptr));
     if (timed)
       if (rt_status s = record_begin(c, c->march_events)) return s;
-    RT_HIP(c, rt::launch_march(c, rs, n, weight, f64, exit_dev));
+    RT_HIP(c, rt::launch_march(c, rs, n, weight, prec_q, exit_dev));
     if (timed)
       if (rt_status s = record_end(c, c->march_events)) return s;
     c->stats.march_launches += 1;
@@ -936,10 +936,14 @@ static rt_status trace_with(rt_ctx c, const rt::RayScratch& rs, uint64_t seed, u
   return RT_OK;
 }
 
+static int march_form(rt_ctx c, int tally_prec, double n_rays_total) {
+  return tally_prec == RT_TALLY_F64 ? rt::prec_points(c, n_rays_total) : 0;
+}
+
 static rt_status trace_batches(rt_ctx c, uint64_t seed, uint64_t begin, uint64_t count,
-                               double weight, bool f64, bool explicit_rays, float* exit_dev) {
+                               double weight, int prec_q, bool explicit_rays, float* exit_dev) {
   if (rt_status s = ensure_batch(c, (int64_t)count)) return s;
-  return trace_with(c, rt::owned_rays(c), seed, begin, count, weight, f64, explicit_rays,
+  return trace_with(c, rt::owned_rays(c), seed, begin, count, weight, prec_q, explicit_rays,
                     exit_dev, true);
 }
 
@@ -971,7 +975,7 @@ rt_status rt_trace_rays(rt_ctx c, uint64_t seed, uint64_t n_rays_total, uint64_t
   if (ray_count == 0) return RT_OK;
   if (rt_status s = set_device(c)) return s;
   return trace_batches(c, seed, ray_begin, ray_count, ray_weight(c, (double)n_rays_total),
-                       tally_prec == RT_TALLY_F64, false, nullptr);
+                       march_form(c, tally_prec, (double)n_rays_total), false, nullptr);
 }
 
 rt_status rt_trace_rays_noalloc(rt_ctx c, uint64_t seed, uint64_t n_rays_total,
@@ -1013,7 +1017,7 @@ rt_status rt_trace_rays_noalloc(rt_ctx c, uint64_t seed, uint64_t n_rays_total,
   rs.max_segs = max_segs;
   rs.cap = cap;
   return trace_with(c, rs, seed, ray_begin, ray_count, ray_weight(c, (double)n_rays_total),
-                    tally_prec == RT_TALLY_F64, false, nullptr, false);
+                    march_form(c, tally_prec, (double)n_rays_total), false, nullptr, false);
 }
 
 rt_status rt_trace_explicit(rt_ctx c, int n_rays, const int64_t* O, const int64_t* D,
@@ -1074,7 +1078,7 @@ rt_status rt_trace_explicit(rt_ctx c, int n_rays, const int64_t* O, const int64_
     }
     exit_dev = c->d_exit;
   }
-  if (rt_status s = trace_batches(c, 0, 0, (uint64_t)n_rays, weight, tally_prec == RT_TALLY_F64,
+  if (rt_status s = trace_batches(c, 0, 0, (uint64_t)n_rays, weight, march_form(c, tally_prec, n_rays),
                                   true, exit_dev))
     return s;
   RT_HIP(c, hipStreamSynchronize(c->stream));  // the host ray buffer goes out of scope

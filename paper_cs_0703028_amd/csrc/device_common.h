@@ -16,7 +16,6 @@ constexpr int kLineTile = 256;
 constexpr int kKappaCells = 8;   // cells per lane in the line sum
 constexpr int kKappaPoints = 2;  // nu points per lane in the line sum
 constexpr int kKappaTilePoints = kKappaThreads * kKappaPoints;
-constexpr int kQ = kChunk / 64;  // contiguous nu points per lane, precision form's march
 constexpr int kPlainQ = 12;      // the same in the plain form's (kMarchPoints = 64 kPlainQ)
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -1055,7 +1054,7 @@ __device__ __forceinline__ double acc_value(const unsigned long long* d) {
 // chunk go the same way to the balance row.
 //
 // The plain form (march_plain) takes kPlainQ contiguous points per lane, the
-// precision form (march_wave) kQ, Planck values from the table, the degree-5
+// precision form (march_prec) 8 or 4, Planck values from the table, the degree-5
 // branch and FP64 partial sums.
 struct MarchWave {
   const float* kappa;   // row c at kappa + c * ld, column j - col0
@@ -1102,127 +1101,54 @@ __host__ __device__ inline void planck_cubic(const double f[4], double half, dou
 }
 
 // Per-wavefront LDS staging of the precision form's per-segment partial sums:
-// [kSegs][2][64].
+// [kSegs][64], even entries absorbed, odd emitted, each over a pair of lanes.
 struct PrecStage {
-  static constexpr int kSegs = 4;
-  static constexpr int kEntries = kSegs * 2 * 64;
+  static constexpr int kSegs = 8;
+  static constexpr int kEntries = kSegs * 64;
 };
 
+__device__ __forceinline__ void prec_stage(double* stage, int np, int lane, double ab, double em) {
+  const double a2 = ab + dpp_f64<0xB1>(ab);  // quad_perm [1,0,3,2]
+  const double e2 = em + dpp_f64<0xB1>(em);
+  stage[np * 64 + lane] = (lane & 1) ? e2 : a2;
+}
+
 // Adds np staged entries to the accumulators.  Entry s is segment k0 + s of
-// the ray, or the ray's balance row bal_row once k0 + s reaches ns.  Value v = 2 s + q
-// (q = 0 absorbed or entering, 1 emitted or escaped) is summed by
-// 64 / (2 kSegs) lanes, each over a fixed run of the 64 partials, then across
-// those lanes with DPP: the same order every time.
-__device__ __forceinline__ void tally_flush(const MarchWave& a, const double* stage,
-                                            const int2* sg, int ns, int k0, int np, int lane,
-                                            int64_t row0, int64_t bal_row) {
-  constexpr int V = 2 * PrecStage::kSegs;
-  constexpr int LPV = 64 / V;  // lanes per value
-  constexpr int E = 64 / LPV;  // partials per lane
-  static_assert(LPV == 8, "flush layout");
+// the ray, or the ray's balance row bal_row once k0 + s reaches ns.  Eight
+// lanes per entry, each over 8 consecutive doubles (4 absorbed or entering, 4
+// emitted or escaped), then across the eight with DPP: the same order every
+// time.
+__device__ __forceinline__ void prec_flush(const MarchWave& a, const double* stage,
+                                           const int2* sg, int ns, int k0, int np, int lane,
+                                           int64_t row0, int64_t bal_row) {
+  static_assert(PrecStage::kSegs == 8, "flush layout");
   __builtin_amdgcn_wave_barrier();
   // a flush runs once per kSegs segments: its lane-derived addresses are
   // formed here rather than hoisted and kept live across the march loop
   int ln = lane;
   asm volatile("" : "+v"(ln));
-  const int v = ln / LPV, part = ln % LPV;
-  const double* src = stage + v * 64 + part * E;
-  double s = src[0];
+  const int seg = ln >> 3, part = ln & 7;
+  const double* src = stage + ln * 8;
+  double s0 = src[0], s1 = src[1];
 #pragma unroll
-  for (int i = 1; i < E; ++i) s += src[i];
-  s += dpp_f64<0xB1>(s);   // quad_perm [1,0,3,2]
-  s += dpp_f64<0x4E>(s);   // quad_perm [2,3,0,1]
-  s += dpp_f64<0x141>(s);  // row_half_mirror: the two quads of 8 lanes
+  for (int i = 2; i < 8; i += 2) {
+    s0 += src[i];
+    s1 += src[i + 1];
+  }
+  s0 += dpp_f64<0xB1>(s0);   // quad_perm [1,0,3,2]
+  s1 += dpp_f64<0xB1>(s1);
+  s0 += dpp_f64<0x4E>(s0);   // quad_perm [2,3,0,1]
+  s1 += dpp_f64<0x4E>(s1);
+  s0 += dpp_f64<0x141>(s0);  // row_half_mirror: the two quads of 8 lanes
+  s1 += dpp_f64<0x141>(s1);
   __builtin_amdgcn_wave_barrier();
-  const int seg = v >> 1;
-  if (part == 0 && seg < np) {
+  if (part < 2 && seg < np) {
     const int k = k0 + seg;
     const int64_t row = k < ns ? row0 + sg[k].x : bal_row;
-    acc_add(a.acc + row * kAccRow + (v & 1) * kAccDigits, s * a.weight, a.ovf);
+    acc_add(a.acc + row * kAccRow + part * kAccDigits, (part ? s1 : s0) * a.weight, a.ovf);
   }
 }
 
-// Precision form.  stage: this wavefront's PrecStage::kEntries LDS entries;
-// slot: the ray's index in its launch, which picks its balance row.
-template <bool EXIT>
-__device__ __forceinline__ void march_wave(const MarchWave& a, const int2* sg, int ns, int64_t j,
-                                           int lane, float* exit_row, double* stage, int64_t slot) {
-  constexpr int kSegs = PrecStage::kSegs;
-  const int64_t row0 = a.row0 + (slot & a.rep_mask) * a.rep_rows;
-  const int64_t col = j - a.col0;
-  float I[kQ];
-#pragma unroll
-  for (int h = 0; h < kQ / 4; ++h) {
-    const float4 v = *reinterpret_cast<const float4*>(a.bwall + j + 4 * h);
-    I[4 * h] = v.x; I[4 * h + 1] = v.y; I[4 * h + 2] = v.z; I[4 * h + 3] = v.w;
-  }
-  double enter = 0;
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) enter += (double)I[q];
-  const float nlog2e = -1.4426950408889634f;
-  int np = 0, k0 = 0;  // staged entries, and the segment of the first
-  for (int k = 0; k < ns; ++k) {
-    const int2 s = sg[k];
-    const int64_t c = s.x;
-    const float l = __int_as_float(s.y);
-    const float xs = l * nlog2e;
-    float kv[kQ], bv[kQ];
-#pragma unroll
-    for (int h = 0; h < kQ / 4; ++h) {
-      const float4 v = *reinterpret_cast<const float4*>(a.kappa + c * a.ld + col + 4 * h);
-      kv[4 * h] = v.x; kv[4 * h + 1] = v.y; kv[4 * h + 2] = v.z; kv[4 * h + 3] = v.w;
-    }
-#pragma unroll
-    for (int h = 0; h < kQ / 4; ++h) {
-      const float4 v = *reinterpret_cast<const float4*>(a.planck + c * a.ld + col + 4 * h);
-      bv[4 * h] = v.x; bv[4 * h + 1] = v.y; bv[4 * h + 2] = v.z; bv[4 * h + 3] = v.w;
-    }
-    // a = 1 - e^{-tau} per point
-    float av[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      const float tau = kv[q] * l;
-      const float big = 1.0f - __builtin_amdgcn_exp2f(kv[q] * xs);
-      av[q] = tau < 0.25f ? poly5(tau) : big;
-    }
-    double ab = 0, em = 0;
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) {
-      ab += (double)(I[q] * av[q]);
-      em += (double)(bv[q] * av[q]);
-      I[q] = fmaf(-(I[q] - bv[q]), av[q], I[q]);
-    }
-    // the update of I is complete here, so a[] dies before the staging and
-    // the flush below (the scheduler would otherwise sink the updates past
-    // them and keep a[] and B[] live across the flush)
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) asm volatile("" ::"v"(I[q]));
-    double* st = stage + np * 128;
-    st[lane] = ab;
-    st[64 + lane] = em;
-    if (++np == kSegs) {
-      tally_flush(a, stage, sg, ns, k0, np, lane, row0, 0);
-      k0 += np;
-      np = 0;
-    }
-  }
-  double esc = 0;
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) esc += (double)I[q];
-  if (EXIT) {
-#pragma unroll
-    for (int h = 0; h < kQ / 4; ++h)
-      *reinterpret_cast<float4*>(exit_row + col + 4 * h) =
-          make_float4(I[4 * h], I[4 * h + 1], I[4 * h + 2], I[4 * h + 3]);
-  }
-  // np < kSegs here: one more entry, the balance row's (entering, escaped)
-  double* st = stage + np * 128;
-  st[lane] = enter;
-  st[64 + lane] = esc;
-  tally_flush(a, stage, sg, ns, k0, np + 1, lane, row0, a.bal_row0 + (slot & a.bal_mask));
-}
-
-// ------------------------------------------------------- the plain form's march
 // Wave-uniform loads through the scalar cache: for data that no block of the
 // same launch writes (the persistent batched kernel, whose blocks write each
 // other's segments, loads the ordinary way and broadcasts).
@@ -1241,6 +1167,100 @@ __device__ __forceinline__ FloatQuad load_quad(const float4* p) {
       reinterpret_cast<uintptr_t>(p));
 }
 
+// Precision form: points [j0, j0 + 64 Q) of one ray, j0 the same for the wave.
+// stage: this wavefront's PrecStage::kEntries LDS entries; slot: the ray's
+// index in its launch, which picks its balance row.
+//
+// A point takes 20 instructions and 8 bytes of the tables, a segment 40 more.
+// Where rays share their cells' rows the instructions bound it and Q = 8 is
+// taken: 24 points per lane left 8^3 cells too few wavefronts (1024 rays of
+// 10,000 points 134 -> 111 us, 4096 rays 300 -> 247).  Where they do not, the
+// rows come from beyond L2 at its rate, 7.4 TB/s, and what counts is how much
+// of the launch's current chunk the caches hold: Q = 4 halves that chunk (24^3
+// cells, 16,384 rays of 20,000 points: Q = 24 8.85 ms, 8 8.48, 4 7.99; 28^3,
+// 65,536 rays 38.6, 38.1, 32.3).
+template <bool EXIT, int Q>
+__device__ __forceinline__ void march_prec(const MarchWave& a, const int2* sg, int ns, int64_t j0,
+                                           int lane, float* exit_row, double* stage, int64_t slot) {
+  constexpr int kSegs = PrecStage::kSegs;
+  const int64_t row0 = a.row0 + (slot & a.rep_mask) * a.rep_rows;
+  float I[Q];
+#pragma unroll
+  for (int h = 0; h < Q / 4; ++h) {
+    const float4 v = *reinterpret_cast<const float4*>(a.bwall + j0 + lane * Q + 4 * h);
+    I[4 * h] = v.x; I[4 * h + 1] = v.y; I[4 * h + 2] = v.z; I[4 * h + 3] = v.w;
+  }
+  double enter = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) enter += (double)I[q];
+  const float nlog2e = -1.4426950408889634f;
+  int np = 0, k0 = 0;  // staged entries, and the segment of the first
+  IntPair s = ns > 0 ? load_seg<true>(sg) : IntPair{0, 0};
+  const unsigned voff = (unsigned)lane * (4 * Q);
+  const char* kchunk = reinterpret_cast<const char*>(a.kappa + j0 - a.col0);
+  const char* pchunk = reinterpret_cast<const char*>(a.planck + j0 - a.col0);
+  for (int k = 0; k < ns; ++k) {
+    const int64_t c = s.x;
+    const float l = __int_as_float(s.y);
+    const float xs = l * nlog2e;
+    float kv[Q], bv[Q];
+    const char* krow = kchunk + c * (a.ld * 4);
+    const char* prow = pchunk + c * (a.ld * 4);
+    unsigned vo = voff;  // opaque: the rows' addresses stay uniform, not per lane
+    asm("" : "+v"(vo));
+#pragma unroll
+    for (int h = 0; h < Q / 4; ++h) {
+      const float4 v = *reinterpret_cast<const float4*>(krow + vo + 16 * h);
+      kv[4 * h] = v.x; kv[4 * h + 1] = v.y; kv[4 * h + 2] = v.z; kv[4 * h + 3] = v.w;
+    }
+#pragma unroll
+    for (int h = 0; h < Q / 4; ++h) {
+      const float4 v = *reinterpret_cast<const float4*>(prow + vo + 16 * h);
+      bv[4 * h] = v.x; bv[4 * h + 1] = v.y; bv[4 * h + 2] = v.z; bv[4 * h + 3] = v.w;
+    }
+    if (k + 1 < ns) s = load_seg<true>(sg + k + 1);  // the next segment's, early
+    // a = 1 - e^{-tau} per point
+    float av[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const float tau = kv[q] * l;
+      const float big = 1.0f - __builtin_amdgcn_exp2f(kv[q] * xs);
+      av[q] = tau < 0.25f ? poly5(tau) : big;
+    }
+    double ab = 0, em = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      ab += (double)(I[q] * av[q]);
+      em += (double)(bv[q] * av[q]);
+      I[q] = fmaf(-(I[q] - bv[q]), av[q], I[q]);
+    }
+    // the update of I is complete here, so a[] dies before the staging and
+    // the flush below (the scheduler would otherwise sink the updates past
+    // them and keep a[] and B[] live across the flush)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) asm volatile("" ::"v"(I[q]));
+    prec_stage(stage, np, lane, ab, em);
+    if (++np == kSegs) {
+      prec_flush(a, stage, sg, ns, k0, np, lane, row0, 0);
+      k0 += np;
+      np = 0;
+    }
+  }
+  double esc = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) esc += (double)I[q];
+  if (EXIT) {
+#pragma unroll
+    for (int h = 0; h < Q / 4; ++h)
+      *reinterpret_cast<float4*>(exit_row + j0 - a.col0 + lane * Q + 4 * h) =
+          make_float4(I[4 * h], I[4 * h + 1], I[4 * h + 2], I[4 * h + 3]);
+  }
+  // np < kSegs here: one more entry, the balance row's (entering, escaped)
+  prec_stage(stage, np, lane, enter, esc);
+  prec_flush(a, stage, sg, ns, k0, np + 1, lane, row0, a.bal_row0 + (slot & a.bal_mask));
+}
+
+// ------------------------------------------------------- the plain form's march
 // Staging of the plain form: one float per lane and segment.  Lanes 2 i and
 // 2 i + 1 hold the pair's absorbed and emitted sums (one DPP add each and a
 // select), so 16 segments take the 4 KB that 8 took unpaired, and a flush,
@@ -1256,14 +1276,14 @@ __device__ __forceinline__ void plain_stage(float* stage, int np, int lane, floa
   stage[np * 64 + lane] = (lane & 1) ? e2 : a2;
 }
 
-// Adds np staged entries to the accumulators (entries as tally_flush).  Four
+// Adds np staged entries to the accumulators (entries as prec_flush).  Four
 // lanes per entry, each over 16 consecutive floats (8 absorbed, 8 emitted),
 // then across the four with DPP: the same order every time.
 __device__ __forceinline__ void plain_flush(const MarchWave& a, const float* stage, const int2* sg,
                                             int ns, int k0, int np, int lane, int64_t row0,
                                             int64_t bal_row) {
   __builtin_amdgcn_wave_barrier();
-  int ln = lane;  // see tally_flush
+  int ln = lane;  // see prec_flush
   asm volatile("" : "+v"(ln));
   const int seg = ln >> 2;
   const float4* src = reinterpret_cast<const float4*>(stage + ln * 16);

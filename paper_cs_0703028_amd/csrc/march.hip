@@ -7,7 +7,7 @@
 //                traversal -> per-ray list of (cell, length) segments
 //   march      : Eq. (3) applied cell after cell for every nu point; each
 //                wavefront owns one ray and a kChunk-point spectral chunk
-//                (dev::march_wave); the absorbed and emitted power of the
+//                (dev::march_prec); the absorbed and emitted power of the
 //                chunk per segment is summed across the wavefront in a fixed
 //                order and added to the cell's fixed-point accumulator
 //   tally      : the accumulators as FP64 powers per cell, and the energy
@@ -116,15 +116,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
 }
 
 // Precision form (Planck table, FP64 partial sums).
-template <bool EXIT>
+template <bool EXIT, int Q>
 __global__ __launch_bounds__(256) void march_prec_kernel(MarchArgs a) {
   __shared__ double stage[4][PrecStage::kEntries];
   int64_t ray;
   int wave, lane;
   if (!march_place(a, ray, wave, lane)) return;
-  march_wave<EXIT>(a.w, a.segs + ray * a.max_segs, a.counts[ray],
-                   (int64_t)blockIdx.y * kChunk + lane * kQ, lane,
-                   EXIT ? a.exit_I + ray * a.w.ld : nullptr, stage[wave], ray);
+  march_prec<EXIT, Q>(a.w, a.segs + ray * a.max_segs, a.counts[ray], (int64_t)blockIdx.y * 64 * Q,
+                      lane, EXIT ? a.exit_I + ray * a.w.ld : nullptr, stage[wave], ray);
 }
 
 // Carries of every accumulator row (rows x 2 digit groups).
@@ -348,7 +347,29 @@ bool planck_cubic_fits(double T_min, double T_max, double nu0, double dnu, int n
   return true;
 }
 
-hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double weight, bool prec,
+// Where the visits of a cell's rows (of n_rays_total rays, a mean path of 3 /
+// (1/nx + 1/ny + 1/nz) segments) are few for the size of the grid, the rows
+// come from beyond L2 and 4 points per lane are faster.  The line, from 16^3 to
+// 28^3 cells (8 against 4, microseconds): 16^3, 10,000 points 80 visits 2647,
+// 2582; 160 4464, 5113.  20^3 80: 6052, 5260; 160 10,533, 10,041.  24^3 160:
+// 19,727, 17,370; 320 29,633, 34,912.  12^3 40: 1103, 1141.  It depends on the
+// ray set and not on the part of it in a call, so that every split of a set
+// adds the same sums.
+int prec_points(rt_ctx c, double n_rays_total) {
+  const double cells = (double)c->n_cells;
+  const double segs = 3.0 / (1.0 / c->nx + 1.0 / c->ny + 1.0 / c->nz);
+  return cells >= 4096 && n_rays_total * segs / cells <= std::min(cells / 64, 200.0) &&
+                 c->n_nu <= (1 << 22)  // a grid's y ends at 65,535
+             ? 4
+             : 8;
+}
+
+// prec_q: points per lane of the precision form, 0 for the plain form.
+int64_t march_chunks(int64_t n_nu, int prec_q) {
+  return prec_q ? (n_nu + 64 * prec_q - 1) / (64 * prec_q) : plain_chunks(n_nu);
+}
+
+hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double weight, int prec_q,
                         float* exit_dev) {
   MarchArgs a;
   a.w.kappa = c->kappa;
@@ -376,16 +397,19 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
   a.max_segs = s.max_segs;
   a.n_rays = count;
   a.exit_I = exit_dev;
-  // the columns past n_nu hold zeros and add nothing: the plain form stops at
-  // the last chunk that holds a point
-  const int64_t n_chunks = prec ? c->ld / kChunk : plain_chunks(c->n_nu);
+  // the columns past n_nu hold zeros and add nothing: the march stops at the
+  // last chunk that holds a point
+  const int64_t n_chunks = march_chunks(c->n_nu, prec_q);
   // x: at most 2^21 rays a batch, 2^19 blocks; y: n_nu < 2^24 points, 2^15 chunks
   const dim3 g((unsigned)(8 * a.ray_blocks_x), (unsigned)n_chunks), t(256);
   // seven wavefronts per SIMD instead of eight: 32^3 workload 498 -> 496 ms
   const unsigned pad = 6000;
-  if (prec) {
-    if (exit_dev) hipLaunchKernelGGL((march_prec_kernel<true>), g, t, 0, c->stream, a);
-    else hipLaunchKernelGGL((march_prec_kernel<false>), g, t, 0, c->stream, a);
+  if (prec_q == 4) {
+    if (exit_dev) hipLaunchKernelGGL((march_prec_kernel<true, 4>), g, t, 0, c->stream, a);
+    else hipLaunchKernelGGL((march_prec_kernel<false, 4>), g, t, 0, c->stream, a);
+  } else if (prec_q) {
+    if (exit_dev) hipLaunchKernelGGL((march_prec_kernel<true, 8>), g, t, 0, c->stream, a);
+    else hipLaunchKernelGGL((march_prec_kernel<false, 8>), g, t, 0, c->stream, a);
   } else if (c->planck_cubic) {
     if (exit_dev) hipLaunchKernelGGL((march_kernel<true, true>), g, t, pad, c->stream, a);
     else hipLaunchKernelGGL((march_kernel<false, true>), g, t, pad, c->stream, a);

@@ -350,7 +350,11 @@ hipError_t launch_planck_cubics(rt_ctx c, const double* theta, int64_t n, float4
 int arith_operands(int op);
 hipError_t launch_arith(rt_ctx c, int op, const float* a, const float* b, const float* z,
                         float* out, int64_t n);
-hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double weight, bool prec,
+// points per lane of the precision form's march of a set of rays, and the
+// spectral chunks of a march (prec_q 0: the plain form)
+int prec_points(rt_ctx c, double n_rays_total);
+int64_t march_chunks(int64_t n_nu, int prec_q);
+hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double weight, int prec_q,
                         float* exit_dev);
 hipError_t launch_tally(rt_ctx c, double* out);
 hipError_t launch_zero(rt_ctx c, bool evals);  // evals: the kept evaluations too
