@@ -386,17 +386,29 @@ hipError_t launch_gas_factor(rt_ctx c, int g) {
 }
 
 // The plain line sum of a.n_tiles tiles of kKappaTilePoints points for
-// `groups` groups of cells.  A block's latency sets the time of a launch that
-// fills the chip little more than once (five blocks fit a CU): below 6 blocks
-// per CU it is cut into tiles of half the points, with the same values bit for
-// bit (6^3 cells, 3,037 points, 162 blocks: 36 -> 30 us; 8^3, 10,000 points,
-// 1,344 blocks: 110 -> 104 us at 25 lines per cm^-1, 932 -> 753 us at 200,
-// 42 us either way at 5; 10^3, 2,625 blocks: 173 us against 176).
+// `groups` groups of cells, or of twice as many tiles of half the points, with
+// the same values bit for bit.  Half tiles have six wavefronts a SIMD instead
+// of five and a tail half as long, and form a line's parameters and a span's
+// interpolation from its far nodes in more blocks.  They win (whole against
+// half tiles, microseconds):
+// - in launches of few blocks, below 6 a CU: 1,344 blocks, windows of +-500
+//   points, 0.25 lines a point 114, 105 (and 1,932 blocks 141, 141; 6,912 391,
+//   448);
+// - where windows of up to +-256 points leave the far nodes little: +-100
+//   points, 0.5 and 6.5 lines a point, 19,200 blocks 1112, 1040 and 19,621,
+//   16,190, 1,539 blocks 162, 117 and 2512, 1687; +-250, 1.2 lines, 19,200
+//   blocks 4091, 3660;
+// - where the list is dense enough that its lines outweigh a span's fixed
+//   work, unless the window makes the parameters of the lines around a tile the
+//   larger part: +-500, 1 line a point, 19,200 blocks 4535, 4440, 1,539 blocks
+//   543, 460 (0.25 a point, 19,200 blocks: 924, 1062); +-1000, 1 line a point
+//   3672, 4155.
 static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
   const int64_t blocks = groups * a.n_tiles * a.parts;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
-  if (blocks < 6 * 256) {
+  const double lines_per_point = (double)a.t.L.n / ((double)a.t.n_nu + 2.0 * a.t.K);
+  if (blocks < 6 * 256 || a.t.K <= 256 || (a.t.K <= 512 && lines_per_point >= 0.9)) {
     a.n_tiles *= 2;
     a.tile_begin *= 2;
     hipLaunchKernelGGL((kappa_linesum_kernel<false, false, 1>), dim3((unsigned)(2 * blocks)),

@@ -90,3 +90,17 @@ def test_tile_sizes_give_the_same_values(rt):
         getattr(big, a)[:64] = getattr(small, a)
     ks, kb = _kappa(rt, small, L), _kappa(rt, big, L)
     assert np.array_equal(ks, kb[:64])
+
+
+@pytest.mark.parametrize("K,lines,cells", [(256, 300, 1600), (257, 300, 1600), (500, 2000, 1600),
+                                           (513, 2100, 1600), (500, 300, 1360), (500, 300, 1366)])
+def test_whole_and_half_tiles(rt, O, K, lines, cells):
+    """Launches at either side of each line between whole and half tiles (window,
+    lines per point, blocks): sampled cells against the oracle."""
+    n_nu, dnu = 1000, 0.01
+    L = I.line_list(lines, 1000.0 - K * dnu, 1000.0 + (n_nu + K) * dnu, seed=K, dnu=dnu, n_nu=n_nu,
+                    cutoff=K * dnu)
+    g = I.linear_T_grid(cells, 0.1, ny=3, nz=1, T_lo=300.0, T_hi=1700.0, x=0.1)
+    print(f"K {K} {lines} lines {g.n_cells} cells", flush=True)
+    pick = np.arange(0, g.n_cells, 97, dtype=np.int32)
+    _check(_kappa(rt, g, L)[pick], O.kappa(g, L, pick), n_nu)
