@@ -14,12 +14,9 @@
 //                            takes any the list had no room for)
 //   kappa_adaptive_kernel  : the plain FP32 line sum of Eq. (2) over those
 //                            windows.  A block stages only the lines whose
-//                            kept window meets its 512 points; a wavefront
-//                            sums its 128 points in passes (two of 64, or
-//                            from eps = 3e-4 four of 32 with 4 cells per
-//                            lane), each over the staged lines whose window
-//                            meets it: first those covering all of its
-//                            points (no membership test), then the rest
+//                            kept window meets its 256 points; a wavefront
+//                            sums its span of 64, each line under the mask of
+//                            the points it keeps, or at the span's nodes
 //   adaptive_wing_kernel   : (wing-return form, an extension) per cell, the
 //                            Lorentz mass of the points its run's windows
 //                            drop, priced by the midpoint rule and spread
@@ -49,16 +46,6 @@ static_assert(kLineTile <= 256, "staged line indices are kept in bytes");
 
 constexpr int kAdThreads = 256;
 constexpr int kCellF = 8;  // floats per cell in the screening's cell record
-constexpr int kAdRec = kLineRec;  // floats per staged line
-// passes per wavefront of the windowed sum: two of 64 points (32^3 workload:
-// 20.3 against 22.5 ms at eps = 1e-3, 71.0 against 70.1 ms at 1e-6)
-constexpr int kAdPasses = 2;
-// From this tolerance on, the windowed sum takes four passes of 32 points
-// with 4 cells per lane: windows of a few tens of points (32^3 workload:
-// 16.1 against 17.3 ms at eps = 1e-3, 11.7 against 12.7 at 1e-2 with the
-// wing return; equal at 1e-4; 51.8 against 49.2 at 1e-5).
-constexpr double kAdNarrowTol = 3e-4;
-
 // Eq. (1) strength ratio in binary64: q exp(-c2 E/T) / exp(-c2 E/T_ref)
 // * expm1(-c2 nu/T) / expm1(-c2 nu/T_ref), taken as
 // q exp(c2 E (1/T_ref - 1/T)) expm1(-nu c2/T) / expm1(-c2 nu/T_ref) with the
@@ -417,196 +404,212 @@ __global__ __launch_bounds__(kAdThreads) void adaptive_window_scan_kernel(Window
   add_block_count(kept, a.kept);
 }
 
-// Adds one staged line to P points x CPL cells of a lane: the cells
-// cg CPL .. cg CPL + CPL - 1 of the run (their amplitudes and squared half
-// widths sit at rec + 4 + 2 CPL cg).  As dev::add_line_terms otherwise.
-template <bool FULL, int P, int CPL>
-__device__ __forceinline__ void add_line_terms_cells(const float* rec, const float (&jf)[P], int cg,
-                                                     float (&part)[P][CPL]) {
-  const float4 h = *reinterpret_cast<const float4*>(rec);
-  float dv[P];
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const float t = jf[p] - h.x;
-    const float d = t - h.y;
-    if (FULL) {
-      dv[p] = d;
-    } else {
-      const bool in = (t >= h.z) & (t <= h.w);
-      dv[p] = in ? d : __builtin_inff();
-    }
-  }
-  const float* ag = rec + 4 + 2 * CPL * cg;
-#pragma unroll
-  for (int c = 0; c < CPL; c += 2) {
-    const float4 v = *reinterpret_cast<const float4*>(ag + 2 * c);
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      part[p][c] = fmaf(v.x, fast_rcp(fmaf(dv[p], dv[p], v.y)), part[p][c]);
-      part[p][c + 1] = fmaf(v.z, fast_rcp(fmaf(dv[p], dv[p], v.w)), part[p][c + 1]);
-    }
-  }
-}
-
-// One block: points [j0, j0 + 512) of the run of 8 cells `run`, as the plain
-// line-sum tile (dev::kappa_tile) with a window per (run, line): the staged
-// line records (dev::kLineRec) carry the run's window offsets lo, hi.  Each
-// wavefront owns 128 points and sums them in NQ passes: a pass lists only
-// the staged lines whose window meets its points, so a narrow window costs
-// the points of the passes it meets rather than all 128.  CPL = 8: a lane
-// takes one point of a 64-point row for all 8 cells; CPL = 4: a half
-// wavefront takes 32 points for 4 cells, which halves a pass's span for
-// windows of a few tens of points.
-template <int NQ, int CPL>
-__global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void kappa_adaptive_kernel(KappaTile a,
-                                                                       const uint32_t* __restrict__ win,
-                                                                       int n_tiles,
-                                                                       const double* __restrict__ wing) {
+// One block: points [j0, j0 + 256) of the run of 8 cells `run`, a span of 64
+// points per wavefront; a lane takes points pt and pt + 32 for 4 of the cells,
+// as dev::kappa_tile_far, with a window per (run, line).
+//
+// A block stages only the lines whose kept window meets its points.  A lane
+// then holds what one staged line keeps of the wavefront's span, as two masks
+// of 32 points, and the wavefront walks the lines by what they keep: some of
+// the lower half, some of the upper, all, some of both.  The terms run under
+// the masks, so a line that keeps part of a half costs no test per point and
+// the half it misses nothing.  Lines that keep the whole span from far enough
+// are left to a list; where a span has kFarLines of them they are summed at its
+// Chebyshev nodes, which are interpolated once.
+//
+// Issue-bound: 0.93 of the SIMD cycles, two thirds of them terms (3.5
+// instructions each), the rest line parameters, classifying and selection.
+// 32^3 cells, 50,000 points, 20,000 lines at tolerances 1e-2, 1e-3, 1e-4 and
+// 1e-5, the whole form with wing return: 10.4, 14.8, 22.0 and 31.0 ms (with
+// tests per point in passes of 32 or 64 points and no nodes: 11.5, 17.9, 30.7
+// and 50.8).
+constexpr int kFarLines = 16;  // a span's interpolation costs as much as 16 lines save
+__global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(6))) void kappa_adaptive_kernel(
+    KappaTile a, const uint32_t* __restrict__ win, int n_tiles, const double* __restrict__ wing) {
   constexpr int C = kKappaCells;
-  constexpr int ROW = 64 * CPL / C;                 // points of a row of lanes
-  constexpr int P = 64 * kKappaPoints / (ROW * NQ); // points per lane per pass
-  static_assert(C % CPL == 0 && P * ROW * NQ == 64 * kKappaPoints, "passes split the wave's points evenly");
-  __shared__ float4 lds4[kLineTile * kAdRec / 4];
+  constexpr FarTables tab = make_far_tables();
+  __shared__ float4 hdr[kLineTile];
+  __shared__ __align__(16) float2 par[kLineTile * C];
+  static_assert(kKappaThreads / 64 * kFarEntries <= 2 * kLineTile * C, "the nodes' values lie where par was");
   __shared__ uint8_t lists[kKappaThreads / 64][kLineTile];
-  __shared__ int sel[kLineTile];
+  __shared__ int sel[2 * kLineTile];  // less than a stage, and a batch
   __shared__ int wkeep[kKappaThreads / 64];
   static_assert(kLineTile == kKappaThreads, "one candidate line per thread");
-  float* lds = reinterpret_cast<float*>(lds4);
   const int tile = blockIdx.x % n_tiles;
   const int64_t run = blockIdx.x / n_tiles;
-  const int j0 = tile * kKappaTilePoints;
+  const int j0 = tile * kKappaThreads;
   const int64_t cell0 = run * C;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
-  const int pt = lane % ROW, cg = lane / ROW;       // point in the row, cell group
-  const int span = ROW * P;                         // points of one pass
-  const int wj0 = j0 + wave * 64 * kKappaPoints;
+  const int pt = lane & 31, cg = lane >> 5;
+  const int wj0 = j0 + wave * 64;
   const int nl = a.L.n;
   // the block's line range from the per-span table (tiles start and end on
   // 64-point spans)
-  const int b0 = j0 / 64, b1 = (j0 + kKappaTilePoints - 1) / 64;
+  const int b0 = j0 / 64, b1 = (j0 + kKappaThreads - 1) / 64;
   const int* sp = reinterpret_cast<const int*>(a.L.span4);
   const int blk_first = b0 < a.L.n_spans ? sp[4 * b0] : nl;
   const int blk_end = b1 < a.L.n_spans ? sp[4 * b1 + 1] : nl;
   const uint32_t* wrow = win + run * (int64_t)nl;
+  // staging: a thread forms the parameters of every 32nd line for one cell
+  const int cc = tid % C;
+  CellFactors cf;
+  {
+    const int64_t scell = min(cell0 + cc, a.n_cells - 1);
+    cf = CellFactors{a.C.beta[scell], a.C.theta[scell], a.C.G[scell], a.C.P[scell], a.C.lam2[scell]};
+  }
+  const float v0 = (float)wj0;
+  const float jl = v0 + (float)pt, ju = jl + 32.f;
+  float acc[2][4], F[kFarNodes];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) acc[0][c] = acc[1][c] = 0.f;
+#pragma unroll
+  for (int n = 0; n < kFarNodes; ++n) F[n] = 0.f;
+  bool nodes = false;
 
-  float jf[NQ][P];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-#pragma unroll
-    for (int p = 0; p < P; ++p) jf[q][p] = (float)(wj0 + q * span + ROW * p + pt);
-  float acc[NQ][P][CPL];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) acc[q][p][c] = 0.f;
+  // staged line l on what its masks keep of the lower and the upper half
+  // (~0: every point; 0: the half is left out)
+  auto direct = [&](auto lower, auto upper, int l, uint32_t lo, uint32_t up) {
+    const float4 h = hdr[l];
+    const float4* g = reinterpret_cast<const float4*>(par + l * C + 4 * cg);
+    const float4 g0 = g[0], g1 = g[1];
+    if constexpr (decltype(lower)::value == kAll) add_half<kAll>(h, g0, g1, jl, acc[0]);
+    if constexpr (decltype(lower)::value == kWithin)
+      if (__builtin_amdgcn_inverse_ballot_w64((uint64_t)lo << 32 | lo)) add_half<kAll>(h, g0, g1, jl, acc[0]);
+    if constexpr (decltype(upper)::value == kAll) add_half<kAll>(h, g0, g1, ju, acc[1]);
+    if constexpr (decltype(upper)::value == kWithin)
+      if (__builtin_amdgcn_inverse_ballot_w64((uint64_t)up << 32 | up)) add_half<kAll>(h, g0, g1, ju, acc[1]);
+  };
 
-  for (int base = blk_first; base < blk_end; base += kLineTile) {
-    // the candidates base .. base + 255 (hard window meets the block) whose
-    // kept window meets the block's points, compacted in order: only they
-    // are staged, so a narrow window costs no amplitude evaluations in the
-    // blocks it misses
-    const int nc = min(kLineTile, blk_end - base);
-    bool keep = false;
-    if (tid < nc) {
-      const uint32_t w = wrow[base + tid];
-      const int lo = (int16_t)(uint16_t)(w & 0xffffu), hi = (int16_t)(uint16_t)(w >> 16);
-      const int m = a.L.m[base + tid];
-      keep = lo <= hi && m + lo <= j0 + kKappaTilePoints - 1 && m + hi >= j0;
-    }
-    const uint64_t bk = __ballot(keep);
-    __syncthreads();  // the previous tile's records, lists and selection read
-    if (lane == 0) wkeep[wave] = __popcll(bk);
-    __syncthreads();
-    int off = 0, nt = 0;
+  for (int base = blk_first, total = 0, done = 0; base < blk_end || done < total;) {
+    // the candidates (hard window meets the block), 256 at a time, whose kept
+    // window meets the block's points, compacted in order until they fill a
+    // stage: only they are staged, so a narrow window costs no amplitude
+    // evaluations in the blocks it misses
+    __syncthreads();  // the previous stage's records and selection read
+    if (done == total) {
+      total = done = 0;
+      for (; base < blk_end && total < kLineTile; base += kLineTile) {
+        const int nc = min(kLineTile, blk_end - base);
+        bool keep = false;
+        if (tid < nc) {
+          const uint32_t w = wrow[base + tid];
+          const int lo = (int16_t)(uint16_t)(w & 0xffffu), hi = (int16_t)(uint16_t)(w >> 16);
+          const int m = a.L.m[base + tid];
+          keep = lo <= hi && m + lo <= j0 + kKappaThreads - 1 && m + hi >= j0;
+        }
+        const uint64_t bk = __ballot(keep);
+        if (lane == 0) wkeep[wave] = __popcll(bk);
+        __syncthreads();
+        int off = total;
 #pragma unroll
-    for (int v = 0; v < kKappaThreads / 64; ++v) {
-      off += v < wave ? wkeep[v] : 0;
-      nt += wkeep[v];
+        for (int v = 0; v < kKappaThreads / 64; ++v) {
+          off += v < wave ? wkeep[v] : 0;
+          total += wkeep[v];
+        }
+        if (keep) sel[off + lanes_below(bk)] = base + tid;
+        __syncthreads();
+      }
+      if (total == 0) continue;
     }
-    if (keep) sel[off + lanes_below(bk)] = base + tid;
-    __syncthreads();
-    if (nt == 0) continue;
-    for (int q = tid; q < nt * C; q += kKappaThreads) {
-      const int li = q / C, cc = q % C;
-      const int i = sel[li];
-      int64_t cell = cell0 + cc;
-      if (cell >= a.n_cells) cell = a.n_cells - 1;
-      float* rec = lds + li * kAdRec;
+    const int* const chosen = sel + done;
+    const int nt = min(kLineTile, total - done);
+    done += nt;
+    for (int li = tid / C; li < nt; li += kKappaThreads / C) {
+      const int i = chosen[li];
+      const LineData d = a.L.data[i];
       if (cc == 0) {
         const uint32_t w = wrow[i];
-        rec[0] = (float)a.L.m[i];
-        rec[1] = a.L.phi[i];
-        rec[2] = (float)(int16_t)(uint16_t)(w & 0xffffu);
-        rec[3] = (float)(int16_t)(uint16_t)(w >> 16);
+        hdr[li] = make_float4(d.m, d.phi, (float)(int16_t)(uint16_t)(w & 0xffffu),
+                              (float)(int16_t)(uint16_t)(w >> 16));
       }
-      line_cell_params(a.L, a.C, i, cell, a.have_E, rec[4 + 2 * cc], rec[5 + 2 * cc]);
+      float amp, g2;
+      line_cell_params(d, cf, a.have_E, amp, g2);
+      par[li * C + cc] = make_float2(amp, g2);
     }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int s0 = wj0 + q * span;
-      __syncthreads();  // records staged; the previous pass's list read
-      // this pass's lines: those whose window meets [s0, s0 + span); indices
-      // of lines covering all of it from the front of the list, the others
-      // from the back
-      int nf = 0, np = 0;
-      for (int l0 = 0; l0 < nt; l0 += 64) {
-        const int l = l0 + lane;
-        bool meet = false, full = false;
-        if (l < nt) {
-          const float4 h = *reinterpret_cast<const float4*>(lds + l * kAdRec);
-          const int m = (int)h.x, w0 = m + (int)h.z, w1 = m + (int)h.w;
-          meet = w0 <= w1 && w0 <= s0 + span - 1 && w1 >= s0;
-          full = meet && w0 <= s0 && w1 >= s0 + span - 1;
+    __syncthreads();
+    int nf = 0;
+    for (int l0 = 0; l0 < nt; l0 += 64) {
+      const int l = l0 + lane;
+      uint32_t lo = 0, up = 0;  // the points of the halves that the line keeps
+      bool far = false;
+      if (l < nt) {
+        const float4 h = hdr[l];
+        const int t = (int)(h.x - v0), w0 = t + (int)h.z, w1 = t + (int)h.w;
+        if (w0 <= 63 && w1 >= 0) {
+          const int first = max(w0, 0), end = min(w1, 63);
+          if (first < 32) lo = (~0u >> (31 - min(end, 31))) & (~0u << first);
+          if (end > 31) up = (~0u >> (63 - end)) & (~0u << max(first - 32, 0));
+          far = lo == ~0u && up == ~0u && (t <= -kFarBelow || t >= kFarAbove);
         }
-        const uint64_t bf = __ballot(full), bp = __ballot(meet && !full);
-        if (full) lists[wave][nf + lanes_below(bf)] = (uint8_t)l;
-        if (meet && !full) lists[wave][kLineTile - 1 - (np + lanes_below(bp))] = (uint8_t)l;
-        nf += __popcll(bf);
-        np += __popcll(bp);
       }
-      __syncthreads();
-      if constexpr (CPL == C) {
-        for (int e = 0; e < nf; ++e) add_line_terms<true, P>(lds + lists[wave][e] * kAdRec, jf[q], acc[q]);
-        for (int e = 0; e < np; ++e)
-          add_line_terms<false, P>(lds + lists[wave][kLineTile - 1 - e] * kAdRec, jf[q], acc[q]);
-      } else {
-        for (int e = 0; e < nf; ++e)
-          add_line_terms_cells<true, P, CPL>(lds + lists[wave][e] * kAdRec, jf[q], cg, acc[q]);
-        for (int e = 0; e < np; ++e)
-          add_line_terms_cells<false, P, CPL>(lds + lists[wave][kLineTile - 1 - e] * kAdRec, jf[q], cg,
-                                              acc[q]);
+      const uint64_t bf = __ballot(far);
+      if (far) lists[wave][nf + lanes_below(bf)] = (uint8_t)l;
+      nf += __popcll(bf);
+      auto lines = [&](auto lower, auto upper, bool of) {
+        for (uint64_t bm = __ballot(of); bm;) {
+          const int bit = __ffsll((unsigned long long)bm) - 1;
+          bm &= ~(1ull << bit);
+          direct(lower, upper, l0 + bit,
+                 decltype(lower)::value == kWithin ? (uint32_t)__builtin_amdgcn_readlane((int)lo, bit) : 0u,
+                 decltype(upper)::value == kWithin ? (uint32_t)__builtin_amdgcn_readlane((int)up, bit) : 0u);
+        }
+      };
+      lines(Take<kWithin>(), Take<kNone>(), lo && !up);
+      lines(Take<kNone>(), Take<kWithin>(), !lo && up);
+      lines(Take<kAll>(), Take<kAll>(), lo == ~0u && up == ~0u && !far);
+      lines(Take<kWithin>(), Take<kWithin>(), lo && up && !(lo == ~0u && up == ~0u));
+    }
+    __builtin_amdgcn_wave_barrier();
+    nodes = nodes || nf >= kFarLines;
+    if (nodes) {
+      for (int e8 = 0; e8 < nf; e8 += 8) {
+        const int e = e8 + (lane >> 3);
+        if (e < nf) {
+          const int l = lists[wave][e];
+          const float2 h = *reinterpret_cast<const float2*>(hdr + l);
+          const float2 ag = par[l * C + (lane & 7)];
+          const float m = ((h.x - v0) - 31.5f) + h.y;  // the centre from the middle
+#pragma unroll
+          for (int n = 0; n < kFarNodes; ++n) {
+            const float d = tab.node[0][n] - m;
+            F[n] = fmaf(ag.x, fast_rcp(fmaf(d, d, ag.y)), F[n]);
+          }
+        }
       }
+    } else {
+      for (int e = 0; e < nf; ++e)
+        direct(Take<kAll>(), Take<kAll>(), __builtin_amdgcn_readfirstlane((int)lists[wave][e]), 0u, 0u);
     }
   }
 
+  __syncthreads();  // the last records read
+  if (nodes) {
+    float lo, hi;
+    far_reduce(F, lane, lo, hi);
+    far_points(lo, hi, lane, reinterpret_cast<float*>(par) + wave * kFarEntries, acc);
+  }
 #pragma unroll
-  for (int c = 0; c < CPL; ++c) {
-    const int64_t cell = cell0 + cg * CPL + c;
+  for (int c = 0; c < 4; ++c) {
+    const int64_t cell = cell0 + 4 * cg + c;
     if (cell >= a.n_cells) break;
     const float add = wing ? (float)wing[cell] : 0.f;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        const int64_t j = wj0 + q * span + ROW * p + pt;
-        if (j < a.ld_out) a.out[cell * a.ld_out + j] = (j < a.n_nu) ? acc[q][p][c] + add : 0.f;
-      }
+    for (int h = 0; h < 2; ++h) {
+      const int64_t j = wj0 + 32 * h + pt;
+      if (j < a.ld_out) a.out[cell * a.ld_out + j] = (j < a.n_nu) ? acc[h][c] + add : 0.f;
+    }
   }
 }
 
-// atan(x1 + d) - atan(x1), d > 0: when both ends have one sign, as
-// atan(d / (1 + x1 (x1 + d))), which keeps the relative accuracy of a narrow
-// span far out in a wing (two arctangents near +-pi/2 would cancel); across
-// the centre the two arctangents have opposite signs and simply add.  The
-// quotient takes the hardware reciprocal (within 1 ulp).
-__device__ inline float atan_span(float x1, float d) {
-  const float x2 = x1 + d;
-  if (x1 >= 0.f || x2 <= 0.f) return atanf(d * __builtin_amdgcn_rcpf(fmaf(x1, x2, 1.f)));
-  return atanf(x2) - atanf(x1);
+// tan of atan(x + d) - atan(x), d > 0: d / (1 + x (x + d)), which keeps the
+// relative accuracy of a narrow span far out in a wing (two arctangents near
+// +-pi/2 would cancel).  Negative where the span turns by more than pi/2, so
+// only from one side of the centre to the other.  Bounded, for the sum below.
+// The quotient takes the hardware reciprocal (within 1 ulp).
+__device__ __forceinline__ float tan_span(float x, float d) {
+  return fminf(d * __builtin_amdgcn_rcpf(fmaf(x, x + d, 1.f)), 3e38f);
 }
 
 // Wing return, one block per run of cells.  The points line i drops in the
@@ -655,9 +658,12 @@ __global__ __launch_bounds__(kAdThreads) void adaptive_wing_kernel(LineSet L, Ce
       float amp, g2;
       line_cell_params(L, C, i, cell, have_E, amp, g2);
       const float ig = __builtin_amdgcn_rsqf(g2);  // 1 / g, within 1 ulp
-      float span = 0.f;
-      if (r0) span += atan_span(e0 * ig, n0 * ig);
-      if (r1) span += atan_span(e1 * ig, n1 * ig);
+      // one arctangent for both ranges: tan(u + v) = (tan u + tan v) / (1 - tan
+      // u tan v); u, v and u + v lie in [0, pi)
+      const float u = r0 ? tan_span(e0 * ig, n0 * ig) : 0.f;
+      const float v = r1 ? tan_span(e1 * ig, n1 * ig) : 0.f;
+      const float t = (u + v) * __builtin_amdgcn_rcpf(fmaf(-u, v, 1.f));
+      const float span = atanf(t) + (t < 0.f ? 3.14159265f : 0.f);
       acc[c] += (double)(amp * ig * span);
     }
   }
@@ -679,7 +685,7 @@ __global__ __launch_bounds__(kAdThreads) void adaptive_wing_kernel(LineSet L, Ce
 static hipError_t launch_adaptive(rt_ctx c, bool wings) {
   const LineSet& L = c->lines;
   const int64_t runs = (c->n_cells + RT_ADAPTIVE_GROUP - 1) / RT_ADAPTIVE_GROUP;
-  const int n_tiles = (int)((c->ld + kKappaTilePoints - 1) / kKappaTilePoints);
+  const int n_tiles = (int)((c->ld + kKappaThreads - 1) / kKappaThreads);
   const int64_t blocks = runs * n_tiles;
   const int64_t pairs = runs * (int64_t)L.n;
   const int64_t wblocks = (pairs + kAdThreads - 1) / kAdThreads;
@@ -750,12 +756,8 @@ static hipError_t launch_adaptive(rt_ctx c, bool wings) {
   t.ld_out = c->ld;
   t.col0 = 0;
   t.col_end = c->ld;
-  if (c->line_tol >= kAdNarrowTol)
-    hipLaunchKernelGGL((kappa_adaptive_kernel<4, 4>), dim3((unsigned)blocks), dim3(kKappaThreads), 0,
-                       c->stream, t, c->d_win, n_tiles, wing);
-  else
-    hipLaunchKernelGGL((kappa_adaptive_kernel<kAdPasses, kKappaCells>), dim3((unsigned)blocks),
-                       dim3(kKappaThreads), 0, c->stream, t, c->d_win, n_tiles, wing);
+  hipLaunchKernelGGL(kappa_adaptive_kernel, dim3((unsigned)blocks), dim3(kKappaThreads), 0, c->stream,
+                     t, c->d_win, n_tiles, wing);
   return hipGetLastError();
 }
 

@@ -495,11 +495,70 @@ __device__ __forceinline__ void far_reduce(const float (&F)[kFarNodes], int lane
   hi = s[2] + t;
 }
 
+// The node sums of a span (far_reduce's lo and hi) at its points, added to acc:
+// points pt and pt + 32 for 4 cells (see kappa_tile_far).
+__device__ __forceinline__ void far_points(float lo, float hi, int lane, float* fx,
+                                           float (&acc)[2][4]) {
+  constexpr int C = kKappaCells;
+  const int pt = lane & 31, cg = lane >> 5;
+  // the nodes relative to one of them: the interpolation's rounding then
+  // scales with their differences
+  const float ref = __int_as_float(
+      __builtin_amdgcn_ds_bpermute(4 * (8 * kFarRef + (lane & 7)), __float_as_int(lo)));
+  __builtin_amdgcn_wave_barrier();
+  fx[lane] = lo - ref;
+  if (lane < 32) fx[64 + lane] = hi - ref;
+  if (lane < C) fx[2 * kFarValues + lane] = ref;
+  __builtin_amdgcn_wave_barrier();
+  float v[2][4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[0][c] = v[1][c] = 0.f;
+#pragma unroll
+  for (int g = 0; g < kFarNodes / 4; ++g) {
+    const float4 wl = *reinterpret_cast<const float4*>(&far_tables.weight[pt][4 * g]);
+    const float4 wu = *reinterpret_cast<const float4*>(&far_tables.weight[pt + 32][4 * g]);
+    const float l4[4] = {wl.x, wl.y, wl.z, wl.w}, u4[4] = {wu.x, wu.y, wu.z, wu.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float4 f = *reinterpret_cast<const float4*>(fx + (4 * g + k) * C + 4 * cg);
+      const float f4[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        v[0][c] = fmaf(l4[k], f4[c], v[0][c]);
+        v[1][c] = fmaf(u4[k], f4[c], v[1][c]);
+      }
+    }
+  }
+  const float4 rf = *reinterpret_cast<const float4*>(fx + 2 * kFarValues + 4 * cg);
+  const float r4[4] = {rf.x, rf.y, rf.z, rf.w};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    acc[0][c] += r4[c] + v[0][c];
+    acc[1][c] += r4[c] + v[1][c];
+  }
+}
+
 // What a half of a span takes of a line: nothing, every point, the points
 // from the window's first, up to its last, or within it.
 constexpr int kNone = 0, kAll = 1, kFrom = 2, kUpTo = 3, kWithin = 4;
 template <int M>
 using Take = std::integral_constant<int, M>;
+
+// Adds what point j takes of a line (header h) for 4 cells (parameters g0, g1).
+template <int M>
+__device__ __forceinline__ void add_half(const float4& h, const float4& g0, const float4& g1, float j,
+                                         float (&s)[4]) {
+  if constexpr (M == kNone) return;
+  const float t = j - h.x;
+  float d = t - h.y;
+  if (M == kFrom) d = t >= h.z ? d : __builtin_inff();
+  if (M == kUpTo) d = t <= h.w ? d : __builtin_inff();
+  if (M == kWithin) d = ((t >= h.z) & (t <= h.w)) ? d : __builtin_inff();
+  s[0] = fmaf(g0.x, fast_rcp(fmaf(d, d, g0.y)), s[0]);
+  s[1] = fmaf(g0.z, fast_rcp(fmaf(d, d, g0.w)), s[1]);
+  s[2] = fmaf(g1.x, fast_rcp(fmaf(d, d, g1.y)), s[2]);
+  s[3] = fmaf(g1.z, fast_rcp(fmaf(d, d, g1.w)), s[3]);
+}
 
 // As kappa_tile for the plain form: points [j0, j0 + 256 SP) x kKappaCells
 // cells; each wavefront owns SP spans of 64 points.  Point by point a lane
@@ -659,21 +718,8 @@ __device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float*
           const float4 h = hdr[l];
           const float4* g = reinterpret_cast<const float4*>(par + l * C + 4 * cg);
           const float4 g0 = g[0], g1 = g[1];
-          auto add = [&](auto take, float j, float (&s)[4]) {
-            constexpr int M = decltype(take)::value;
-            if constexpr (M == kNone) return;
-            const float t = j - h.x;
-            float d = t - h.y;
-            if (M == kFrom) d = t >= h.z ? d : __builtin_inff();
-            if (M == kUpTo) d = t <= h.w ? d : __builtin_inff();
-            if (M == kWithin) d = ((t >= h.z) & (t <= h.w)) ? d : __builtin_inff();
-            s[0] = fmaf(g0.x, fast_rcp(fmaf(d, d, g0.y)), s[0]);
-            s[1] = fmaf(g0.z, fast_rcp(fmaf(d, d, g0.w)), s[1]);
-            s[2] = fmaf(g1.x, fast_rcp(fmaf(d, d, g1.y)), s[2]);
-            s[3] = fmaf(g1.z, fast_rcp(fmaf(d, d, g1.w)), s[3]);
-          };
-          add(lower, jl, acc[p][0]);
-          add(upper, ju, acc[p][1]);
+          add_half<decltype(lower)::value>(h, g0, g1, jl, acc[p][0]);
+          add_half<decltype(upper)::value>(h, g0, g1, ju, acc[p][1]);
         }
       };
       const Cuts& q = cut[p];
@@ -719,41 +765,7 @@ __device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float*
         hi = fmaf(dh[k], f, hi);
       }
     }
-    // the nodes relative to one of them: the interpolation's rounding then
-    // scales with their differences
-    const float ref = __int_as_float(__builtin_amdgcn_ds_bpermute(
-        4 * (8 * kFarRef + (lane & 7)), __float_as_int(lo)));
-    __builtin_amdgcn_wave_barrier();
-    fx[lane] = lo - ref;
-    if (lane < 32) fx[64 + lane] = hi - ref;
-    if (lane < C) fx[2 * kFarValues + lane] = ref;
-    __builtin_amdgcn_wave_barrier();
-    float v[2][4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) v[0][c] = v[1][c] = 0.f;
-#pragma unroll
-    for (int g = 0; g < kFarNodes / 4; ++g) {
-      const float4 wl = *reinterpret_cast<const float4*>(&far_tables.weight[pt][4 * g]);
-      const float4 wu = *reinterpret_cast<const float4*>(&far_tables.weight[pt + 32][4 * g]);
-      const float l4[4] = {wl.x, wl.y, wl.z, wl.w}, u4[4] = {wu.x, wu.y, wu.z, wu.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float4 f = *reinterpret_cast<const float4*>(fx + (4 * g + k) * C + 4 * cg);
-        const float f4[4] = {f.x, f.y, f.z, f.w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          v[0][c] = fmaf(l4[k], f4[c], v[0][c]);
-          v[1][c] = fmaf(u4[k], f4[c], v[1][c]);
-        }
-      }
-    }
-    const float4 rf = *reinterpret_cast<const float4*>(fx + 2 * kFarValues + 4 * cg);
-    const float r4[4] = {rf.x, rf.y, rf.z, rf.w};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      acc[p][0][c] += r4[c] + v[0][c];
-      acc[p][1][c] += r4[c] + v[1][c];
-    }
+    far_points(lo, hi, lane, fx, acc[p]);
   }
 
 #pragma unroll

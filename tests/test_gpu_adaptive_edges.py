@@ -1,0 +1,56 @@
+"""The adaptive line sum where its paths meet: windows narrower and wider than
+a half and a whole 64-point span, spectra that end in a span, lists beyond one
+stage of 256 lines, and enough far lines for a span's nodes; every cell against
+the FP64 oracle, within the repository's 1e-5.
+"""
+import numpy as np
+import pytest
+
+from paper_cs_0703028_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+REL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def rt():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_cs_0703028_amd import rtlbl
+    return rtlbl
+
+
+@pytest.fixture(scope="module")
+def O():
+    from oracle import oracle
+    oracle.build()
+    return oracle
+
+
+@pytest.mark.parametrize("wings", [False, True])
+@pytest.mark.parametrize("n_nu,n_lines,K,eps", [
+    (1, 5, 10, 1e-3), (63, 40, 500, 1e-1), (65, 60, 20, 1e-3), (257, 900, 500, 1e-2),
+    (511, 1500, 500, 1e-5), (700, 500, 300, 1e-8), (1537, 2500, 500, 1e-4), (300, 30, 31, 1e-9),
+])
+def test_windows_stages_and_nodes(rt, O, n_nu, n_lines, K, eps, wings):
+    dnu = 0.01
+    g = I.linear_T_grid(11, 0.1, ny=1, nz=1, T_lo=300.0, T_hi=1700.0, x=0.1, p=1.1)
+    L = I.line_list(n_lines, 1000.0 - 0.3, 1000.3 + n_nu * dnu, seed=n_nu, dnu=dnu, n_nu=n_nu,
+                    cutoff=K * dnu)
+    t = rt.Tracer(0)
+    t.setup_grid(g)
+    t.setup_lines(L)
+    t.set_line_tolerance(eps)
+    print(f"adaptive edges n_nu {n_nu} lines {n_lines} K {K} eps {eps:g} wings {wings}", flush=True)
+    kap, _ = t.compute_kappa(rt.KAPPA_ADAPTIVE_WINGS if wings else rt.KAPPA_ADAPTIVE)
+    kept = t.stats()["line_evals"]
+    got = kap.cpu().numpy().astype(np.float64)
+    t.close()
+    want = O.kappa_adaptive(g, L, eps, wings=wings)
+    assert kept == O.adaptive_evals(g, L, eps)
+    assert (got[:, n_nu:] == 0).all()
+    got = got[:, :n_nu]
+    nz = want != 0
+    assert (got[~nz] == 0).all()
+    assert (np.abs(got[nz] - want[nz]) <= REL * np.abs(want[nz])).all()
