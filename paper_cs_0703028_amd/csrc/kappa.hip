@@ -131,18 +131,22 @@ __attribute__((amdgpu_waves_per_eu(COMP ? 1 : 5))) void kappa_linesum_kernel(Kap
   sum_tile(a.t, j0, cg * kKappaCells, wave_on);
 }
 
-// Planck table: one block per (cell, 256-point segment of the row).
-__global__ void planck_table_kernel(const float2* __restrict__ theta2, int64_t n_cells,
-                                    int n_nu, int64_t ld, int tiles_per_row, float2 nu0,
-                                    float2 dnu, float c1, float* __restrict__ B) {
+// Planck table: one block per (kPlanckCells cells, 256-point segment of their
+// rows), so that a point's wavenumber and its cube serve several cells.
+// Issue-bound; 16^3 cells, 20,000 points: 73 us (one cell per block: 175).
+constexpr int kPlanckCells = 8;
+__global__ __launch_bounds__(256) void planck_table_kernel(
+    const float2* __restrict__ theta2, int64_t n_cells, int n_nu, int64_t ld, int tiles_per_row,
+    float2 nu0, float2 dnu, float c1, float* __restrict__ B) {
   const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  const int64_t cell = b / tiles_per_row;
-  if (cell >= n_cells) return;
-  const int64_t j = (b % tiles_per_row) * 256 + threadIdx.x;
-  if (j >= ld) return;
-  float v = 0.f;
-  if (j < n_nu) v = planck_f32(nu_at(j, pair_of(nu0), pair_of(dnu)), pair_of(theta2[cell]), c1);
-  B[cell * ld + j] = v;
+  const int64_t cell0 = b / tiles_per_row * kPlanckCells;
+  const int64_t j = b % tiles_per_row * 256 + threadIdx.x;
+  if (cell0 >= n_cells || j >= ld) return;
+  const Pair nu = nu_at(j, pair_of(nu0), pair_of(dnu));
+  const int cells = (int)min<int64_t>(kPlanckCells, n_cells - cell0);
+  float* o = B + cell0 * ld + j;
+  for (int k = 0; k < cells; ++k, o += ld)
+    *o = j < n_nu ? planck_f32(nu, pair_of(theta2[cell0 + k]), c1) : 0.f;
 }
 
 // The walls' row B(nu_j, T_wall); theta_wall = c2 / T_wall (zero: cold walls).
@@ -519,7 +523,7 @@ hipError_t launch_planck(rt_ctx c) {
   const float2 nu0 = host_pair(c->nu0), dnu = host_pair(c->dnu);
   const int tiles = (int)((c->ld + 255) / 256);
   if (c->planck) {
-    const int64_t blocks = c->n_cells * tiles;
+    const int64_t blocks = (c->n_cells + kPlanckCells - 1) / kPlanckCells * tiles;
     const unsigned gx = (unsigned)std::min<int64_t>(blocks, 65536);
     const unsigned gy = (unsigned)((blocks + gx - 1) / gx);
     hipLaunchKernelGGL(planck_table_kernel, dim3(gx, gy), dim3(256), 0, c->stream,
