@@ -335,11 +335,11 @@ rt_status rt_create(rt_ctx* out, int hip_device, void* hip_stream) {
   e = hipSetDevice(hip_device);
   if (e == hipSuccess) e = scratch_address(hip_device, n, &c->noalloc_scratch);
   // tally sums and ticket, segment count, kept evaluations
-  const size_t counters = (rt::kAccRow + 3) * sizeof(unsigned long long);
+  const size_t counters = (2 * rt::kAccRow + 3) * sizeof(unsigned long long);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_tally_sums), counters);
   if (e == hipSuccess) e = hipMemset(c->d_tally_sums, 0, counters);
-  c->d_segcount = c->d_tally_sums ? c->d_tally_sums + rt::kAccRow + 1 : nullptr;
-  c->d_adapt_evals = c->d_tally_sums ? c->d_tally_sums + rt::kAccRow + 2 : nullptr;
+  c->d_segcount = c->d_tally_sums ? c->d_tally_sums + 2 * rt::kAccRow + 1 : nullptr;
+  c->d_adapt_evals = c->d_tally_sums ? c->d_tally_sums + 2 * rt::kAccRow + 2 : nullptr;
   if (e != hipSuccess) {
     (void)hipGetLastError();  // not left for the next launch check
     rt_destroy(c);

@@ -154,18 +154,24 @@ __device__ void acc_block_sum(unsigned long long (&d)[kAccRow]) {
 // sum emitted, sum absorbed, escaped}, each from the exact sum of its
 // accumulators (cells, or the balance rows), converted once.  A block adds its
 // cells' digits to the handle's sums (normalised digits are below 2^28 and
-// there are fewer than 2^31 cells); the last block to do so, which leaves them
-// and the ticket cleared, converts them.  out: absorbed[n], emitted[n],
-// balance[4], overflow flag.  13 us at 512 cells, where a launch over the cells
-// and one of a single block over all rows took 4 and 11 with a gap of 5, and 57
-// against 73 a call at 32^3 cells.
+// there are fewer than 2^31 cells), the last block of the grid those of the
+// balance rows; the last block to finish converts the sums and leaves them and
+// the ticket cleared.  out: absorbed[n], emitted[n], balance[4], overflow flag.
+// sums: cells' digits, balance digits, ticket.
+//
+// A chain of loads, exchanges and atomics: 8 us at 512 cells (a launch over
+// the cells and one of a single block over all rows took 4 and 11 with a gap of
+// 5), and 53 against 133 a call with its copies at 32^3 cells.
 __global__ __launch_bounds__(256) void tally_kernel(const unsigned long long* __restrict__ acc,
                                                     int64_t n_cells, int copies, int64_t rows,
                                                     unsigned long long* sums, double* out) {
   __shared__ bool last;
+  const bool bal = blockIdx.x == gridDim.x - 1;
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   unsigned long long d[kAccRow];
-  if (c < n_cells) {
+  if (bal) {
+    acc_sum_copies(acc + rows * kAccRow, threadIdx.x, 256, kBalRows / 256, d);
+  } else if (c < n_cells) {
     acc_sum_copies(acc, c, n_cells, copies, d);
     out[c] = acc_value(d);
     out[n_cells + c] = acc_value(d + kAccDigits);
@@ -174,38 +180,28 @@ __global__ __launch_bounds__(256) void tally_kernel(const unsigned long long* __
     for (int k = 0; k < kAccRow; ++k) d[k] = 0;
   }
   acc_block_sum(d);
+  unsigned long long* const ticket = sums + 2 * kAccRow;
   if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < kAccRow; ++k) atomicAdd(sums + k, d[k]);
+    for (int k = 0; k < kAccRow; ++k) atomicAdd(sums + (bal ? kAccRow : 0) + k, d[k]);
     __threadfence();
-    last = atomicAdd(sums + kAccRow, 1ull) == gridDim.x - 1;
+    last = atomicAdd(ticket, 1ull) == gridDim.x - 1;
   }
   __syncthreads();
-  if (!last) return;
-  // the balance rows
-#pragma unroll
-  for (int k = 0; k < kAccRow; ++k) d[k] = 0;
-  for (int64_t r = rows + threadIdx.x; r < rows + kBalRows; r += 256)
-#pragma unroll
-    for (int k = 0; k < kAccRow; ++k) d[k] += acc[r * kAccRow + k];
-  acc_block_sum(d);
-  if (threadIdx.x == 0) {
-    unsigned long long cells[kAccRow];
-#pragma unroll
-    for (int k = 0; k < kAccRow; ++k) cells[k] = atomicExch(sums + k, 0ull);
-    atomicExch(sums + kAccRow, 0ull);
-    acc_normalize(d);
-    acc_normalize(d + kAccDigits);
-    acc_normalize(cells);
-    acc_normalize(cells + kAccDigits);
-    double* balance = out + 2 * n_cells;
-    balance[0] = acc_value(d);
-    balance[1] = acc_value(cells + kAccDigits);
-    balance[2] = acc_value(cells);
-    balance[3] = acc_value(d + kAccDigits);
-    // the flag behind the balance rows
+  if (!last || threadIdx.x > 4) return;
+  double* const balance = out + 2 * n_cells;
+  if (threadIdx.x == 4) {  // the flag behind the balance rows
     balance[4] = *reinterpret_cast<const unsigned*>(acc + (rows + kBalRows) * kAccRow) ? 1.0 : 0.0;
+    atomicExch(ticket, 0ull);
+    return;
   }
+  // absorbed, emitted, entering, escaped
+  unsigned long long v[kAccDigits];
+#pragma unroll
+  for (int k = 0; k < kAccDigits; ++k) v[k] = atomicExch(sums + threadIdx.x * kAccDigits + k, 0ull);
+  acc_normalize(v);
+  const int at[4] = {2, 1, 0, 3};
+  balance[at[threadIdx.x]] = acc_value(v);
 }
 
 // Clears the accumulators (and the overflow flag behind them), the segment
@@ -424,7 +420,7 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
 }
 
 hipError_t launch_tally(rt_ctx c, double* out) {
-  hipLaunchKernelGGL(tally_kernel, dim3((unsigned)((c->n_cells + 255) / 256)), dim3(256), 0,
+  hipLaunchKernelGGL(tally_kernel, dim3((unsigned)((c->n_cells + 255) / 256 + 1)), dim3(256), 0,
                      c->stream, c->d_acc, c->n_cells, acc_copies(c->n_cells), c->acc_rows,
                      c->d_tally_sums, out);
   return hipGetLastError();
