@@ -92,12 +92,35 @@ int64_t align_up(int64_t v) { return (v + 255) / 256 * 256; }
 // Builds the plan (sizes, stages) without touching device memory; returns
 // the workspace bytes through *bytes.  limit_points > 0 restricts the
 // spectral range to the first limit_points points (autotuner trials).
-rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch_tuning& t,
+rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, rt_batch_tuning t,
                      int64_t limit_points, BatchPlan& pl, int64_t* bytes) {
-  pl.tuning = t;
   pl.chunked = t.mode == RT_BATCH_CHUNKED;
   pl.n_cases = n_cases;
   const int64_t n_nu = limit_points > 0 ? std::min<int64_t>(limit_points, c->n_nu) : c->n_nu;
+  // A single slab serves as two of half the points, so that the line sum of a
+  // chunk, which the arithmetic bounds, runs beside the march of the one before,
+  // which the tables' rows bound: where half a chunk's tiles still fill the chip
+  // and, by the rates of both (1e13 evaluations and 1e12 updates a second), the
+  // shorter of the two is a sixteenth of the other (one slab of 3072 points against two of 1536: 6 cases of 16^3 to 32^3 cells
+  // 88.9, 83.6 ms; 3 of 19^3 to 37^3 29.9, 26.5; 4 dense ones of 8^3 to 16^3
+  // 18.4, 18.0; 6 of 6^3 to 10^3 2.71, 2.78; 3 of 4^3 to 6^3 with compensated
+  // sums 2.7, 3.3; 7 of 8^3 to 16^3 with dense compensated sums and 424 rays
+  // 278, 281).
+  int64_t all_cells = 0;
+  double updates = 0;
+  for (int k = 0; k < n_cases; ++k) {
+    const rt_case& q = cases[k];
+    all_cells += (int64_t)q.nx * q.ny * q.nz;
+    updates += (double)q.n_rays * c->n_nu * 3.0 / (1.0 / q.nx + 1.0 / q.ny + 1.0 / q.nz);
+  }
+  const double sum_s = c->line_evals_per_cell * (double)all_cells * 1e-13, march_s = updates * 1e-12;
+  const int64_t half_tiles = all_cells / dev::kKappaCells * (t.chunk_points / 2 / dev::kKappaTilePoints);
+  if (pl.chunked && t.slots == 1 && t.chunk_points % (2 * kChunk) == 0 && n_nu > t.chunk_points &&
+      half_tiles >= 8 * 256 && std::min(sum_s, march_s) >= std::max(sum_s, march_s) / 16) {
+    t.chunk_points /= 2;
+    t.slots = 2;
+  }
+  pl.tuning = t;
   pl.n_chunks = (int)((n_nu + t.chunk_points - 1) / t.chunk_points);
   pl.bwall_ld = (int64_t)pl.n_chunks * t.chunk_points;
   pl.cases.assign(n_cases, BatchCase());

@@ -276,11 +276,11 @@ constexpr int kAccBits = 28;
 constexpr int kAccDigits = 7;
 constexpr int kAccLsb = -112;
 constexpr int kAccRow = 2 * kAccDigits;
-// terms one launch may add to one accumulator word (rays x spectral chunks)
 // Grids of up to this many cells have rt_tally's kernel write its results to
 // host memory (1 MB) instead of copying them out of device memory: a call
 // takes 26 us instead of 65 at 16^3 cells, 53 instead of 95 at 32^3.
 constexpr int64_t kHostTallyCells = int64_t(1) << 16;
+// terms one launch may add to one accumulator word (rays x spectral chunks)
 constexpr int64_t kAccMaxTerms = int64_t(1) << 35;
 // Balance rows (entering, escaped) per grid: rays spread over them so that
 // their additions do not all meet in one accumulator.
