@@ -568,10 +568,13 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
       // the chunk's parts that hold a point of the spectrum
       const dim3 mg((unsigned)march_blocks,
                     (unsigned)plain_chunks(std::min<int64_t>(cp, c->n_nu - t.col0)));
-      // six wavefronts per SIMD: fewer rows compete for L2 (6 cases of 16^3 to
-      // 32^3 cells, 2^15 and 2^16 rays, per launch: 127.1 ms with eight, 124.4
-      // with seven, 122.5 with six, 121.0 with five; dense rays lose below six)
-      const unsigned pad = 10000;
+      // six wavefronts per SIMD where the rows a part of the chunk reads exceed
+      // the 32 MB of the L2s, for which fewer then compete (3 cases of 16^3 to
+      // 32^3 cells, 20,000 rays, per launch: 13.4 ms, with eight 14.2; 4 cases
+      // of 11^3 to 21^3, 60,000 rays: 23.7, 23.0; fewer than six lose where the
+      // rays are dense)
+      const bool beyond = pl.max_cells * (int64_t)(kMarchPoints * sizeof(float)) > (int64_t(32) << 20);
+      const unsigned pad = beyond ? 10000 : 0;
       if (pl.any_cubic) hipLaunchKernelGGL(chunk_march_kernel<true>, mg, dim3(256), pad, s, m);
       if (pl.any_general) hipLaunchKernelGGL(chunk_march_kernel<false>, mg, dim3(256), pad, s, m);
       if (two) e = hipEventRecord(ev[1 + pl.n_chunks + ch], s);
