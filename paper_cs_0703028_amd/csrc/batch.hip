@@ -104,7 +104,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   constexpr int kLdsFloats = kLineTile * (4 + 2 * kKappaCells);
   static_assert(kLdsFloats >= 4 * PlainStage::kEntries, "march staging fits");
   __shared__ float4 lds4[kLdsFloats / 4];
-  __shared__ float4 fx4[4 * kFarEntries / 4];
+  __shared__ float4 fx4[kFarEntries];  // kFarEntries floats or kCompEntries doubles a wavefront
+  static_assert(2 * kCompEntries <= kFarEntries, "shared by the two forms");
   __shared__ long long s_item;
   __shared__ int s_ok;
   float* lds = reinterpret_cast<float*>(lds4);
@@ -177,8 +178,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
       const int j0 = (int)(t.col0 + (int64_t)tile * kKappaTilePoints);
       const int64_t g_end = min((gb + 1) * a.kappa_groups, n_groups);
       for (int64_t g = gb * a.kappa_groups; g < g_end; ++g) {
-        if (a.comp) kappa_tile<false>(t, j0, g * kKappaCells, lds);
-        else
+        if (a.comp) {
+          for (int h = 0; h < kKappaPoints; ++h)
+            kappa_tile_comp(t, j0 + h * kKappaThreads, g * kKappaCells, lds,
+                            reinterpret_cast<double*>(fx4) + wave * kCompEntries);
+        } else
           kappa_tile_far<kKappaPoints>(t, j0, g * kKappaCells, lds,
                                        reinterpret_cast<float*>(fx4) + wave * kFarEntries);
       }

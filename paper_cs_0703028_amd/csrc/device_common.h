@@ -279,10 +279,9 @@ struct TileGate {
   int n_chunks = 0;
 };
 
-// Compensated: blocks of 16 lines are summed plainly and folded in with
-// TwoSum.  F32: line records from line_cell_params_f32 (the precision form).
-template <bool F32>
-__device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds) {
+// Compensated, the precision form: line records from line_cell_params_f32;
+// blocks of 16 lines are summed plainly and folded in with TwoSum.
+__device__ inline void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds) {
   constexpr int P = kKappaPoints;
   constexpr int C = kKappaCells;
   constexpr int REC = kLineRec;
@@ -357,10 +356,7 @@ __device__ void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds
         rec[2] = (float)(a.L.wlo[i] - a.L.m[i]);  // -K + [phi > 0]
         rec[3] = (float)a.K;
       }
-      if (F32)
-        line_cell_params_f32(a.L, a.C, i, cell, a.have_E, rec[4 + 2 * cc], rec[5 + 2 * cc]);
-      else
-        line_cell_params(a.L, a.C, i, cell, a.have_E, rec[4 + 2 * cc], rec[5 + 2 * cc]);
+      line_cell_params_f32(a.L, a.C, i, cell, a.have_E, rec[4 + 2 * cc], rec[5 + 2 * cc]);
     }
     __syncthreads();
 
@@ -784,6 +780,246 @@ __device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float*
           *o = (j < a.n_nu) ? (a.accumulate ? *o + v : v) : 0.f;
         }
       }
+  }
+}
+
+// -------------------------------------------- the compensated sum with far nodes
+// Lane (s, c) holds chain s of cell c for every node; adds the eight chains in
+// FP64, as far_reduce.
+__device__ __forceinline__ void row_swap64(double& a, double& b) {
+  float2 x = *reinterpret_cast<float2*>(&a), y = *reinterpret_cast<float2*>(&b);
+  row_swap(x.x, y.x);
+  row_swap(x.y, y.y);
+  a = *reinterpret_cast<double*>(&x);
+  b = *reinterpret_cast<double*>(&y);
+}
+__device__ __forceinline__ void half_swap64(double& a, double& b) {
+  float2 x = *reinterpret_cast<float2*>(&a), y = *reinterpret_cast<float2*>(&b);
+  half_swap(x.x, y.x);
+  half_swap(x.y, y.y);
+  a = *reinterpret_cast<double*>(&x);
+  b = *reinterpret_cast<double*>(&y);
+}
+__device__ __forceinline__ void far_reduce64(const float (&F)[kFarNodes], const float (&E)[kFarNodes],
+                                             int lane, double& lo, double& hi) {
+  double g[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    double a = (double)F[2 * i] + (double)E[2 * i];
+    double b = (double)F[2 * i + 1] + (double)E[2 * i + 1];
+    a += dpp_f64<0x128>(a);  // row_ror:8
+    b += dpp_f64<0x128>(b);
+    g[i] = (lane & 8) ? b : a;
+  }
+  double s[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    row_swap64(g[2 * i], g[2 * i + 1]);
+    s[i] = g[2 * i] + g[2 * i + 1];
+  }
+  half_swap64(s[0], s[1]);
+  lo = s[0] + s[1];
+  double t = s[2];
+  half_swap64(s[2], t);
+  hi = s[2] + t;
+}
+
+struct FarWeights64 {
+  alignas(16) double weight[64][kFarNodes];  // FarTables::weight for these nodes
+};
+constexpr FarWeights64 make_far_weights64() {
+  constexpr FarTables f = make_far_tables();
+  FarWeights64 t{};
+  for (int i = 0; i < kFarNodes; ++i)
+    for (int j = 0; j < 64; ++j) {
+      double w = 1.0;
+      for (int k = 0; k < kFarNodes; ++k)
+        if (k != i)
+          w *= ((double)j - 31.5 - (double)f.node[0][k]) / ((double)f.node[0][i] - (double)f.node[0][k]);
+      t.weight[j][i] = w;
+    }
+  return t;
+}
+static __device__ const FarWeights64 far_weights64 = make_far_weights64();
+constexpr int kCompEntries = kFarValues;  // LDS doubles per wavefront
+
+// The compensated sum of the batched launches, with the plain form's line
+// parameters: points [j0, j0 + 256) x kKappaCells cells, a span of 64 points per
+// wavefront.  Runs of up to 8 lines point by point (32 at the nodes, in eight
+// chains) are summed plainly and folded in with TwoSum; the chains are added and
+// the nodes interpolated in FP64, so the result is rounded once.  The span's
+// nodes alone are used (a wavefront with one span would not share a pair's).
+// lds: kLineTile * kLineRec floats; fx: this wavefront's kCompEntries doubles.
+// (The precision form keeps kappa_tile: its powers are FP64 sums, and another
+// order of additions, which changes a table's last bit at one point in five,
+// would move them by up to 2e-9 at 1,500 points.)
+//
+// Issue-bound.  16^3 cells, 20,000 points, 5,000 lines: 2.75 -> 1.42 ms.  Error
+// against 64 bits (rms over the points, 3 to 200 lines per cm^-1, steps of 0.005
+// to 0.05): 7.2e-8 to 9.5e-8, every line at every point 7.8e-8 to 1.1e-7.
+__device__ inline void kappa_tile_comp(const KappaTile& a, int j0, int64_t cell0, float* lds, double* fx) {
+  constexpr int C = kKappaCells;
+  constexpr FarTables tab = make_far_tables();
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int pt = lane & 31, cg = lane >> 5;
+  const int nl = a.L.n;
+  auto bound = [&](const int4* table, int b, int k) {  // a scalar load: b is uniform
+    return b < a.L.n_spans ? reinterpret_cast<const __attribute__((address_space(4))) int*>(
+                                 reinterpret_cast<uintptr_t>(table))[4 * b + k]
+                           : nl;
+  };
+  const int blk_first = bound(a.L.span4, j0 / 64, 0);
+  const int blk_end = bound(a.L.span4, (j0 + kKappaThreads - 1) / 64, 1);
+  // the span's cuts, as kappa_tile_far's
+  const int wj0 = j0 + wave * 64, b = wj0 / 64;
+  const int x = bound(a.L.span4, b, 0), y = bound(a.L.span4, b, 1);
+  const int c0 = min(max(bound(a.L.span4, b, 2), x), y);
+  const int c1 = max(c0, min(bound(a.L.span4, b, 3), y));
+  const int m0 = min(max(bound(a.L.span_far, b, 0), c0), c1);
+  const int m1 = min(max(bound(a.L.span_far, b, 1), m0), c1);
+  const int s0 = min(max(bound(a.L.span4, b, 3), x), c0);
+  const int h0 = min(max(bound(a.L.span_far, b, 2), x), s0);
+  const int h1 = min(max(bound(a.L.span_far, b, 3), c1), y);
+
+  float acc[2][4], cmp[2][4], F[kFarNodes], E[kFarNodes];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[h][c] = cmp[h][c] = 0.f;
+#pragma unroll
+  for (int n = 0; n < kFarNodes; ++n) F[n] = E[n] = 0.f;
+
+  float4* hdr = reinterpret_cast<float4*>(lds);
+  float2* par = reinterpret_cast<float2*>(lds + 4 * kLineTile);
+  const int cc = tid % C;
+  CellFactors cf;
+  {
+    int64_t scell = cell0 + cc;
+    if (scell >= a.n_cells) scell = a.n_cells - 1;
+    if (a.cell_list) scell = a.cell_list[scell];
+    cf = CellFactors{a.C.beta[scell], a.C.theta[scell], a.C.G[scell], a.C.P[scell],
+                     a.C.lam2[scell]};
+  }
+  const float v0 = (float)wj0;
+  const float jl = v0 + (float)pt, ju = jl + 32.f;
+
+  for (int base = blk_first & ~7; base < blk_end; base += kLineTile) {
+    const int nt = min(kLineTile, blk_end - base);
+    __syncthreads();
+#pragma unroll 2
+    for (int li = tid / C; li < nt; li += kKappaThreads / C) {
+      const LineData d = a.L.data[base + li];
+      if (cc == 0) hdr[li] = make_float4(d.m, d.phi, d.lo, (float)a.K);
+      float amp, g2;
+      line_cell_params(d, cf, a.have_E, amp, g2);
+      par[li * C + cc] = make_float2(amp, g2);
+    }
+    __syncthreads();
+    const int first = max(base, blk_first), end = base + nt;
+    auto direct = [&](auto lower, auto upper, int l0, int l1) {
+      l0 = __builtin_amdgcn_readfirstlane(max(l0, first) - base);
+      l1 = __builtin_amdgcn_readfirstlane(min(l1, end) - base);
+      while (l0 < l1) {
+        const int le = min(l0 + 8, l1);
+        float part[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) part[h][c] = 0.f;
+        for (int l = l0; l < le; ++l) {
+          const float4 h = hdr[l];
+          const float4* g = reinterpret_cast<const float4*>(par + l * C + 4 * cg);
+          const float4 g0 = g[0], g1 = g[1];
+          add_half<decltype(lower)::value>(h, g0, g1, jl, part[0]);
+          add_half<decltype(upper)::value>(h, g0, g1, ju, part[1]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (decltype(lower)::value != kNone) two_sum_acc(acc[0][c], cmp[0][c], part[0][c]);
+          if (decltype(upper)::value != kNone) two_sum_acc(acc[1][c], cmp[1][c], part[1][c]);
+        }
+        l0 = le;
+      }
+    };
+    direct(Take<kUpTo>(), Take<kNone>(), x, h0);
+    direct(Take<kAll>(), Take<kUpTo>(), h0, s0);
+    direct(Take<kWithin>(), Take<kWithin>(), s0, c0);
+    direct(Take<kAll>(), Take<kAll>(), m0, m1);
+    direct(Take<kFrom>(), Take<kAll>(), c1, h1);
+    direct(Take<kNone>(), Take<kFrom>(), h1, y);
+    if (c0 < m0 || m1 < c1) {
+      float part[kFarNodes];
+#pragma unroll
+      for (int n = 0; n < kFarNodes; ++n) part[n] = 0.f;
+      auto far = [&](int l0, int l1) {
+        l0 = __builtin_amdgcn_readfirstlane(max(l0, first) - base);
+        l1 = __builtin_amdgcn_readfirstlane(min(l1, end) - base);
+        for (int l8 = l0 & ~7; l8 < l1; l8 += 8) {  // base: a multiple of 8
+          const int l = l8 + (lane >> 3);
+          if (l >= l0 && l < l1) {
+            const float2 h = *reinterpret_cast<const float2*>(hdr + l);
+            const float2 ag = par[l8 * C + lane];
+            const float e = ((h.x - v0) - 31.5f) + h.y;  // the centre from the middle
+#pragma unroll
+            for (int n = 0; n < kFarNodes; ++n) {
+              const float d = tab.node[0][n] - e;
+              part[n] = fmaf(ag.x, fast_rcp(fmaf(d, d, ag.y)), part[n]);
+            }
+          }
+        }
+      };
+      far(c0, m0);
+      far(m1, c1);
+#pragma unroll
+      for (int n = 0; n < kFarNodes; ++n) two_sum_acc(F[n], E[n], part[n]);
+    }
+  }
+
+  double v[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[h][c] = (double)acc[h][c] + (double)cmp[h][c];
+  if (c0 < m0 || m1 < c1) {
+    double lo, hi;
+    far_reduce64(F, E, lane, lo, hi);
+    __builtin_amdgcn_wave_barrier();
+    fx[lane] = lo;
+    if (lane < 32) fx[64 + lane] = hi;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int n = 0; n < kFarNodes; n += 2) {
+      const double2 wl = *reinterpret_cast<const double2*>(&far_weights64.weight[pt][n]);
+      const double2 wu = *reinterpret_cast<const double2*>(&far_weights64.weight[pt + 32][n]);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const double* f = fx + (n + k) * C + 4 * cg;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          v[0][c] = fma(k ? wl.y : wl.x, f[c], v[0][c]);
+          v[1][c] = fma(k ? wu.y : wu.x, f[c], v[1][c]);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();  // a next call writes fx
+  }
+
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    int64_t cell = cell0 + 4 * cg + c;
+    if (cell >= a.n_cells) break;
+    if (a.cell_list && !a.compact_rows) cell = a.cell_list[cell];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t j = wj0 + 32 * h + pt;
+      if (j >= a.col0 && j < a.col_end) {
+        float* o = a.out + cell * a.ld_out + (j - a.col0);
+        const float r = (float)v[h][c];
+        *o = (j < a.n_nu) ? (a.accumulate ? *o + r : r) : 0.f;
+      }
+    }
   }
 }
 

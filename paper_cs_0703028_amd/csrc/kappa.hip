@@ -3,7 +3,8 @@
 //   cell_params   : per-cell gas state -> FP32/FP64 factors (FP64 arithmetic)
 //   kappa_linesum : Eq. (2) with the Eq. (1) strength ratio (line tiles staged
 //                   in LDS, kappa written coalesced along nu): plain
-//                   (dev::kappa_tile_far) and compensated (dev::kappa_tile)
+//                   (dev::kappa_tile_far) and compensated (dev::kappa_tile,
+//                   dev::kappa_tile_comp)
 //   planck_table  : Eq. (4), wavenumber form, per (cell, nu) and for the walls,
 //                   evaluated in FP32 (pair arguments, exp_pair/expm1_pair)
 #include <cfloat>
@@ -79,19 +80,25 @@ struct KappaArgs {
   int64_t part_stride = 0;   // floats between the shares' outputs
 };
 
-template <bool COMP, bool F32 = false, int P = kKappaPoints>
+// FORM: kPlainSum (P spans per wavefront), kCompSum (the batched launches'
+// compensated sum, one span), kPrecSum (the precision form's).
+constexpr int kPlainSum = 0, kCompSum = 1, kPrecSum = 2;
+template <int FORM, int P>
 __global__ __launch_bounds__(kKappaThreads)
-__attribute__((amdgpu_waves_per_eu(COMP ? 1 : 5))) void kappa_linesum_kernel(KappaArgs a) {
+__attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 1 : 5))) void kappa_linesum_kernel(KappaArgs a) {
+  static_assert(FORM != kCompSum || P == 1, "a span per wavefront");
+  static_assert(FORM != kPrecSum || P == kKappaPoints, "kappa_tile's points");
   __shared__ float4 lds4[kLineTile * kLineRec / 4];
-  __shared__ float4 fx4[COMP ? 1 : kKappaThreads / 64 * kFarEntries / 4];
+  __shared__ float4 fx4[FORM == kPrecSum ? 1 : kFarEntries];  // floats, or doubles, of 4 wavefronts
   auto sum_tile = [&](const KappaTile& t, int j0, int64_t cell0, bool on) {
     float* lds = reinterpret_cast<float*>(lds4);
-    if constexpr (COMP) {
-      kappa_tile<F32>(t, j0, cell0, lds);
-    } else {
-      const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (FORM == kPrecSum)
+      kappa_tile(t, j0, cell0, lds);
+    else if constexpr (FORM == kCompSum)
+      kappa_tile_comp(t, j0, cell0, lds, reinterpret_cast<double*>(fx4) + wave * kCompEntries);
+    else
       kappa_tile_far<P>(t, j0, cell0, lds, reinterpret_cast<float*>(fx4) + wave * kFarEntries, on);
-    }
   };
   const int part = (int)(blockIdx.x % (unsigned)a.parts);
   const int64_t tb = blockIdx.x / (unsigned)a.parts;
@@ -415,10 +422,10 @@ static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
   if (blocks < 6 * 256 || a.t.K <= 256 || (a.t.K <= 512 && lines_per_point >= 0.9)) {
     a.n_tiles *= 2;
     a.tile_begin *= 2;
-    hipLaunchKernelGGL((kappa_linesum_kernel<false, false, 1>), dim3((unsigned)(2 * blocks)),
+    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, 1>), dim3((unsigned)(2 * blocks)),
                        dim3(kKappaThreads), 0, s, a);
   } else {
-    hipLaunchKernelGGL((kappa_linesum_kernel<false>), dim3((unsigned)blocks), dim3(kKappaThreads),
+    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, kKappaPoints>), dim3((unsigned)blocks), dim3(kKappaThreads),
                        0, s, a);
   }
   return hipGetLastError();
@@ -444,7 +451,7 @@ hipError_t launch_kappa(rt_ctx c, bool compensated) {
   auto launch = [&]() {
     if (!compensated) return launch_plain(a, groups, c->stream);
     // the precision form: FP32 line parameters
-    hipLaunchKernelGGL((kappa_linesum_kernel<true, true>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((kappa_linesum_kernel<kPrecSum, kKappaPoints>), dim3((unsigned)blocks),
                        dim3(kKappaThreads), 0, c->stream, a);
     return hipGetLastError();
   };
@@ -474,11 +481,14 @@ hipError_t launch_kappa_tiles(rt_ctx c, const KappaTile& t, int64_t n_cell_group
   a.parts = parts < 1 ? 1 : parts;
   a.part_stride = part_stride;
   if (!comp) return launch_plain(a, n_cell_groups, s);
-  const int64_t blocks = n_cell_groups * n_tiles;
+  // the compensated sum has its own tiles of 256 points
+  a.n_tiles *= kKappaPoints;
+  a.tile_begin *= kKappaPoints;
+  const int64_t blocks = n_cell_groups * a.n_tiles;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((kappa_linesum_kernel<true>), dim3((unsigned)blocks), dim3(kKappaThreads), 0,
-                     s, a);
+  hipLaunchKernelGGL((kappa_linesum_kernel<kCompSum, 1>), dim3((unsigned)blocks), dim3(kKappaThreads),
+                     0, s, a);
   return hipGetLastError();
 }
 
@@ -497,7 +507,7 @@ hipError_t launch_kappa_tiles_fine(rt_ctx c, const KappaTile& t, int64_t n_cell_
   const int64_t blocks = n_cell_groups * n_tiles;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((kappa_linesum_kernel<false, false, 1>), dim3((unsigned)blocks),
+  hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, 1>), dim3((unsigned)blocks),
                      dim3(kKappaThreads), 0, s, a);
   return hipGetLastError();
 }
