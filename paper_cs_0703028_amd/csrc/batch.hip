@@ -93,11 +93,10 @@ __device__ __forceinline__ bool wait_count(const unsigned* p, unsigned target, u
 }
 
 // Five wavefronts per SIMD (at most 102 VGPRs): the march items wait on memory
-// and need the wavefronts to hide it.  Left alone the combined code paths take
-// 142 VGPRs and three wavefronts; at five, 33 VGPRs go to scratch, a few
-// accesses per march segment, which costs less than the two wavefronts gain
-// (measured: 4.57 s at three, 4.33 s at four, 4.26 s at five for the 64-case
-// launch; six spills 62 and is not used).
+// and need the wavefronts to hide it.  At five, 59 VGPRs of the combined code
+// paths go to scratch, which costs less than the wavefronts gain (64 cases of
+// 16^3 to 48^3 cells, five blocks per CU: 4.51 s at three, 4.12 s at four, 3.99 s
+// at five).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void batch_kernel(BatchArgs a) {
   // line-sum tiles stage line records here; march items stage their
   // per-segment partial sums (4 wavefronts) in the same memory
