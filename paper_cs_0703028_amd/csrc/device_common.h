@@ -556,7 +556,7 @@ __device__ __forceinline__ void add_half(const float4& h, const float4& g0, cons
   s[3] = fmaf(g1.z, fast_rcp(fmaf(d, d, g1.w)), s[3]);
 }
 
-// As kappa_tile for the plain form: points [j0, j0 + 256 SP) x kKappaCells
+// The plain form: points [j0, j0 + 256 SP) x kKappaCells
 // cells; each wavefront owns SP spans of 64 points.  Point by point a lane
 // takes points pt and pt + 32 of a span for 4 of the cells (2 LDS reads of
 // parameters per line, where one point of 8 cells would take 4 and leave the

@@ -6,8 +6,8 @@
 //                cosine-weighted inward direction) and exact integer
 //                traversal -> per-ray list of (cell, length) segments
 //   march      : Eq. (3) applied cell after cell for every nu point; each
-//                wavefront owns one ray and a kChunk-point spectral chunk
-//                (dev::march_prec); the absorbed and emitted power of the
+//                wavefront owns one ray and one spectral chunk
+//                (dev::march_plain, dev::march_prec); the absorbed and emitted power of the
 //                chunk per segment is summed across the wavefront in a fixed
 //                order and added to the cell's fixed-point accumulator
 //   tally      : the accumulators as FP64 powers per cell, and the energy
