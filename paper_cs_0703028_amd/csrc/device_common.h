@@ -186,57 +186,29 @@ __device__ __forceinline__ void line_cell_params(const LineSet& L, const CellSet
 // The same record in FP32 only (the precision form): the Eq. (1) factors from
 // the host-formed FP32 inputs with exp_pair, the half width's temperature
 // power and the partition ratio (in Gq) with the hardware base-2 exponential.
-__device__ __forceinline__ void line_cell_params_f32(const LineSet& L, const CellSet& C, int i,
-                                                     int64_t cell, int have_E, float& amp,
-                                                     float& g2) {
-  const float gp = L.gamma[i] * C.Pf[cell] * fast_exp2(L.nexp[i] * C.lamf[cell]);
-  float a = C.Gq[cell] * L.S[i] * gp;
+struct CellFactors32 {
+  float2 beta2, theta2;
+  float Gq, Pf, lamf;
+};
+__device__ __forceinline__ void line_cell_params_f32(const LineSet& L, const CellFactors32& c, int i,
+                                                     int have_E, float& amp, float& g2) {
+  const float gp = L.gamma[i] * c.Pf * fast_exp2(L.nexp[i] * c.lamf);
+  float a = c.Gq * L.S[i] * gp;
   if (have_E) {
-    a *= exp_pair(pair_mul(pair_of(L.E2p[i]), pair_of(C.beta2[cell])));
-    a *= one_minus_exp_neg_pair(pair_mul(pair_of(L.nup[i]), pair_of(C.theta2[cell])));
+    a *= exp_pair(pair_mul(pair_of(L.E2p[i]), pair_of(c.beta2)));
+    a *= one_minus_exp_neg_pair(pair_mul(pair_of(L.nup[i]), pair_of(c.theta2)));
   }
   amp = a;
   g2 = gp * gp;
 }
 
-// Adds one staged line to P points x kKappaCells cells of a lane: jf are the
-// lane's points as floats.  FULL: every point is inside [m + lo, m + hi];
-// otherwise a point outside gets an infinite offset, whose term is 0.
-template <bool FULL, int P>
-__device__ __forceinline__ void add_line_terms(const float* rec, const float (&jf)[P],
-                                               float (&part)[P][kKappaCells]) {
-  const float4 h = *reinterpret_cast<const float4*>(rec);
-  float dv[P];
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const float t = jf[p] - h.x;
-    const float d = t - h.y;
-    if (FULL) {
-      dv[p] = d;
-    } else {
-      const bool in = (t >= h.z) & (t <= h.w);
-      dv[p] = in ? d : __builtin_inff();
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < kKappaCells; c += 2) {
-    const float4 ag = *reinterpret_cast<const float4*>(rec + 4 + 2 * c);
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      part[p][c] = fmaf(ag.x, fast_rcp(fmaf(dv[p], dv[p], ag.y)), part[p][c]);
-      part[p][c + 1] = fmaf(ag.z, fast_rcp(fmaf(dv[p], dv[p], ag.w)), part[p][c + 1]);
-    }
-  }
-}
-
 // ------------------------------------------------------------ line sum tile
-// The compensated sum.  Eq. (2) with the Eq. (1) strength ratio for one block: nu points
-// [j0, j0 + 512) x kKappaCells cells starting at cell0.  Wave w owns the
-// points j0 + 128 w + 64 p + lane (p < 2).  Lines whose window meets the
-// block's points are staged kLineTile at a time as line records (m, phi,
-// the window's offsets -K + [phi > 0] and K, and per cell the Lorentz
-// amplitude A = u S s gamma / (pi dnu^2) and the squared half width
-// g2 = (gamma/dnu)^2), so that a line adds
+// Eq. (2) with the Eq. (1) strength ratio for one block: nu points from j0 on
+// x kKappaCells cells starting at cell0.  Lines whose window meets the block's
+// points are staged kLineTile at a time as line records (m, phi, the window's
+// offsets -K + [phi > 0] and K, and per cell the Lorentz amplitude A = u S s
+// gamma / (pi dnu^2) and the squared half width g2 = (gamma/dnu)^2), so that a
+// line adds
 //   A / ((j - r_i)^2 + g2)
 // to kappa at point j.  Grid units: line i sits at r_i = (nu_i - nu0)/dnu =
 // m_i + phi_i with integer m_i; the offset j - r_i is the exact float
@@ -244,8 +216,8 @@ __device__ __forceinline__ void add_line_terms(const float* rec, const float (&j
 // occurs in FP32.  Window membership is the integer range
 // [m_i - K + [phi_i > 0], m_i + K], the exact form of |j - r_i| <= K.
 // Output: out[(cell - 0) * ld_out + (j - col0)] for col0 <= j < col_end;
-// points at or beyond n_nu are written as 0.  Must be called by all 256
-// threads of the block; `lds` holds kLineTile * kLineRec floats.
+// points at or beyond n_nu are written as 0.  Must be called by all threads of
+// the block; `lds` holds kLineTile * kLineRec floats.
 struct KappaTile {
   LineSet L;
   CellSet C;          // per-cell factors of this grid (row 0 = its first cell)
@@ -278,112 +250,6 @@ struct TileGate {
   int chunk_w = 0;
   int n_chunks = 0;
 };
-
-// Compensated, the precision form: line records from line_cell_params_f32;
-// blocks of 16 lines are summed plainly and folded in with TwoSum.
-__device__ inline void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds) {
-  constexpr int P = kKappaPoints;
-  constexpr int C = kKappaCells;
-  constexpr int REC = kLineRec;
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
-  const int span = 64 * P;
-  const int wj0 = j0 + wave * span;
-
-  const int nl = a.L.n;
-  // line ranges of the block's points and of the wavefront's (both start
-  // and end on 64-point spans)
-  auto bound = [&](int b, int k) {  // field k of span b (all n past the table)
-    return b < a.L.n_spans ? reinterpret_cast<const int*>(a.L.span4)[4 * b + k] : nl;
-  };
-  const int blk_first = bound(j0 / 64, 0);
-  const int blk_end = bound((j0 + kKappaThreads * P - 1) / 64, 1);
-  const int wb0 = wj0 / 64, wb1 = (wj0 + span - 1) / 64;
-  const int w_first = bound(wb0, 0);
-  const int w_end = bound(wb1, 1);
-
-  float jf[P];
-#pragma unroll
-  for (int p = 0; p < P; ++p) jf[p] = (float)(wj0 + 64 * p + lane);
-
-  // windows are non-decreasing along the sorted list, so the lines whose
-  // window covers [wj0, wj0 + span) are the contiguous range [f_first, f_end)
-  const int f_first = bound(wb1, 2);
-  const int f_end = bound(wb0, 3);
-
-  float acc[P][C];
-  float cmp[P][C];
-#pragma unroll
-  for (int p = 0; p < P; ++p)
-#pragma unroll
-    for (int c = 0; c < C; ++c) { acc[p][c] = 0.f; cmp[p][c] = 0.f; }
-
-  // Adds lines [l0, l1) of the staged tile starting at line `base`.  FULL:
-  // every point is inside the window.  Otherwise a point outside it gets an
-  // infinite offset, whose reciprocal term is 0.
-  auto sum_lines = [&](auto full_tag, int base, int l0, int l1) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    for (int s0 = l0; s0 < l1;) {
-      const int s1 = min(s0 + 16, l1);
-      float part[P][C];
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int c = 0; c < C; ++c) part[p][c] = 0.f;
-      for (int l = s0; l < s1; ++l) add_line_terms<FULL, P>(lds + (l - base) * REC, jf, part);
-#pragma unroll
-      for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int c = 0; c < C; ++c) two_sum_acc(acc[p][c], cmp[p][c], part[p][c]);
-      s0 = s1;
-    }
-  };
-
-  for (int base = blk_first; base < blk_end; base += kLineTile) {
-    const int nt = min(kLineTile, blk_end - base);
-    __syncthreads();
-    for (int q = tid; q < nt * C; q += kKappaThreads) {
-      const int li = q / C, cc = q % C;
-      const int i = base + li;
-      int64_t cell = cell0 + cc;
-      if (cell >= a.n_cells) cell = a.n_cells - 1;
-      if (a.cell_list) cell = a.cell_list[cell];
-      float* rec = lds + li * REC;
-      if (cc == 0) {
-        rec[0] = (float)a.L.m[i];
-        rec[1] = a.L.phi[i];
-        rec[2] = (float)(a.L.wlo[i] - a.L.m[i]);  // -K + [phi > 0]
-        rec[3] = (float)a.K;
-      }
-      line_cell_params_f32(a.L, a.C, i, cell, a.have_E, rec[4 + 2 * cc], rec[5 + 2 * cc]);
-    }
-    __syncthreads();
-
-    const int lb = max(base, w_first), le = min(base + nt, w_end);
-    // lines [f_first, f_end) cover all of the wave's points: no membership test
-    const int fb = min(le, max(lb, f_first)), fe = max(fb, min(le, f_end));
-    sum_lines(std::false_type(), base, lb, fb);
-    sum_lines(std::true_type(), base, fb, fe);
-    sum_lines(std::false_type(), base, fe, le);
-  }
-
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    int64_t cell = cell0 + c;
-    if (cell >= a.n_cells) break;
-    if (a.cell_list && !a.compact_rows) cell = a.cell_list[cell];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const int64_t j = wj0 + 64 * p + lane;
-      if (j >= a.col0 && j < a.col_end) {
-        const float v = acc[p][c] + cmp[p][c];
-        float* o = a.out + cell * a.ld_out + (j - a.col0);
-        *o = (j < a.n_nu) ? (a.accumulate ? *o + v : v) : 0.f;
-      }
-    }
-  }
-}
 
 // ------------------------------------------- line sum tile with far nodes
 // The plain form's line sum.  Over a span of the grid a line whose window
@@ -780,6 +646,144 @@ __device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float*
           *o = (j < a.n_nu) ? (a.accumulate ? *o + v : v) : 0.f;
         }
       }
+  }
+}
+
+// ------------------------------------------------- the precision form's line sum
+// Points [j0, j0 + 512) x kKappaCells cells, every line at every point, with line
+// records from line_cell_params_f32; 512 threads, a span of 64 points per
+// wavefront, each lane points pt and pt + 32 for 4 cells.
+//
+// The order of additions is fixed: the lines of a run of 128 points are taken a
+// stage of 256 at a time, in three ranges (windows that end in the run, cover it,
+// start in it), each range in blocks of 16 lines that are summed plainly and
+// folded in with TwoSum.  A span belongs to a run of 128 points and follows its
+// blocks, and takes of a block the lines that meet it: the others would add zeros.
+//
+// Issue-bound (0.96 of the issue slots).  One span a wavefront instead of two
+// passes over the lines that miss it and leaves registers for seven wavefronts per
+// SIMD instead of five, and eight wavefronts share a stage as four of two spans
+// did.  A call with its Planck table, two spans -> one: 16^3 cells, 20,000 points,
+// 5,000 lines 2.81 -> 2.73 ms; 12^3 cells, 12,000 points, 78,000 lines in windows
+// of 200 points 9.67 -> 6.17 ms, 3,000 lines in windows of 1000 points 0.82 ->
+// 0.77 ms; 5 x 6 x 7 cells, 3,037 points, 760 lines 0.096 -> 0.070 ms.  16^3 cells
+// and 14,000 points with windows of 2000, which few lines miss, 1.83 -> 1.85 ms.
+constexpr int kPrecThreads = 512;
+__device__ inline void kappa_tile(const KappaTile& a, int j0, int64_t cell0, float* lds) {
+  constexpr int C = kKappaCells;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int pt = lane & 31, cg = lane >> 5;
+  const int nl = a.L.n;
+  auto bound = [&](const int4* table, int b, int k) {  // a scalar load: b is uniform
+    return b < a.L.n_spans ? reinterpret_cast<const __attribute__((address_space(4))) int*>(
+                                 reinterpret_cast<uintptr_t>(table))[4 * b + k]
+                           : nl;
+  };
+  const int blk_first = bound(a.L.span4, j0 / 64, 0);
+  const int blk_end = bound(a.L.span4, (j0 + 511) / 64, 1);
+  // the run of 128 points: its lines, and those covering it
+  const int wj0 = j0 + wave * 64, b = wj0 / 64, r = (j0 + (wave >> 1) * 128) / 64;
+  const int w_first = bound(a.L.span4, r, 0), w_end = bound(a.L.span4, r + 1, 1);
+  const int f_first = bound(a.L.span4, r + 1, 2), f_end = bound(a.L.span4, r, 3);
+  // the span's cuts (see kappa_tile_far)
+  const int x = bound(a.L.span4, b, 0), y = bound(a.L.span4, b, 1);
+  const int c0 = min(max(bound(a.L.span4, b, 2), x), y);
+  const int c1 = max(c0, min(bound(a.L.span4, b, 3), y));
+  const int s0 = min(max(bound(a.L.span4, b, 3), x), c0);
+  const int h0 = min(max(bound(a.L.span_far, b, 2), x), s0);
+  const int h1 = min(max(bound(a.L.span_far, b, 3), c1), y);
+
+  float acc[2][4], cmp[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[h][c] = cmp[h][c] = 0.f;
+  float4* hdr = reinterpret_cast<float4*>(lds);
+  float2* par = reinterpret_cast<float2*>(lds + 4 * kLineTile);
+  const int cc = tid % C;
+  CellFactors32 cf;
+  {
+    int64_t scell = cell0 + cc;
+    if (scell >= a.n_cells) scell = a.n_cells - 1;
+    if (a.cell_list) scell = a.cell_list[scell];
+    cf = CellFactors32{a.C.beta2[scell], a.C.theta2[scell], a.C.Gq[scell], a.C.Pf[scell],
+                       a.C.lamf[scell]};
+  }
+  const float jl = (float)wj0 + (float)pt, ju = jl + 32.f;
+
+  for (int base = blk_first; base < blk_end; base += kLineTile) {
+    const int nt = min(kLineTile, blk_end - base);
+    __syncthreads();
+    for (int li = tid / C; li < nt; li += kPrecThreads / C) {
+      const int i = base + li;
+      if (cc == 0) {
+        const int m = a.L.m[i];
+        hdr[li] = make_float4((float)m, a.L.phi[i], (float)(a.L.wlo[i] - m), (float)a.K);
+      }
+      float amp, g2;
+      line_cell_params_f32(a.L, cf, i, a.have_E, amp, g2);
+      par[li * C + cc] = make_float2(amp, g2);
+    }
+    __syncthreads();
+    const int lb = max(base, w_first), le = min(base + nt, w_end);
+    const int fb = min(le, max(lb, f_first)), fe = max(fb, min(le, f_end));
+    auto range = [&](int r0, int r1) {
+      const int first = max(r0, x), end = min(r1, y);
+      for (int g = r0 + ((first - r0) & ~15); g < end; g += 16) {  // the blocks that meet the span
+        const int g0 = max(g, first), g1 = min(g + 16, end);
+        float part[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) part[h][c] = 0.f;
+        auto direct = [&](auto lower, auto upper, int l0, int l1) {
+          l0 = __builtin_amdgcn_readfirstlane(max(l0, g0) - base);
+          l1 = __builtin_amdgcn_readfirstlane(min(l1, g1) - base);
+          for (int l = l0; l < l1; ++l) {
+            const float4 h = hdr[l];
+            const float4* g = reinterpret_cast<const float4*>(par + l * C + 4 * cg);
+            const float4 p0 = g[0], p1 = g[1];
+            add_half<decltype(lower)::value>(h, p0, p1, jl, part[0]);
+            add_half<decltype(upper)::value>(h, p0, p1, ju, part[1]);
+          }
+        };
+        if (g0 >= c0 && g1 <= c1) {
+          direct(Take<kAll>(), Take<kAll>(), c0, c1);
+        } else {
+          direct(Take<kUpTo>(), Take<kNone>(), x, h0);
+          direct(Take<kAll>(), Take<kUpTo>(), h0, s0);
+          direct(Take<kWithin>(), Take<kWithin>(), s0, c0);
+          direct(Take<kAll>(), Take<kAll>(), c0, c1);
+          direct(Take<kFrom>(), Take<kAll>(), c1, h1);
+          direct(Take<kNone>(), Take<kFrom>(), h1, y);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) two_sum_acc(acc[h][c], cmp[h][c], part[h][c]);
+      }
+    };
+    range(lb, fb);
+    range(fb, fe);
+    range(fe, le);
+  }
+
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    int64_t cell = cell0 + 4 * cg + c;
+    if (cell >= a.n_cells) break;
+    if (a.cell_list && !a.compact_rows) cell = a.cell_list[cell];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t j = wj0 + 32 * h + pt;
+      if (j >= a.col0 && j < a.col_end) {
+        const float v = acc[h][c] + cmp[h][c];
+        float* o = a.out + cell * a.ld_out + (j - a.col0);
+        *o = (j < a.n_nu) ? (a.accumulate ? *o + v : v) : 0.f;
+      }
+    }
   }
 }
 

@@ -84,10 +84,10 @@ struct KappaArgs {
 // compensated sum, one span), kPrecSum (the precision form's).
 constexpr int kPlainSum = 0, kCompSum = 1, kPrecSum = 2;
 template <int FORM, int P>
-__global__ __launch_bounds__(kKappaThreads)
-__attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 1 : 5))) void kappa_linesum_kernel(KappaArgs a) {
+__global__ __launch_bounds__(FORM == kPrecSum ? kPrecThreads : kKappaThreads)
+__attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 6 : 5))) void kappa_linesum_kernel(KappaArgs a) {
   static_assert(FORM != kCompSum || P == 1, "a span per wavefront");
-  static_assert(FORM != kPrecSum || P == kKappaPoints, "kappa_tile's points");
+  static_assert(FORM != kPrecSum || kKappaThreads * P == kPrecThreads, "kappa_tile's points");
   __shared__ float4 lds4[kLineTile * kLineRec / 4];
   __shared__ float4 fx4[FORM == kPrecSum ? 1 : kFarEntries];  // floats, or doubles, of 4 wavefronts
   auto sum_tile = [&](const KappaTile& t, int j0, int64_t cell0, bool on) {
@@ -452,7 +452,7 @@ hipError_t launch_kappa(rt_ctx c, bool compensated) {
     if (!compensated) return launch_plain(a, groups, c->stream);
     // the precision form: FP32 line parameters
     hipLaunchKernelGGL((kappa_linesum_kernel<kPrecSum, kKappaPoints>), dim3((unsigned)blocks),
-                       dim3(kKappaThreads), 0, c->stream, a);
+                       dim3(kPrecThreads), 0, c->stream, a);
     return hipGetLastError();
   };
   hipError_t e = launch();
