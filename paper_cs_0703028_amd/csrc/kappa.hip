@@ -71,6 +71,29 @@ __global__ void gas_factor_kernel(int64_t n, const double* __restrict__ T,
   G[c] = cell_G(T[c], x[c], p[c], T_ref, dnu, have_E);
 }
 
+// The walls' row B(nu_j, T_wall); theta = c2 / T_wall (zero: cold walls).  Its
+// blocks ride in a launch of the same call, behind that launch's own.  A launch
+// of its own took 4.5 us, nearly all latency; a plain line sum with it, without:
+// 4^3 cells, 1,000 points 28.2, 26.3 us, 5 x 6 x 7 cells, 3,037 points 38.4, 36.4,
+// 8^3 cells, 10,000 points, dense 745, 736.
+struct WallRow {
+  float2 theta, nu0, dnu;
+  float c1;
+  int n_nu;
+  int64_t ld;
+  float* out = nullptr;
+  unsigned first = 0xffffffffu;  // its first block in the line sum's launch
+};
+
+__device__ __forceinline__ void wall_row(const WallRow& w, int64_t block) {
+  const int64_t j = block * 256 + threadIdx.x;
+  if (j >= w.ld) return;
+  float v = 0.f;
+  if (j < w.n_nu && w.theta.x > 0.f)
+    v = planck_f32(nu_at(j, pair_of(w.nu0), pair_of(w.dnu)), pair_of(w.theta), w.c1);
+  w.out[j] = v;
+}
+
 struct KappaArgs {
   KappaTile t;
   int n_tiles;
@@ -78,6 +101,7 @@ struct KappaArgs {
   TileGate gate;
   int parts = 1;             // line shares per tile, each into its own output
   int64_t part_stride = 0;   // floats between the shares' outputs
+  WallRow wall;              // plain form: its blocks follow the tiles'
 };
 
 // FORM: kPlainSum (P spans per wavefront), kCompSum (the batched launches'
@@ -100,6 +124,13 @@ __attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 6 : 5))) void kappa_linesu
     else
       kappa_tile_far<P>(t, j0, cell0, lds, reinterpret_cast<float*>(fx4) + wave * kFarEntries, on);
   };
+  if constexpr (FORM == kPlainSum) {
+    static_assert(kKappaThreads == 256, "wall_row's blocks");
+    if (blockIdx.x >= a.wall.first) {
+      wall_row(a.wall, blockIdx.x - a.wall.first);
+      return;
+    }
+  }
   const int part = (int)(blockIdx.x % (unsigned)a.parts);
   const int64_t tb = blockIdx.x / (unsigned)a.parts;
   const int tile = (int)(tb % a.n_tiles);
@@ -140,13 +171,19 @@ __attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 6 : 5))) void kappa_linesu
 
 // Planck table: one block per (kPlanckCells cells, 256-point segment of their
 // rows), so that a point's wavenumber and its cube serve several cells.
-// Issue-bound; 16^3 cells, 20,000 points: 73 us (one cell per block: 175).
+// Issue-bound; 16^3 cells, 20,000 points: 73 us (one cell per block: 175).  The
+// walls' row follows the last cells'.
 constexpr int kPlanckCells = 8;
 __global__ __launch_bounds__(256) void planck_table_kernel(
     const float2* __restrict__ theta2, int64_t n_cells, int n_nu, int64_t ld, int tiles_per_row,
-    float2 nu0, float2 dnu, float c1, float* __restrict__ B) {
+    float2 nu0, float2 dnu, float c1, float* __restrict__ B, WallRow wall) {
   const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   const int64_t cell0 = b / tiles_per_row * kPlanckCells;
+  const int64_t wall0 = (n_cells + kPlanckCells - 1) / kPlanckCells * tiles_per_row;
+  if (b >= wall0) {  // (a grid of several rows of blocks has more than needed)
+    wall_row(wall, b - wall0);
+    return;
+  }
   const int64_t j = b % tiles_per_row * 256 + threadIdx.x;
   if (cell0 >= n_cells || j >= ld) return;
   const Pair nu = nu_at(j, pair_of(nu0), pair_of(dnu));
@@ -156,15 +193,9 @@ __global__ __launch_bounds__(256) void planck_table_kernel(
     *o = j < n_nu ? planck_f32(nu, pair_of(theta2[cell0 + k]), c1) : 0.f;
 }
 
-// The walls' row B(nu_j, T_wall); theta_wall = c2 / T_wall (zero: cold walls).
-__global__ void wall_table_kernel(float2 theta_wall, int n_nu, int64_t ld, float2 nu0,
-                                  float2 dnu, float c1, float* bw) {
-  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= ld) return;
-  float v = 0.f;
-  if (j < n_nu && theta_wall.x > 0.f)
-    v = planck_f32(nu_at(j, pair_of(nu0), pair_of(dnu)), pair_of(theta_wall), c1);
-  bw[j] = v;
+// The walls' row alone, for the forms whose call has no launch for it to ride in.
+__global__ __launch_bounds__(256) void wall_table_kernel(WallRow wall) {
+  wall_row(wall, blockIdx.x);
 }
 
 // Planck cubics of the plain march: one thread per (cell, chunk of
@@ -414,25 +445,48 @@ hipError_t launch_gas_factor(rt_ctx c, int g) {
 //   larger part: +-500, 1 line a point, 19,200 blocks 4535, 4440, 1,539 blocks
 //   543, 460 (0.25 a point, 19,200 blocks: 924, 1062); +-1000, 1 line a point
 //   3672, 4155.
+// With a walls' row (a.wall.out) its blocks follow.
 static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
   const int64_t blocks = groups * a.n_tiles * a.parts;
+  const int64_t walls = a.wall.out ? a.wall.ld / 256 : 0;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
   const double lines_per_point = (double)a.t.L.n / ((double)a.t.n_nu + 2.0 * a.t.K);
   if (blocks < 6 * 256 || a.t.K <= 256 || (a.t.K <= 512 && lines_per_point >= 0.9)) {
     a.n_tiles *= 2;
     a.tile_begin *= 2;
-    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, 1>), dim3((unsigned)(2 * blocks)),
+    if (walls) a.wall.first = (unsigned)(2 * blocks);
+    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, 1>), dim3((unsigned)(2 * blocks + walls)),
                        dim3(kKappaThreads), 0, s, a);
   } else {
-    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, kKappaPoints>), dim3((unsigned)blocks), dim3(kKappaThreads),
-                       0, s, a);
+    if (walls) a.wall.first = (unsigned)blocks;
+    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, kKappaPoints>),
+                       dim3((unsigned)(blocks + walls)), dim3(kKappaThreads), 0, s, a);
   }
   return hipGetLastError();
 }
 
+// v as an FP32 pair hi + lo (host).
+static float2 host_pair(double v) {
+  const float h = (float)v;
+  return make_float2(h, (float)(v - (double)h));
+}
+
+static WallRow wall_row_of(rt_ctx c) {
+  WallRow w;
+  w.theta = c->T_wall > 0.0 ? host_pair(second_radiation_cm_K() / c->T_wall) : make_float2(0.f, 0.f);
+  w.nu0 = host_pair(c->nu0);
+  w.dnu = host_pair(c->dnu);
+  w.c1 = (float)first_radiation_wavenumber();
+  w.n_nu = c->n_nu;
+  w.ld = c->ld;  // a multiple of 256
+  w.out = c->d_bwall;
+  return w;
+}
+
 hipError_t launch_kappa(rt_ctx c, bool compensated) {
   KappaArgs a;
+  if (!compensated && !c->planck) a.wall = wall_row_of(c);
   a.t.L = c->lines;
   a.t.C = c->cells;
   a.t.n_cells = c->n_cells;
@@ -456,6 +510,8 @@ hipError_t launch_kappa(rt_ctx c, bool compensated) {
     return hipGetLastError();
   };
   hipError_t e = launch();
+  a.wall.out = nullptr;  // written
+  a.wall.first = 0xffffffffu;
   // further gases add their line sums, each with its own lines and G
   for (int g = 1; g < kMaxGases && e == hipSuccess; ++g) {
     const ExtraGas& gs = c->gas[g - 1];
@@ -521,30 +577,19 @@ hipError_t launch_planck_cubics(rt_ctx c, const double* theta, int64_t n, float4
   return hipGetLastError();
 }
 
-// v as an FP32 pair hi + lo (host).
-static float2 host_pair(double v) {
-  const float h = (float)v;
-  return make_float2(h, (float)(v - (double)h));
-}
-
 hipError_t launch_planck(rt_ctx c) {
-  const float c1 = (float)first_radiation_wavenumber();
-  const double c2 = second_radiation_cm_K();
-  const float2 nu0 = host_pair(c->nu0), dnu = host_pair(c->dnu);
-  const int tiles = (int)((c->ld + 255) / 256);
+  const WallRow wall = wall_row_of(c);
+  const int tiles = (int)(c->ld / 256);
   if (c->planck) {
-    const int64_t blocks = (c->n_cells + kPlanckCells - 1) / kPlanckCells * tiles;
+    const int64_t blocks = ((c->n_cells + kPlanckCells - 1) / kPlanckCells + 1) * tiles;
     const unsigned gx = (unsigned)std::min<int64_t>(blocks, 65536);
     const unsigned gy = (unsigned)((blocks + gx - 1) / gx);
     hipLaunchKernelGGL(planck_table_kernel, dim3(gx, gy), dim3(256), 0, c->stream,
-                       c->cells.theta2, c->n_cells, c->n_nu, c->ld, tiles, nu0, dnu, c1,
-                       c->planck);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+                       c->cells.theta2, c->n_cells, c->n_nu, c->ld, tiles, wall.nu0, wall.dnu,
+                       wall.c1, c->planck, wall);
+  } else {
+    hipLaunchKernelGGL(wall_table_kernel, dim3((unsigned)tiles), dim3(256), 0, c->stream, wall);
   }
-  const float2 theta_wall = c->T_wall > 0.0 ? host_pair(c2 / c->T_wall) : make_float2(0.f, 0.f);
-  hipLaunchKernelGGL(wall_table_kernel, dim3((unsigned)((c->ld + 255) / 256)), dim3(256), 0,
-                     c->stream, theta_wall, c->n_nu, c->ld, nu0, dnu, c1, c->d_bwall);
   return hipGetLastError();
 }
 
