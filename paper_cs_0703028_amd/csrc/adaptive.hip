@@ -417,24 +417,27 @@ __global__ __launch_bounds__(kAdThreads) void adaptive_window_scan_kernel(Window
 // are left to a list; where a span has kFarLines of them they are summed at its
 // Chebyshev nodes, which are interpolated once.
 //
-// Issue-bound: 0.93 of the SIMD cycles, two thirds of them terms (3.5
-// instructions each), the rest line parameters, classifying and selection.
-// 32^3 cells, 50,000 points, 20,000 lines at tolerances 1e-2, 1e-3, 1e-4 and
-// 1e-5, the whole form with wing return: 10.4, 14.8, 22.0 and 31.0 ms (with
-// tests per point in passes of 32 or 64 points and no nodes: 11.5, 17.9, 30.7
-// and 50.8).
+// Issue-bound where lines are many: two thirds of the instructions are terms (3.5
+// each), the rest line parameters, classifying and selection.  Where they are few
+// a block is a chain of dependent loads, and the blocks in flight set the time:
+// stages of 192 lines leave the LDS for eight blocks a CU, against six with 256.
+// 12^3 cells, 12,479 points, 3 lines per cm^-1, tolerance 1e-2: 71.1 -> 67.0 us the
+// call; 32^3 cells, 50,000 points, 20,000 lines with wing return at 1e-3 14.74 ->
+// 13.96 ms (stages of 128: 14.05).  That form with tests per point in passes of 32
+// or 64 points and no nodes took 17.7.
+constexpr int kAdStage = 192;
 constexpr int kFarLines = 16;  // a span's interpolation costs as much as 16 lines save
-__global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(6))) void kappa_adaptive_kernel(
+__global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(8))) void kappa_adaptive_kernel(
     KappaTile a, const uint32_t* __restrict__ win, int n_tiles, const double* __restrict__ wing) {
   constexpr int C = kKappaCells;
   constexpr FarTables tab = make_far_tables();
-  __shared__ float4 hdr[kLineTile];
-  __shared__ __align__(16) float2 par[kLineTile * C];
-  static_assert(kKappaThreads / 64 * kFarEntries <= 2 * kLineTile * C, "the nodes' values lie where par was");
-  __shared__ uint8_t lists[kKappaThreads / 64][kLineTile];
-  __shared__ int sel[2 * kLineTile];  // less than a stage, and a batch
+  __shared__ float4 hdr[kAdStage];
+  __shared__ __align__(16) float2 par[kAdStage * C];
+  static_assert(kKappaThreads / 64 * kFarEntries <= 2 * kAdStage * C, "the nodes' values lie where par was");
+  __shared__ uint8_t lists[kKappaThreads / 64][kAdStage];
+  static_assert(kAdStage <= 256, "a list's entries");
+  __shared__ int sel[kAdStage + kKappaThreads];  // less than a stage, and a batch
   __shared__ int wkeep[kKappaThreads / 64];
-  static_assert(kLineTile == kKappaThreads, "one candidate line per thread");
   const int tile = blockIdx.x % n_tiles;
   const int64_t run = blockIdx.x / n_tiles;
   const int j0 = tile * kKappaThreads;
@@ -483,15 +486,15 @@ __global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(6
   };
 
   for (int base = blk_first, total = 0, done = 0; base < blk_end || done < total;) {
-    // the candidates (hard window meets the block), 256 at a time, whose kept
+    // the candidates (hard window meets the block), one a thread, whose kept
     // window meets the block's points, compacted in order until they fill a
     // stage: only they are staged, so a narrow window costs no amplitude
     // evaluations in the blocks it misses
     __syncthreads();  // the previous stage's records and selection read
     if (done == total) {
       total = done = 0;
-      for (; base < blk_end && total < kLineTile; base += kLineTile) {
-        const int nc = min(kLineTile, blk_end - base);
+      for (; base < blk_end && total < kAdStage; base += kKappaThreads) {
+        const int nc = min(kKappaThreads, blk_end - base);
         bool keep = false;
         if (tid < nc) {
           const uint32_t w = wrow[base + tid];
@@ -514,7 +517,7 @@ __global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(6
       if (total == 0) continue;
     }
     const int* const chosen = sel + done;
-    const int nt = min(kLineTile, total - done);
+    const int nt = min(kAdStage, total - done);
     done += nt;
     for (int li = tid / C; li < nt; li += kKappaThreads / C) {
       const int i = chosen[li];

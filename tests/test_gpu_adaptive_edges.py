@@ -54,3 +54,23 @@ def test_windows_stages_and_nodes(rt, O, n_nu, n_lines, K, eps, wings):
     nz = want != 0
     assert (got[~nz] == 0).all()
     assert (np.abs(got[nz] - want[nz]) <= REL * np.abs(want[nz])).all()
+
+
+@pytest.mark.parametrize("n_lines", [191, 192, 193, 255, 257, 384, 385, 447, 449, 640])
+def test_full_stages(rt, O, n_lines):
+    """Every line kept at every point: lists that end at a stage of 192 lines,
+    at a batch of 256 candidates, and at both."""
+    n_nu, dnu = 257, 0.01
+    g = I.linear_T_grid(9, 0.1, ny=1, nz=1, T_lo=300.0, T_hi=1700.0, x=0.1, p=1.1)
+    L = I.line_list(n_lines, 1000.0 - 0.5, 1000.5 + n_nu * dnu, seed=n_lines, dnu=dnu, n_nu=n_nu,
+                    cutoff=5.0)
+    t = rt.Tracer(0)
+    t.setup_grid(g)
+    t.setup_lines(L)
+    t.set_line_tolerance(1e-12)
+    print(f"adaptive full stages, {n_lines} lines", flush=True)
+    kap, _ = t.compute_kappa(rt.KAPPA_ADAPTIVE)
+    got = kap.cpu().numpy().astype(np.float64)[:, :n_nu]
+    t.close()
+    want = O.kappa_adaptive(g, L, 1e-12)
+    assert (np.abs(got - want) <= REL * np.abs(want)).all()
