@@ -235,14 +235,14 @@ __global__ void planck_cubics_kernel(const double* __restrict__ theta, int64_t n
 // amplitudes of the 64 cells, lane = cell, so that a line's inputs are scalar
 // loads.  32 points wide, a tile meets the lines of 47 points, so a third of
 // the products are real ones; a tile of 64 points would have a fifth, and
-// 16-point tiles twice the LDS reads per product.  ACC adds to the rows (a
-// further gas).
+// 16-point tiles twice the LDS reads per product.  All gases add into one set of
+// accumulators, so a row is written once.
 // 32^3 cells, 50,000 points, 20,000 lines: 1.7 ms, of which writing the 6.6 GB
 // is 1.0, the amplitudes' instructions 0.8 and the matrix instructions 0.45
 // (8 cells per thread and a multiply-add per point and line of its 64 points
-// took 4.1).  The stores bypass the caches: with ordinary ones 2.1 ms.  Four
-// wavefronts of two tiles each took 2% less here and 20% more where a second
-// gas adds to the rows (16^3 cells, 20,000 points: 337 us against 279).
+// took 4.1).  The stores bypass the caches: with ordinary ones 2.1 ms.  Two
+// gases in a launch each, that adds to the rows, and in one: 5,850 cells, 8,297
+// points, 12 lines per cm^-1 172, 53 us; 16^3 cells, 20,000 points 278, 96.
 constexpr int kT16Points = 256;
 constexpr int kT16Cells = 64;
 constexpr int kT16Stage = 64;
@@ -254,10 +254,21 @@ template <class T>
 __device__ __forceinline__ T load_const(const T* p) {  // a wave's same address: a scalar load
   return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
 }
-template <bool ACC>
+struct T16Gas {
+  const int2* tile16;
+  const LineData* data;
+  const float* prof16;
+  const int* m;
+  const float* G;
+  int n_tiles16, have_E;
+};
+struct T16Gases {
+  T16Gas g[kMaxGases];
+  int n;
+};
 __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))) void kappa_table16_kernel(
-    LineSet L, CellSet C, int have_E, int64_t n_cells, int n_nu, int64_t ld, int n_tiles,
-    double pi_dnu, float* __restrict__ out) {
+    T16Gases gases, const double* __restrict__ beta_, const double* __restrict__ theta_,
+    int64_t n_cells, int n_nu, int64_t ld, int n_tiles, double pi_dnu, float* __restrict__ out) {
   // one row more than staged lines: a pair's second line past the last one
   __shared__ int s_m[kT16Stage + 1];
   __shared__ float s_tab[(kT16Stage + 1) * 17];
@@ -267,15 +278,17 @@ __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, sub = lane & 31;
-  const int2 range = tile < L.n_tiles16 ? L.tile16[tile] : make_int2(0, 0);
   const int wj = tile * kT16Points + 32 * wave;
   const int64_t own = min(cell0 + lane, n_cells - 1);
-  const float G = (float)((double)C.G[own] * pi_dnu);
-  const double beta = C.beta[own], theta = C.theta[own];
-  auto amplitude = [&](int i) {
-    const LineData* d = L.data + i;
+  const double beta = beta_[own], theta = theta_[own];
+  auto lines_of = [&](const T16Gas& g) {  // those whose 16 points meet the block's
+    return tile < g.n_tiles16 ? g.tile16[tile] : make_int2(0, 0);
+  };
+  auto factor_of = [&](const T16Gas& g) { return (float)((double)g.G[own] * pi_dnu); };
+  auto amplitude = [&](const T16Gas& g, float G, int i) {
+    const LineData* d = g.data + i;
     float amp = G * load_const(&d->S);
-    if (have_E) {
+    if (g.have_E) {
       amp *= exp_split(load_const(&d->E2) * beta);
       amp *= one_minus_exp_neg_d(load_const(&d->nu) * theta);
     }
@@ -283,39 +296,44 @@ __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))
   };
   bool over = false;  // an amplitude beyond float: its line is left to the end
   f32x16 acc[2] = {};  // [cell half]
-  for (int base = range.x; base < range.y; base += kT16Stage) {
-    const int nt = min(kT16Stage, range.y - base);
-    __syncthreads();
+  for (int k = 0; k < gases.n; ++k) {
+    const T16Gas& g = gases.g[k];
+    const int2 range = lines_of(g);
+    const float G = factor_of(g);
+    for (int base = range.x; base < range.y; base += kT16Stage) {
+      const int nt = min(kT16Stage, range.y - base);
+      __syncthreads();
 #pragma unroll 2
-    for (int li = wave; li < nt; li += kT16Threads / 64) {
-      const float amp = amplitude(base + li);
-      const bool fits = fabsf(amp) <= FLT_MAX;
-      over |= !fits;
-      s_amp[li * kT16Cells + lane] = fits ? amp : 0.f;
-    }
-    for (int q = tid; q < nt * 16; q += kT16Threads)
-      s_tab[(q >> 4) * 17 + (q & 15)] = L.prof16[(int64_t)base * 16 + q];
-    int m = INT_MAX / 2;  // a lane's staged line
-    if (lane < nt) m = L.m[base + lane];
-    if (wave == 0) {
-      s_m[lane] = m;
-      s_tab[lane * 17 + 16] = 0.f;
-    } else if (wave == 1) {  // the row behind the last line
-      s_amp[nt * kT16Cells + lane] = 0.f;
-      if (lane < 17) s_tab[nt * 17 + lane] = 0.f;
-      if (lane == 0) s_m[kT16Stage] = INT_MAX / 2;
-    }
-    __syncthreads();
-    // the staged lines meeting the tile's points: m in [wj - 8, wj + 31 + 7]
-    const int l0 = __popcll(__ballot(m < wj - 8)), l1 = __popcll(__ballot(m <= wj + 38));
-    const int jt = wj + sub + 7;
-    for (int l = l0; l < l1; l += 2) {
-      const int li = l + half;
-      const unsigned u = min((unsigned)(jt - s_m[li]), 16u);
-      const float f = s_tab[li * 17 + u];
-      acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(s_amp[li * kT16Cells + sub], f, acc[0], 0, 0, 0);
-      acc[1] =
-          __builtin_amdgcn_mfma_f32_32x32x2f32(s_amp[li * kT16Cells + 32 + sub], f, acc[1], 0, 0, 0);
+      for (int li = wave; li < nt; li += kT16Threads / 64) {
+        const float amp = amplitude(g, G, base + li);
+        const bool fits = fabsf(amp) <= FLT_MAX;
+        over |= !fits;
+        s_amp[li * kT16Cells + lane] = fits ? amp : 0.f;
+      }
+      for (int q = tid; q < nt * 16; q += kT16Threads)
+        s_tab[(q >> 4) * 17 + (q & 15)] = g.prof16[(int64_t)base * 16 + q];
+      int m = INT_MAX / 2;  // a lane's staged line
+      if (lane < nt) m = g.m[base + lane];
+      if (wave == 0) {
+        s_m[lane] = m;
+        s_tab[lane * 17 + 16] = 0.f;
+      } else if (wave == 1) {  // the row behind the last line
+        s_amp[nt * kT16Cells + lane] = 0.f;
+        if (lane < 17) s_tab[nt * 17 + lane] = 0.f;
+        if (lane == 0) s_m[kT16Stage] = INT_MAX / 2;
+      }
+      __syncthreads();
+      // the staged lines meeting the tile's points: m in [wj - 8, wj + 31 + 7]
+      const int l0 = __popcll(__ballot(m < wj - 8)), l1 = __popcll(__ballot(m <= wj + 38));
+      const int jt = wj + sub + 7;
+      for (int l = l0; l < l1; l += 2) {
+        const int li = l + half;
+        const unsigned u = min((unsigned)(jt - s_m[li]), 16u);
+        const float f = s_tab[li * 17 + u];
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(s_amp[li * kT16Cells + sub], f, acc[0], 0, 0, 0);
+        acc[1] =
+            __builtin_amdgcn_mfma_f32_32x32x2f32(s_amp[li * kT16Cells + 32 + sub], f, acc[1], 0, 0, 0);
+      }
     }
   }
   if (wj < ld) {
@@ -324,8 +342,7 @@ __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))
 #pragma unroll
       for (int i = 0; i < 32; ++i) {
         float* o = out + (cell0 + t16_row(i)) * ld + wj;
-        const float v = acc[i >> 4][i & 15];
-        __builtin_nontemporal_store(ACC ? o[off] + v : v, o + off);
+        __builtin_nontemporal_store(acc[i >> 4][i & 15], o + off);
       }
     } else {
 #pragma unroll
@@ -333,21 +350,25 @@ __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))
         const int64_t cell = cell0 + t16_row(i);
         if (cell + 4 * half >= n_cells) continue;
         float* o = out + cell * ld + wj;
-        const float v = wj + sub < n_nu ? acc[i >> 4][i & 15] : 0.f;
-        __builtin_nontemporal_store(ACC ? o[off] + v : v, o + off);
+        __builtin_nontemporal_store(wj + sub < n_nu ? acc[i >> 4][i & 15] : 0.f, o + off);
       }
     }
   }
   // Zeros of the band times an infinite amplitude would be NaN: such lines add
   // to their own 16 points only.  One wavefront, a lane per row.
   if (__syncthreads_or(over) && wave == 0 && cell0 + lane < n_cells) {
-    for (int i = range.x; i < range.y; ++i) {
-      const float amp = amplitude(i);
-      if (fabsf(amp) <= FLT_MAX) continue;
-      for (int t = 0; t < 16; ++t) {
-        const int j = L.m[i] - 7 + t;
-        if (j >= tile * kT16Points && j < min((tile + 1) * kT16Points, n_nu))
-          out[own * ld + j] = fmaf(amp, L.prof16[(int64_t)i * 16 + t], out[own * ld + j]);
+    for (int k = 0; k < gases.n; ++k) {
+      const T16Gas& g = gases.g[k];
+      const int2 range = lines_of(g);
+      const float G = factor_of(g);
+      for (int i = range.x; i < range.y; ++i) {
+        const float amp = amplitude(g, G, i);
+        if (fabsf(amp) <= FLT_MAX) continue;
+        for (int t = 0; t < 16; ++t) {
+          const int j = g.m[i] - 7 + t;
+          if (j >= tile * kT16Points && j < min((tile + 1) * kT16Points, n_nu))
+            out[own * ld + j] = fmaf(amp, g.prof16[(int64_t)i * 16 + t], out[own * ld + j]);
+        }
       }
     }
   }
@@ -359,22 +380,17 @@ hipError_t launch_kappa_table16(rt_ctx c) {
   const int n_tiles = (int)((c->ld + kT16Points - 1) / kT16Points);
   const int64_t blocks = (c->n_cells + kT16Cells - 1) / kT16Cells * n_tiles;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const double pi_dnu = M_PI * c->dnu;
-  hipLaunchKernelGGL((kappa_table16_kernel<false>), dim3((unsigned)blocks), dim3(kT16Threads), 0,
-                     c->stream, c->lines, c->cells, c->have_E ? 1 : 0, c->n_cells, c->n_nu,
-                     c->ld, n_tiles, pi_dnu, c->kappa);
-  hipError_t e = hipGetLastError();
-  for (int g = 1; g < kMaxGases && e == hipSuccess; ++g) {
-    const ExtraGas& gs = c->gas[g - 1];
-    if (!gs.active) continue;
-    CellSet cg = c->cells;
-    cg.G = gs.G;
-    hipLaunchKernelGGL((kappa_table16_kernel<true>), dim3((unsigned)blocks), dim3(kT16Threads), 0,
-                       c->stream, gs.lines, cg, gs.have_E ? 1 : 0, c->n_cells, c->n_nu, c->ld,
-                       n_tiles, pi_dnu, c->kappa);
-    e = hipGetLastError();
-  }
-  return e;
+  T16Gases gases{};
+  auto add = [&](const LineSet& L, const float* G, bool have_E) {
+    gases.g[gases.n++] = T16Gas{L.tile16, L.data, L.prof16, L.m, G, L.n_tiles16, have_E ? 1 : 0};
+  };
+  add(c->lines, c->cells.G, c->have_E);
+  for (const auto& gs : c->gas)
+    if (gs.active) add(gs.lines, gs.G, gs.have_E);
+  hipLaunchKernelGGL(kappa_table16_kernel, dim3((unsigned)blocks), dim3(kT16Threads), 0, c->stream,
+                     gases, c->cells.beta, c->cells.theta, c->n_cells, c->n_nu, c->ld, n_tiles,
+                     M_PI * c->dnu, c->kappa);
+  return hipGetLastError();
 }
 
 hipError_t launch_line_data(rt_ctx c, const LineSet& L) {

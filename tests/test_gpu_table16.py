@@ -135,3 +135,41 @@ def test_table16_tile_edges(rt, O, cells, n_nu, n_lines, huge):
     assert not np.isfinite(kg[:, :n_nu][~fits]).any()
     r = _rel(np.where(fits, kg[:, :n_nu], 0), np.where(fits, ko, 0))
     assert r.size == 0 or r.max() <= REL
+
+
+@pytest.mark.parametrize("cells,n_nu,n_lines,huge", [
+    ((1, 1, 1), 1, (3, 2), 0), ((5, 13, 1), 257, (3, 200), 0), ((8, 8, 1), 256, (64, 1, 65), 0),
+    ((7, 3, 3), 545, (0, 130, 0, 64), 0), ((5, 13, 1), 700, (100, 90), 2),
+])
+def test_table16_gases_share_one_launch(rt, O, cells, n_nu, n_lines, huge):
+    """Two to four gases with lists from a few lines to several stages, some
+    of zero strengths.  huge: lines of the last gas whose
+    amplitude is beyond float."""
+    nx, ny, nz = cells
+    g = I.linear_T_grid(nx, 0.1, ny=ny, nz=nz, x=0.2)
+    lists = [I.line_list(max(n, 1), 999.9, 1000.1 + n_nu * 0.01, seed=n_nu + k, dnu=0.01, n_nu=n_nu)
+             for k, n in enumerate(n_lines)]
+    for L, n in zip(lists, n_lines):
+        if n == 0:  # a list whose lines absorb nothing
+            L.S[:] = 0.0
+    for k in range(huge):
+        lists[-1].S[7 + 30 * k] = 1e300
+    t = rt.Tracer(0)
+    t.setup_grid(g)
+    t.setup_lines(lists[0])
+    gases = [I.Gas(np.full(g.n_cells, 0.05 * (k + 1)), L) for k, L in enumerate(lists[1:])]
+    for k, gas in enumerate(gases, start=1):
+        t.setup_gas(k, gas)
+    print(f"table16 gases {cells} {n_nu} points {n_lines} lines", flush=True)
+    kap, _ = t.compute_kappa(rt.KAPPA_TABLE16)
+    kg = kap.cpu().numpy().astype(np.float64)
+    t.close()
+    ko = O.kappa_table16(g, lists[0])
+    for gas in gases:
+        ko = ko + O.kappa_table16(replace(g, x=gas.x), gas.lines)
+    assert (kg[:, n_nu:] == 0).all()
+    fits = ko < 1e30
+    assert fits.all() == (huge == 0)
+    assert not np.isfinite(kg[:, :n_nu][~fits]).any()
+    r = _rel(np.where(fits, kg[:, :n_nu], 0), np.where(fits, ko, 0))
+    assert r.size == 0 or r.max() <= REL
