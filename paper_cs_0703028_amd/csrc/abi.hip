@@ -884,10 +884,9 @@ rt_status rt_compute_kappa(rt_ctx c, int mode, float* kappa_dev, float* planck_d
     RT_HIP(c, rt::launch_kappa(c, mode == RT_KAPPA_COMPENSATED));
   }
   if (rt_status s = record_end(c, c->kappa_events)) return s;
-  // wall row always (without a cell table the learned form and the plain line
-  // sum have written it); cell table if requested
-  if ((mode != RT_KAPPA_SURROGATE && mode != RT_KAPPA_PLAIN) || c->planck)
-    RT_HIP(c, rt::launch_planck(c));
+  // the walls' row always: with the cell table if requested, else the forms but
+  // the precision form's have written it
+  if (c->planck || mode == RT_KAPPA_COMPENSATED) RT_HIP(c, rt::launch_planck(c));
   if (mode == RT_KAPPA_TABLE16) {
     double lines = c->lines.n;
     for (const auto& g : c->gas)

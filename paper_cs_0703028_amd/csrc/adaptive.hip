@@ -428,7 +428,12 @@ __global__ __launch_bounds__(kAdThreads) void adaptive_window_scan_kernel(Window
 constexpr int kAdStage = 192;
 constexpr int kFarLines = 16;  // a span's interpolation costs as much as 16 lines save
 __global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(8))) void kappa_adaptive_kernel(
-    KappaTile a, const uint32_t* __restrict__ win, int n_tiles, const double* __restrict__ wing) {
+    KappaTile a, const uint32_t* __restrict__ win, int n_tiles, const double* __restrict__ wing,
+    WallRow wall) {
+  if (blockIdx.x >= wall.first) {
+    wall_row(wall, blockIdx.x - wall.first, kKappaThreads);
+    return;
+  }
   constexpr int C = kKappaCells;
   constexpr FarTables tab = make_far_tables();
   __shared__ float4 hdr[kAdStage];
@@ -759,8 +764,10 @@ static hipError_t launch_adaptive(rt_ctx c, bool wings) {
   t.ld_out = c->ld;
   t.col0 = 0;
   t.col_end = c->ld;
-  hipLaunchKernelGGL(kappa_adaptive_kernel, dim3((unsigned)blocks), dim3(kKappaThreads), 0, c->stream,
-                     t, c->d_win, n_tiles, wing);
+  WallRow wall;
+  const unsigned walls = add_wall_row(c, wall, blocks, kKappaThreads);
+  hipLaunchKernelGGL(kappa_adaptive_kernel, dim3((unsigned)blocks + walls), dim3(kKappaThreads), 0,
+                     c->stream, t, c->d_win, n_tiles, wing, wall);
   return hipGetLastError();
 }
 

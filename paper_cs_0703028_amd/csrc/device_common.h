@@ -202,6 +202,29 @@ __device__ __forceinline__ void line_cell_params_f32(const LineSet& L, const Cel
   g2 = gp * gp;
 }
 
+// The walls' row B(nu_j, T_wall); theta = c2 / T_wall (zero: cold walls).  Its
+// blocks ride in a launch of the same call, behind that launch's own.  A launch
+// of its own took 4.5 us, nearly all latency; a plain line sum with it, without:
+// 4^3 cells, 1,000 points 28.2, 26.3 us, 5 x 6 x 7 cells, 3,037 points 38.4, 36.4,
+// 8^3 cells, 10,000 points, dense 745, 736.
+struct WallRow {
+  float2 theta, nu0, dnu;
+  float c1;
+  int n_nu;
+  int64_t ld;
+  float* out = nullptr;
+  unsigned first = 0xffffffffu;  // its first block in the launch
+};
+
+__device__ __forceinline__ void wall_row(const WallRow& w, int64_t block, int threads) {
+  const int64_t j = block * threads + threadIdx.x;
+  if (j >= w.ld) return;
+  float v = 0.f;
+  if (j < w.n_nu && w.theta.x > 0.f)
+    v = planck_f32(nu_at(j, pair_of(w.nu0), pair_of(w.dnu)), pair_of(w.theta), w.c1);
+  w.out[j] = v;
+}
+
 // ------------------------------------------------------------ line sum tile
 // Eq. (2) with the Eq. (1) strength ratio for one block: nu points from j0 on
 // x kKappaCells cells starting at cell0.  Lines whose window meets the block's
@@ -1743,6 +1766,12 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
 }
 
 }  // namespace dev
+
+// kappa.hip: the handle's walls' row; and, where the call writes no Planck table
+// (whose launch has it), its place behind the `blocks` of a launch: the number of
+// its blocks (else none)
+dev::WallRow wall_row_of(rt_ctx c);
+unsigned add_wall_row(rt_ctx c, dev::WallRow& w, int64_t blocks, int threads);
 
 // Line-sum tiles [tile_begin, tile_begin + n_tiles) for n_cell_groups groups
 // of kKappaCells cells (kappa.hip).

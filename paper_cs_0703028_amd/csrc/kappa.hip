@@ -71,29 +71,6 @@ __global__ void gas_factor_kernel(int64_t n, const double* __restrict__ T,
   G[c] = cell_G(T[c], x[c], p[c], T_ref, dnu, have_E);
 }
 
-// The walls' row B(nu_j, T_wall); theta = c2 / T_wall (zero: cold walls).  Its
-// blocks ride in a launch of the same call, behind that launch's own.  A launch
-// of its own took 4.5 us, nearly all latency; a plain line sum with it, without:
-// 4^3 cells, 1,000 points 28.2, 26.3 us, 5 x 6 x 7 cells, 3,037 points 38.4, 36.4,
-// 8^3 cells, 10,000 points, dense 745, 736.
-struct WallRow {
-  float2 theta, nu0, dnu;
-  float c1;
-  int n_nu;
-  int64_t ld;
-  float* out = nullptr;
-  unsigned first = 0xffffffffu;  // its first block in the line sum's launch
-};
-
-__device__ __forceinline__ void wall_row(const WallRow& w, int64_t block) {
-  const int64_t j = block * 256 + threadIdx.x;
-  if (j >= w.ld) return;
-  float v = 0.f;
-  if (j < w.n_nu && w.theta.x > 0.f)
-    v = planck_f32(nu_at(j, pair_of(w.nu0), pair_of(w.dnu)), pair_of(w.theta), w.c1);
-  w.out[j] = v;
-}
-
 struct KappaArgs {
   KappaTile t;
   int n_tiles;
@@ -125,9 +102,8 @@ __attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 6 : 5))) void kappa_linesu
       kappa_tile_far<P>(t, j0, cell0, lds, reinterpret_cast<float*>(fx4) + wave * kFarEntries, on);
   };
   if constexpr (FORM == kPlainSum) {
-    static_assert(kKappaThreads == 256, "wall_row's blocks");
     if (blockIdx.x >= a.wall.first) {
-      wall_row(a.wall, blockIdx.x - a.wall.first);
+      wall_row(a.wall, blockIdx.x - a.wall.first, kKappaThreads);
       return;
     }
   }
@@ -181,7 +157,7 @@ __global__ __launch_bounds__(256) void planck_table_kernel(
   const int64_t cell0 = b / tiles_per_row * kPlanckCells;
   const int64_t wall0 = (n_cells + kPlanckCells - 1) / kPlanckCells * tiles_per_row;
   if (b >= wall0) {  // (a grid of several rows of blocks has more than needed)
-    wall_row(wall, b - wall0);
+    wall_row(wall, b - wall0, 256);
     return;
   }
   const int64_t j = b % tiles_per_row * 256 + threadIdx.x;
@@ -191,11 +167,6 @@ __global__ __launch_bounds__(256) void planck_table_kernel(
   float* o = B + cell0 * ld + j;
   for (int k = 0; k < cells; ++k, o += ld)
     *o = j < n_nu ? planck_f32(nu, pair_of(theta2[cell0 + k]), c1) : 0.f;
-}
-
-// The walls' row alone, for the forms whose call has no launch for it to ride in.
-__global__ __launch_bounds__(256) void wall_table_kernel(WallRow wall) {
-  wall_row(wall, blockIdx.x);
 }
 
 // Planck cubics of the plain march: one thread per (cell, chunk of
@@ -268,7 +239,12 @@ struct T16Gases {
 };
 __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))) void kappa_table16_kernel(
     T16Gases gases, const double* __restrict__ beta_, const double* __restrict__ theta_,
-    int64_t n_cells, int n_nu, int64_t ld, int n_tiles, double pi_dnu, float* __restrict__ out) {
+    int64_t n_cells, int n_nu, int64_t ld, int n_tiles, double pi_dnu, float* __restrict__ out,
+    WallRow wall) {
+  if (blockIdx.x >= wall.first) {
+    wall_row(wall, blockIdx.x - wall.first, kT16Threads);
+    return;
+  }
   // one row more than staged lines: a pair's second line past the last one
   __shared__ int s_m[kT16Stage + 1];
   __shared__ float s_tab[(kT16Stage + 1) * 17];
@@ -376,6 +352,31 @@ __global__ __launch_bounds__(kT16Threads) __attribute__((amdgpu_waves_per_eu(6))
 
 }  // namespace
 
+// v as an FP32 pair hi + lo (host).
+static float2 host_pair(double v) {
+  const float h = (float)v;
+  return make_float2(h, (float)(v - (double)h));
+}
+
+dev::WallRow wall_row_of(rt_ctx c) {
+  dev::WallRow w;
+  w.theta = c->T_wall > 0.0 ? host_pair(second_radiation_cm_K() / c->T_wall) : make_float2(0.f, 0.f);
+  w.nu0 = host_pair(c->nu0);
+  w.dnu = host_pair(c->dnu);
+  w.c1 = (float)first_radiation_wavenumber();
+  w.n_nu = c->n_nu;
+  w.ld = c->ld;  // a multiple of 1536: whole blocks of 256 or 512
+  w.out = c->d_bwall;
+  return w;
+}
+
+unsigned add_wall_row(rt_ctx c, dev::WallRow& w, int64_t blocks, int threads) {
+  if (c->planck) return 0;
+  w = wall_row_of(c);
+  w.first = (unsigned)blocks;
+  return (unsigned)(c->ld / threads);
+}
+
 hipError_t launch_kappa_table16(rt_ctx c) {
   const int n_tiles = (int)((c->ld + kT16Points - 1) / kT16Points);
   const int64_t blocks = (c->n_cells + kT16Cells - 1) / kT16Cells * n_tiles;
@@ -387,9 +388,11 @@ hipError_t launch_kappa_table16(rt_ctx c) {
   add(c->lines, c->cells.G, c->have_E);
   for (const auto& gs : c->gas)
     if (gs.active) add(gs.lines, gs.G, gs.have_E);
-  hipLaunchKernelGGL(kappa_table16_kernel, dim3((unsigned)blocks), dim3(kT16Threads), 0, c->stream,
-                     gases, c->cells.beta, c->cells.theta, c->n_cells, c->n_nu, c->ld, n_tiles,
-                     M_PI * c->dnu, c->kappa);
+  dev::WallRow wall;
+  const unsigned walls = add_wall_row(c, wall, blocks, kT16Threads);
+  hipLaunchKernelGGL(kappa_table16_kernel, dim3((unsigned)blocks + walls), dim3(kT16Threads), 0,
+                     c->stream, gases, c->cells.beta, c->cells.theta, c->n_cells, c->n_nu, c->ld,
+                     n_tiles, M_PI * c->dnu, c->kappa, wall);
   return hipGetLastError();
 }
 
@@ -464,7 +467,7 @@ hipError_t launch_gas_factor(rt_ctx c, int g) {
 // With a walls' row (a.wall.out) its blocks follow.
 static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
   const int64_t blocks = groups * a.n_tiles * a.parts;
-  const int64_t walls = a.wall.out ? a.wall.ld / 256 : 0;
+  const int64_t walls = a.wall.out ? a.wall.ld / kKappaThreads : 0;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (blocks == 0) return hipSuccess;
   const double lines_per_point = (double)a.t.L.n / ((double)a.t.n_nu + 2.0 * a.t.K);
@@ -480,24 +483,6 @@ static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
                        dim3((unsigned)(blocks + walls)), dim3(kKappaThreads), 0, s, a);
   }
   return hipGetLastError();
-}
-
-// v as an FP32 pair hi + lo (host).
-static float2 host_pair(double v) {
-  const float h = (float)v;
-  return make_float2(h, (float)(v - (double)h));
-}
-
-static WallRow wall_row_of(rt_ctx c) {
-  WallRow w;
-  w.theta = c->T_wall > 0.0 ? host_pair(second_radiation_cm_K() / c->T_wall) : make_float2(0.f, 0.f);
-  w.nu0 = host_pair(c->nu0);
-  w.dnu = host_pair(c->dnu);
-  w.c1 = (float)first_radiation_wavenumber();
-  w.n_nu = c->n_nu;
-  w.ld = c->ld;  // a multiple of 256
-  w.out = c->d_bwall;
-  return w;
 }
 
 hipError_t launch_kappa(rt_ctx c, bool compensated) {
@@ -594,18 +579,14 @@ hipError_t launch_planck_cubics(rt_ctx c, const double* theta, int64_t n, float4
 }
 
 hipError_t launch_planck(rt_ctx c) {
-  const WallRow wall = wall_row_of(c);
+  const dev::WallRow wall = wall_row_of(c);
   const int tiles = (int)(c->ld / 256);
-  if (c->planck) {
-    const int64_t blocks = ((c->n_cells + kPlanckCells - 1) / kPlanckCells + 1) * tiles;
-    const unsigned gx = (unsigned)std::min<int64_t>(blocks, 65536);
-    const unsigned gy = (unsigned)((blocks + gx - 1) / gx);
-    hipLaunchKernelGGL(planck_table_kernel, dim3(gx, gy), dim3(256), 0, c->stream,
-                       c->cells.theta2, c->n_cells, c->n_nu, c->ld, tiles, wall.nu0, wall.dnu,
-                       wall.c1, c->planck, wall);
-  } else {
-    hipLaunchKernelGGL(wall_table_kernel, dim3((unsigned)tiles), dim3(256), 0, c->stream, wall);
-  }
+  const int64_t n = c->planck ? c->n_cells : 0;
+  const int64_t blocks = ((n + kPlanckCells - 1) / kPlanckCells + 1) * tiles;
+  const unsigned gx = (unsigned)std::min<int64_t>(blocks, 65536);
+  const unsigned gy = (unsigned)((blocks + gx - 1) / gx);
+  hipLaunchKernelGGL(planck_table_kernel, dim3(gx, gy), dim3(256), 0, c->stream, c->cells.theta2,
+                     n, c->n_nu, c->ld, tiles, wall.nu0, wall.dnu, wall.c1, c->planck, wall);
   return hipGetLastError();
 }
 

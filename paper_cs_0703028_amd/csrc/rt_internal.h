@@ -326,8 +326,8 @@ hipError_t launch_kappa_table16(rt_ctx c);
 // adds the kept evaluations to *c->d_adapt_evals.
 hipError_t launch_kappa_adaptive(rt_ctx c);
 // the Planck table (when c->planck is set) and the wall row, both evaluated in
-// FP32 from the precision form's inputs (without a table the plain line sum
-// writes the wall row in its own launch)
+// FP32 from the precision form's inputs; without a table the kappa forms but the
+// precision form's write the wall row in their own launch
 hipError_t launch_planck(rt_ctx c);
 // the handle's own ray scratch (rt_trace_rays, rt_trace_explicit, rt_debug_segments)
 RayScratch owned_rays(rt_ctx c);
