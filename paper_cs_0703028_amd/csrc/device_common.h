@@ -1624,26 +1624,25 @@ __device__ __forceinline__ void planck_lane(const PlanckLane& p, double th, floa
 // (uniform), kPlainQ per lane.
 //
 // Issue-bound where rays are dense: a point takes its multiply, the
-// exponential, B, I - B, the update and two sums, 7 instructions, and a
-// segment 33 more (Planck cubic, tests, staging, flush, the ray's ends),
-// shared by the lane's kPlainQ points.  24 points per lane spread those best
-// but put 6 KB of each crossed cell's row in flight per wavefront, a whole
-// XCD's L2.  32^3 cells, 50,000 points, 2^20 rays: 9.7 instructions per
-// update and 2.5 TB past L2 in 498 ms at 12 points, 530 ms at 24, 526 ms at
-// 16, 655 ms at 8 (with sums over a per point, general Planck values and 24
-// points it was 11.6 instructions, 3.45 TB and 543 ms).  Where rays are sparse
+// exponential, a, B, I - B, the update, two sums and half a maximum, 8.5
+// instructions, and a segment 24 more (Planck cubic, test, staging, flush, the
+// ray's ends), shared by the lane's kPlainQ points.  24 points per lane spread
+// those best but put 6 KB of each crossed cell's row in flight per wavefront, a
+// whole XCD's L2.  32^3 cells, 50,000 points, 2^20 rays: 10.5 instructions per
+// update and 2.6 TB past L2 in 512 ms at 12 points (at 24 points with general
+// Planck values, the result copied around the loop, it was 11.6 instructions,
+// 3.45 TB and 562 ms).  Where rays are sparse
 // (about 100 per cell) each row is read from beyond L2 for nearly every
 // crossing, at 7 TB/s, and fewer wavefronts in flight are better: the launches
 // pad the block's LDS to hold 6 or 7 per SIMD.
 //
-// The sums run over t = e^{-tau} itself: with W = sum I t and V = sum B t a
-// segment emits sum B - V and absorbs S - W, S = sum I being W + emitted of
-// the segment before, so that a = 1 - t is not formed per point.  These
-// differences lose at most a factor 1/a <= 32 of FP32 rounding, no more than
-// 1 - t loses at tau = 1/32, while every lane emits and absorbs at least 1/32
-// of its sums.  Where a lane does not, the segment's sums are formed again over
-// a = tau - tau^2/2 + tau^3/6, written in x = -tau log2(e) (truncation below
-// tau^3/24 = 1.3e-6 relative), or 1 - t from tau = 1/32 on.
+// Both the sums and the update of I take a and not e^-tau: sums of I e^-tau and
+// (I - B) e^-tau + B save an instruction a point and lose a thin cell's a, and
+// with it what the cells behind absorb and the walls receive (cold walls, 16
+// cells of tau = 1e-4: 2e-4 of the absorbed power).  a is tau - tau^2/2 +
+// tau^3/6, written in x = -tau log2(e) (truncation below tau^3/24 = 1.3e-6
+// relative), below tau = 1/32 and 1 - e^-tau from there on; a wavefront without
+// a thinner point skips the series.
 // CUBIC: Planck cubics, else planck_lane.  SCALAR: see load_seg.
 // stage: this wavefront's PlainStage::kEntries LDS floats; slot: the ray's
 // index in its launch, which picks its balance row.
@@ -1653,8 +1652,8 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
                                             int64_t slot) {
   constexpr int Q = kPlainQ;
   const int64_t row0 = a.row0 + (slot & a.rep_mask) * a.rep_rows;
-  constexpr float kThin = 0.03125f;
   constexpr float nlog2e = -1.4426950408889634f;
+  constexpr float kThinX = 0.03125f * nlog2e;  // tau = 1/32
   const unsigned voff = (unsigned)lane * (Q * 4);            // bytes into the chunk's row
   const char* kchunk = reinterpret_cast<const char*>(a.kappa + (j0 - a.col0));
   const int64_t j = j0 + lane * Q;
@@ -1677,10 +1676,9 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
     pl.three_nu2 = (float)(3.0 / (pl.nu_a * pl.nu_a));
     pl.dnu = (float)a.dnu;
   }
-  float S = 0.f;  // sum of I over the lane's points
+  float enter = 0.f;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) S += I[q];
-  const float enter = S;
+  for (int q = 0; q < Q; ++q) enter += I[q];
   int np = 0, k0 = 0;  // staged entries, and the segment of the first
   IntPair s = ns > 0 ? load_seg<SCALAR>(sg) : IntPair{0, 0};
   for (int k = 0; k < ns; ++k) {
@@ -1699,7 +1697,7 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
         kv[4 * h] = v.x; kv[4 * h + 1] = v.y; kv[4 * h + 2] = v.z; kv[4 * h + 3] = v.w;
       }
     }
-    if (k + 1 < ns) s = load_seg<SCALAR>(sg + k + 1);  // the next segment's, early
+    s = load_seg<SCALAR>(sg + min(k + 1, ns - 1));  // the next segment's, early
     const float xs = l * nlog2e;
     float B0, K1, K2 = 0.f;
     if (CUBIC) {
@@ -1710,43 +1708,35 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
     } else {
       planck_lane(pl, a.theta[c], B0, K1, K2);
     }
-    float x[Q], t[Q], B[Q];
+    asm("" : "+v"(B0), "+v"(K1));  // formed here: their load is not put off past the test
+    float av[Q], B[Q];  // a, and x until the series have been chosen
+    float xmax = kv[0] * xs;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      x[q] = kv[q] * xs;
-      t[q] = __builtin_amdgcn_exp2f(x[q]);
+      const float x = kv[q] * xs;
+      xmax = fmaxf(xmax, x);
+      av[q] = 1.0f - __builtin_amdgcn_exp2f(x);
       B[q] = q == 0 ? B0 : fmaf(CUBIC ? K1 : fmaf(K2, (float)q, K1), (float)q, B0);
     }
-    float W = I[0] * t[0], V = B[0] * t[0];
-#pragma unroll
-    for (int q = 1; q < Q; ++q) {
-      W = fmaf(I[q], t[q], W);
-      V = fmaf(B[q], t[q], V);
-    }
-    constexpr float s1 = 0.5f * Q * (Q - 1), s2 = Q * (Q - 1) * (2 * Q - 1) / 6.0f;
-    float sumB = fmaf(K1, s1, B0 * (float)Q);
-    if (!CUBIC) sumB = fmaf(K2, s2, sumB);
-    float em = sumB - V, ab = S - W;
-    if (__ballot(!(fminf(fmaf(-kThin, sumB, em), fmaf(-kThin, S, ab)) >= 0.f))) {
+    if (__ballot(xmax > kThinX)) {
       constexpr float L1 = -0.69314718055994531f, L2 = -0.24022650695910071f,
                       L3 = -0.055504108664821576f;
-      constexpr float xlim = kThin * nlog2e;
-      ab = 0.f;
-      em = 0.f;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const float ser = x[q] * fmaf(x[q], fmaf(x[q], L3, L2), L1);
-        const float av = x[q] > xlim ? ser : 1.0f - t[q];
-        ab = fmaf(I[q], av, ab);
-        em = fmaf(B[q], av, em);
+        const float x = kv[q] * xs;
+        const float ser = x * fmaf(x, fmaf(x, L3, L2), L1);
+        av[q] = x > kThinX ? ser : av[q];
       }
     }
-    S = W + em;
-    // I = (I - B) t + B in the three-address form: the compiler would add into
-    // B's register and copy the Q results back around the loop
+    float ab = 0.f, em = 0.f;
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
-      asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(I[q]) : "v"(I[q] - B[q]), "v"(t[q]), "v"(B[q]));
+    for (int q = 0; q < Q; ++q) {
+      ab = fmaf(I[q], av[q], ab);
+      em = fmaf(B[q], av[q], em);
+      // I <- I - (I - B) a, in place: the compiler would form it beside I, keep
+      // a and B live across the flush and copy the Q results back around the loop
+      asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(I[q]) : "v"(B[q] - I[q]), "v"(av[q]));
+    }
     plain_stage(stage, np, lane, ab, em);
     if (++np == PlainStage::kSegs) {
       plain_flush(a, stage, sg, ns, k0, np, lane, row0, 0);
@@ -1754,6 +1744,9 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
       np = 0;
     }
   }
+  float esc = 0.f;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) esc += I[q];
   if (EXIT) {
 #pragma unroll
     for (int h = 0; h < Q / 4; ++h)
@@ -1761,7 +1754,7 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
           make_float4(I[4 * h], I[4 * h + 1], I[4 * h + 2], I[4 * h + 3]);
   }
   // np < kSegs here: one more entry, the balance row's (entering, escaped)
-  plain_stage(stage, np, lane, enter, S);
+  plain_stage(stage, np, lane, enter, esc);
   plain_flush(a, stage, sg, ns, k0, np + 1, lane, row0, a.bal_row0 + (slot & a.bal_mask));
 }
 
