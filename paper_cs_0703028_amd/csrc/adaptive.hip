@@ -35,6 +35,7 @@
 
 #include "adaptive.h"
 #include "device_common.h"
+#include "launch_pieces.h"
 
 namespace rt {
 namespace {
@@ -428,8 +429,8 @@ __global__ __launch_bounds__(kAdThreads) void adaptive_window_scan_kernel(Window
 constexpr int kAdStage = 192;
 constexpr int kFarLines = 16;  // a span's interpolation costs as much as 16 lines save
 __global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(8))) void kappa_adaptive_kernel(
-    KappaTile a, const uint32_t* __restrict__ win, int n_tiles, const double* __restrict__ wing,
-    WallRow wall) {
+    KappaTile a, const uint32_t* __restrict__ win, int n_tiles, int64_t run0,
+    const double* __restrict__ wing, WallRow wall) {
   if (blockIdx.x >= wall.first) {
     wall_row(wall, blockIdx.x - wall.first, kKappaThreads);
     return;
@@ -444,7 +445,7 @@ __global__ __launch_bounds__(kKappaThreads) __attribute__((amdgpu_waves_per_eu(8
   __shared__ int sel[kAdStage + kKappaThreads];  // less than a stage, and a batch
   __shared__ int wkeep[kKappaThreads / 64];
   const int tile = blockIdx.x % n_tiles;
-  const int64_t run = blockIdx.x / n_tiles;
+  const int64_t run = run0 + blockIdx.x / n_tiles;
   const int j0 = tile * kKappaThreads;
   const int64_t cell0 = run * C;
   const int tid = threadIdx.x;
@@ -694,12 +695,11 @@ static hipError_t launch_adaptive(rt_ctx c, bool wings) {
   const LineSet& L = c->lines;
   const int64_t runs = (c->n_cells + RT_ADAPTIVE_GROUP - 1) / RT_ADAPTIVE_GROUP;
   const int n_tiles = (int)((c->ld + kKappaThreads - 1) / kKappaThreads);
-  const int64_t blocks = runs * n_tiles;
   const int64_t pairs = runs * (int64_t)L.n;
   const int64_t wblocks = (pairs + kAdThreads - 1) / kAdThreads;
   const int line_blocks = (L.n + kAdThreads - 1) / kAdThreads;
   const int64_t sblocks = runs * line_blocks;
-  if (blocks > 0x7fffffffLL || wblocks > 0x7fffffffLL || sblocks > 0x7fffffffLL ||
+  if (wblocks > 0x7fffffffLL || sblocks > 0x7fffffffLL ||
       c->n_cells > 0x7fffffffLL)
     return hipErrorInvalidValue;
   double* cellv = c->d_sbar;  // [2][cells]: sbar, q; then the FP32 records
@@ -764,11 +764,17 @@ static hipError_t launch_adaptive(rt_ctx c, bool wings) {
   t.ld_out = c->ld;
   t.col0 = 0;
   t.col_end = c->ld;
-  WallRow wall;
-  const unsigned walls = add_wall_row(c, wall, blocks, kKappaThreads);
-  hipLaunchKernelGGL(kappa_adaptive_kernel, dim3((unsigned)blocks + walls), dim3(kKappaThreads), 0,
-                     c->stream, t, c->d_win, n_tiles, wing, wall);
-  return hipGetLastError();
+  const int64_t walls = c->planck ? 0 : c->ld / kKappaThreads;  // blocks of the walls' row
+  const bool fits = for_pieces(
+      runs, n_tiles, walls, kKappaThreads, [&](int64_t first, int64_t, int64_t blocks, bool last) {
+        WallRow wall;
+        const unsigned extra = last ? add_wall_row(c, wall, blocks, kKappaThreads) : 0;
+        hipLaunchKernelGGL(kappa_adaptive_kernel, dim3((unsigned)blocks + extra),
+                           dim3(kKappaThreads), 0, c->stream, t, c->d_win, n_tiles, first, wing, wall);
+        e = hipGetLastError();
+        return e == hipSuccess;
+      });
+  return fits || e != hipSuccess ? e : hipErrorInvalidValue;
 }
 
 hipError_t launch_kappa_adaptive(rt_ctx c) { return launch_adaptive(c, false); }

@@ -12,6 +12,7 @@
 
 #include "batch_plan.h"
 #include "device_common.h"
+#include "launch_pieces.h"
 
 namespace rt {
 namespace {
@@ -75,6 +76,7 @@ struct KappaArgs {
   KappaTile t;
   int n_tiles;
   int tile_begin;
+  int64_t group0 = 0;        // the launch's first group of cells
   TileGate gate;
   int parts = 1;             // line shares per tile, each into its own output
   int64_t part_stride = 0;   // floats between the shares' outputs
@@ -110,7 +112,7 @@ __attribute__((amdgpu_waves_per_eu(FORM == kPrecSum ? 6 : 5))) void kappa_linesu
   const int part = (int)(blockIdx.x % (unsigned)a.parts);
   const int64_t tb = blockIdx.x / (unsigned)a.parts;
   const int tile = (int)(tb % a.n_tiles);
-  const int64_t cg = tb / a.n_tiles;
+  const int64_t cg = a.group0 + tb / a.n_tiles;
   constexpr int kTilePoints = kKappaThreads * P;
   const int j0 = (a.tile_begin + tile) * kTilePoints;
   bool wave_on = true;
@@ -380,7 +382,7 @@ unsigned add_wall_row(rt_ctx c, dev::WallRow& w, int64_t blocks, int threads) {
 hipError_t launch_kappa_table16(rt_ctx c) {
   const int n_tiles = (int)((c->ld + kT16Points - 1) / kT16Points);
   const int64_t blocks = (c->n_cells + kT16Cells - 1) / kT16Cells * n_tiles;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (!launch_fits(blocks + c->ld / kT16Threads, kT16Threads)) return hipErrorInvalidValue;
   T16Gases gases{};
   auto add = [&](const LineSet& L, const float* G, bool have_E) {
     gases.g[gases.n++] = T16Gas{L.tile16, L.data, L.prof16, L.m, G, L.n_tiles16, have_E ? 1 : 0};
@@ -446,6 +448,25 @@ hipError_t launch_gas_factor(rt_ctx c, int g) {
   return hipGetLastError();
 }
 
+// One form of the line sum: a.n_tiles tiles (of the form's points) and a.parts
+// shares for `groups` groups of cells, and `walls` blocks of the walls' row.
+template <int FORM, int P>
+static hipError_t launch_sum(KappaArgs a, int64_t groups, int64_t walls, hipStream_t s) {
+  constexpr int threads = FORM == kPrecSum ? kPrecThreads : kKappaThreads;
+  hipError_t e = hipSuccess;
+  const bool fits = for_pieces(
+      groups, (int64_t)a.n_tiles * a.parts, walls, threads,
+      [&](int64_t first, int64_t, int64_t blocks, bool last) {
+        a.group0 = first;
+        a.wall.first = last && walls ? (unsigned)blocks : 0xffffffffu;
+        hipLaunchKernelGGL((kappa_linesum_kernel<FORM, P>),
+                           dim3((unsigned)(blocks + (last ? walls : 0))), dim3(threads), 0, s, a);
+        e = hipGetLastError();
+        return e == hipSuccess;
+      });
+  return fits || e != hipSuccess ? e : hipErrorInvalidValue;
+}
+
 // The plain line sum of a.n_tiles tiles of kKappaTilePoints points for
 // `groups` groups of cells, or of twice as many tiles of half the points, with
 // the same values bit for bit.  Half tiles have six wavefronts a SIMD instead
@@ -464,25 +485,18 @@ hipError_t launch_gas_factor(rt_ctx c, int g) {
 //   larger part: +-500, 1 line a point, 19,200 blocks 4535, 4440, 1,539 blocks
 //   543, 460 (0.25 a point, 19,200 blocks: 924, 1062); +-1000, 1 line a point
 //   3672, 4155.
-// With a walls' row (a.wall.out) its blocks follow.
+// With a walls' row (a.wall.out) its blocks follow.  Tables of more blocks than a
+// launch holds (137 GB in half tiles) take several.
 static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
   const int64_t blocks = groups * a.n_tiles * a.parts;
   const int64_t walls = a.wall.out ? a.wall.ld / kKappaThreads : 0;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (blocks == 0) return hipSuccess;
   const double lines_per_point = (double)a.t.L.n / ((double)a.t.n_nu + 2.0 * a.t.K);
   if (blocks < 6 * 256 || a.t.K <= 256 || (a.t.K <= 512 && lines_per_point >= 0.9)) {
     a.n_tiles *= 2;
     a.tile_begin *= 2;
-    if (walls) a.wall.first = (unsigned)(2 * blocks);
-    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, 1>), dim3((unsigned)(2 * blocks + walls)),
-                       dim3(kKappaThreads), 0, s, a);
-  } else {
-    if (walls) a.wall.first = (unsigned)blocks;
-    hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, kKappaPoints>),
-                       dim3((unsigned)(blocks + walls)), dim3(kKappaThreads), 0, s, a);
+    return launch_sum<kPlainSum, 1>(a, groups, walls, s);
   }
-  return hipGetLastError();
+  return launch_sum<kPlainSum, kKappaPoints>(a, groups, walls, s);
 }
 
 hipError_t launch_kappa(rt_ctx c, bool compensated) {
@@ -501,18 +515,13 @@ hipError_t launch_kappa(rt_ctx c, bool compensated) {
   a.n_tiles = (int)((c->ld + kKappaTilePoints - 1) / kKappaTilePoints);
   a.tile_begin = 0;
   const int64_t groups = (c->n_cells + kKappaCells - 1) / kKappaCells;
-  const int64_t blocks = groups * a.n_tiles;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   auto launch = [&]() {
     if (!compensated) return launch_plain(a, groups, c->stream);
     // the precision form: FP32 line parameters
-    hipLaunchKernelGGL((kappa_linesum_kernel<kPrecSum, kKappaPoints>), dim3((unsigned)blocks),
-                       dim3(kPrecThreads), 0, c->stream, a);
-    return hipGetLastError();
+    return launch_sum<kPrecSum, kKappaPoints>(a, groups, 0, c->stream);
   };
   hipError_t e = launch();
   a.wall.out = nullptr;  // written
-  a.wall.first = 0xffffffffu;
   // further gases add their line sums, each with its own lines and G
   for (int g = 1; g < kMaxGases && e == hipSuccess; ++g) {
     const ExtraGas& gs = c->gas[g - 1];
@@ -541,12 +550,7 @@ hipError_t launch_kappa_tiles(rt_ctx c, const KappaTile& t, int64_t n_cell_group
   // the compensated sum has its own tiles of 256 points
   a.n_tiles *= kKappaPoints;
   a.tile_begin *= kKappaPoints;
-  const int64_t blocks = n_cell_groups * a.n_tiles;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((kappa_linesum_kernel<kCompSum, 1>), dim3((unsigned)blocks), dim3(kKappaThreads),
-                     0, s, a);
-  return hipGetLastError();
+  return launch_sum<kCompSum, 1>(a, n_cell_groups, 0, s);
 }
 
 // The plain line sum in 256-point tiles (one span per wavefront): twice the
@@ -561,12 +565,7 @@ hipError_t launch_kappa_tiles_fine(rt_ctx c, const KappaTile& t, int64_t n_cell_
   a.gate = gate;
   a.n_tiles = n_tiles;
   a.tile_begin = 0;
-  const int64_t blocks = n_cell_groups * n_tiles;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((kappa_linesum_kernel<kPlainSum, 1>), dim3((unsigned)blocks),
-                     dim3(kKappaThreads), 0, s, a);
-  return hipGetLastError();
+  return launch_sum<kPlainSum, 1>(a, n_cell_groups, 0, s);
 }
 
 hipError_t launch_planck_cubics(rt_ctx c, const double* theta, int64_t n, float4* poly,
