@@ -346,7 +346,11 @@ typedef struct {
 } rt_batch_tuning;
 
 /* A tuning that is valid for any batch: chunked, 3072 points per chunk,
- * one slab (persistent fields 16, 64, 2; the queue needs slots >= 2). */
+ * one slab (persistent fields 16, 64, 2; the queue needs slots >= 2).
+ * A tuning that a call is given runs as it is.  Where a call's tuning is NULL,
+ * this one is used, its slab as two of half the points (the second stream of
+ * slots = 2) in batches where line sum and march then overlap to a gain: the
+ * same tallies bit for bit in the same workspace. */
 rt_status rt_batch_default_tuning(rt_batch_tuning* out);
 
 /* Device workspace the batch needs with this tuning (tuning NULL: default):

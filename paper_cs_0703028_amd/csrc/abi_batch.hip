@@ -32,8 +32,8 @@ rt_status bfail(rt_ctx c, rt_status s, const std::string& m) {
                    std::string(#call) + ": " + hipGetErrorString(e_));                  \
   } while (0)
 
-rt_batch_tuning default_tuning() {
-  rt_batch_tuning t;
+constexpr rt_batch_tuning default_tuning() {
+  rt_batch_tuning t{};
   t.chunk_points = 2 * kChunk;
   t.kappa_groups = 16;
   t.march_rays = 64;
@@ -89,40 +89,50 @@ rt_status check_cases(rt_ctx c, int n_cases, const rt_case* cases) {
 
 int64_t align_up(int64_t v) { return (v + 255) / 256 * 256; }
 
-// Builds the plan (sizes, stages) without touching device memory; returns
-// the workspace bytes through *bytes.  limit_points > 0 restricts the
-// spectral range to the first limit_points points (autotuner trials).
-rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, rt_batch_tuning t,
-                     int64_t limit_points, BatchPlan& pl, int64_t* bytes) {
-  pl.chunked = t.mode == RT_BATCH_CHUNKED;
-  pl.n_cases = n_cases;
-  const int64_t n_nu = limit_points > 0 ? std::min<int64_t>(limit_points, c->n_nu) : c->n_nu;
-  // A single slab serves as two of half the points, so that the line sum of a
-  // chunk, which the arithmetic bounds, runs beside the march of the one before,
-  // which the tables' rows bound: where half a chunk's tiles still fill the chip
-  // and, by the rates of both (1e13 evaluations and 1e12 updates a second), the
-  // shorter of the two is a sixteenth of the other (one slab of 3072 points against two of 1536: 6 cases of 16^3 to 32^3 cells
-  // 88.9, 83.6 ms; 3 of 19^3 to 37^3 29.9, 26.5; 4 dense ones of 8^3 to 16^3
-  // 18.4, 18.0; 6 of 6^3 to 10^3 2.71, 2.78; 3 of 4^3 to 6^3 with compensated
-  // sums 2.7, 3.3; 7 of 8^3 to 16^3 with dense compensated sums and 424 rays
-  // 278, 281).
-  int64_t all_cells = 0;
+// Whether the default tuning's slab runs as two of half the points, so that the
+// line sum of a chunk, which the arithmetic bounds, runs beside the march of the
+// one before, which the tables' rows bound: where half a chunk's tiles still fill
+// the chip and, by the rates of both (1e13 evaluations and 1e12 updates a second),
+// the shorter of the two is a sixteenth of the other (one slab of 3072 points
+// against two of 1536: 6 cases of 16^3 to 32^3 cells 88.9, 83.6 ms; 3 of 19^3 to
+// 37^3 29.9, 26.5; 4 dense ones of 8^3 to 16^3 18.4, 18.0; 6 of 6^3 to 10^3 2.71,
+// 2.78; 3 of 4^3 to 6^3 with compensated sums 2.7, 3.3; 7 of 8^3 to 16^3 with dense
+// compensated sums and 424 rays 278, 281).
+bool halves_pay(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch_tuning& t) {
+  int64_t cells = 0;
   double updates = 0;
   for (int k = 0; k < n_cases; ++k) {
     const rt_case& q = cases[k];
-    all_cells += (int64_t)q.nx * q.ny * q.nz;
+    cells += (int64_t)q.nx * q.ny * q.nz;
     updates += (double)q.n_rays * c->n_nu * 3.0 / (1.0 / q.nx + 1.0 / q.ny + 1.0 / q.nz);
   }
-  const double sum_s = c->line_evals_per_cell * (double)all_cells * 1e-13, march_s = updates * 1e-12;
-  const int64_t half_tiles = all_cells / dev::kKappaCells * (t.chunk_points / 2 / dev::kKappaTilePoints);
-  if (pl.chunked && t.slots == 1 && t.chunk_points % (2 * kChunk) == 0 && n_nu > t.chunk_points &&
-      half_tiles >= 8 * 256 && std::min(sum_s, march_s) >= std::max(sum_s, march_s) / 16) {
+  const double sum_s = c->line_evals_per_cell * (double)cells * 1e-13, march_s = updates * 1e-12;
+  const int64_t half_tiles = cells / dev::kKappaCells * (t.chunk_points / 2 / dev::kKappaTilePoints);
+  return c->n_nu > t.chunk_points && half_tiles >= 8 * 256 &&
+         std::min(sum_s, march_s) >= std::max(sum_s, march_s) / 16;
+}
+
+// Builds the plan (sizes, stages) without touching device memory; returns
+// the workspace bytes through *bytes.  tuning NULL: the default, which may run
+// in halves (halves_pay) in the same workspace; a tuning that the caller gives
+// runs as it is.  limit_points > 0 restricts the spectral range to the first
+// limit_points points (autotuner trials).
+rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch_tuning* tuning,
+                     int64_t limit_points, BatchPlan& pl, int64_t* bytes) {
+  rt_batch_tuning t = tuning ? *tuning : default_tuning();
+  pl.chunked = t.mode == RT_BATCH_CHUNKED;
+  pl.n_cases = n_cases;
+  const int64_t n_nu = limit_points > 0 ? std::min<int64_t>(limit_points, c->n_nu) : c->n_nu;
+  pl.bwall_ld = (n_nu + t.chunk_points - 1) / t.chunk_points * t.chunk_points;
+  static_assert(default_tuning().mode == RT_BATCH_CHUNKED && default_tuning().slots == 1 &&
+                    default_tuning().chunk_points % (2 * kChunk) == 0,
+                "one slab that halves into march chunks");
+  if (!tuning && halves_pay(c, n_cases, cases, t)) {
     t.chunk_points /= 2;
     t.slots = 2;
   }
   pl.tuning = t;
   pl.n_chunks = (int)((n_nu + t.chunk_points - 1) / t.chunk_points);
-  pl.bwall_ld = (int64_t)pl.n_chunks * t.chunk_points;
   pl.cases.assign(n_cases, BatchCase());
   int64_t cell_off = 0, seg_off = 0, ray_off = 0, blk_off = 0, max_cells = 0, row_off = 0;
   double evals = 0;
@@ -357,7 +367,7 @@ rt_status materialize(rt_ctx c, int n_cases, const rt_case* cases, BatchPlan& pl
 }
 
 rt_status prepare_impl(rt_ctx c, int n_cases, const rt_case* cases, int kappa_mode,
-                       const rt_batch_tuning& t, void* ws, int64_t bytes, int64_t limit_points) {
+                       const rt_batch_tuning* t, void* ws, int64_t bytes, int64_t limit_points) {
   for (const auto& g : c->gas)
     if (g.active)
       return bfail(c, RT_EUNSUPPORTED, "batched form: one gas only (gas 0); remove gases 1.. first");
@@ -458,11 +468,11 @@ rt_status rt_batch_default_tuning(rt_batch_tuning* out) {
 rt_status rt_batch_workspace_size(rt_ctx c, int n_cases, const rt_case* cases,
                                   const rt_batch_tuning* tuning, int64_t* bytes) {
   if (!c || !bytes) return RT_EINVAL;
-  const rt_batch_tuning t = tuning ? *tuning : default_tuning();
-  if (rt_status s = check_tuning(c, t)) return s;
+  if (tuning)
+    if (rt_status s = check_tuning(c, *tuning)) return s;
   if (rt_status s = check_cases(c, n_cases, cases)) return s;
   BatchPlan pl;
-  return build_plan(c, n_cases, cases, t, 0, pl, bytes);
+  return build_plan(c, n_cases, cases, tuning, 0, pl, bytes);
 }
 
 rt_status rt_batch_prepare(rt_ctx c, int n_cases, const rt_case* cases, int kappa_mode,
@@ -472,10 +482,10 @@ rt_status rt_batch_prepare(rt_ctx c, int n_cases, const rt_case* cases, int kapp
     return bfail(c, RT_EINVAL, "rt_batch_prepare: unknown kappa mode");
   if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255))
     return bfail(c, RT_EINVAL, "rt_batch_prepare: workspace must be 256-byte aligned device memory");
-  const rt_batch_tuning t = tuning ? *tuning : default_tuning();
-  if (rt_status s = check_tuning(c, t)) return s;
+  if (tuning)
+    if (rt_status s = check_tuning(c, *tuning)) return s;
   if (rt_status s = check_cases(c, n_cases, cases)) return s;
-  return prepare_impl(c, n_cases, cases, kappa_mode, t, ws, bytes, 0);
+  return prepare_impl(c, n_cases, cases, kappa_mode, tuning, ws, bytes, 0);
 }
 
 rt_status rt_batch_launch(rt_ctx c) {
@@ -570,11 +580,11 @@ rt_status rt_batch_autotune(rt_ctx c, int n_cases, const rt_case* cases, int kap
   auto trial = [&](const rt_batch_tuning& t, double* ms) -> rt_status {
     BatchPlan probe;
     int64_t need = 0;
-    if (build_plan(c, n_cases, cases, t, trial_points, probe, &need) != RT_OK || need > bytes) {
+    if (build_plan(c, n_cases, cases, &t, trial_points, probe, &need) != RT_OK || need > bytes) {
       *ms = -1;
       return RT_OK;  // does not fit: skip
     }
-    if (rt_status s = prepare_impl(c, n_cases, cases, kappa_mode, t, ws, bytes, trial_points)) return s;
+    if (rt_status s = prepare_impl(c, n_cases, cases, kappa_mode, &t, ws, bytes, trial_points)) return s;
     for (int rep = 0; rep < 2; ++rep) {
       if (rt_status s = rt_batch_launch(c)) return s;
       if (rt_status s = rt_batch_results(c, nullptr, nullptr, nullptr)) return s;
