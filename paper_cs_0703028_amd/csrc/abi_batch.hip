@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "batch_plan.h"
+#include "launch_pieces.h"
 #include "device_common.h"
 
 namespace {
@@ -151,10 +152,15 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
     b.row_off = row_off;
     row_off += b.copies * b.n_cells + kCaseBalRows;
     b.n_rays = (int64_t)q.n_rays;
-    // one launch adds up to rays x spectral chunks terms to a case's
-    // accumulator words, which hold kAccMaxTerms until normalised
+    // a launch adds up to a term per ray and kMarchPoints points to an
+    // accumulator word: at most 2 kAccMaxTerms where the rays times the chunks of
+    // twice the points stay within kAccMaxTerms, which a cleared word holds, with
+    // the carry from the word below when it is normalised
+    static_assert(kChunk == 2 * dev::kMarchPoints, "a chunk is two of the march's");
+    static_assert((unsigned __int128)(2 * kAccMaxTerms) * ((1u << kAccBits) - 1) +
+                          ((uint64_t)-1 >> kAccBits) <= (uint64_t)-1, "the words' room");
     if ((double)q.n_rays * (double)((c->n_nu + kChunk - 1) / kChunk) > (double)kAccMaxTerms)
-      return bfail(c, RT_EINVAL, "rt_batch: n_rays x spectral chunks of a case must be <= 2^35");
+      return bfail(c, RT_EINVAL, "rt_batch: n_rays x chunks of 1536 points of a case must be <= 2^35");
     b.seg_off = seg_off;
     b.ray_off = ray_off;
     b.blk_off = blk_off;
@@ -182,9 +188,9 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   pl.total_rows = row_off;
   pl.total_rays = ray_off;
   pl.ray_blocks = blk_off;
-  if (pl.chunked && 8 * blk_off > 0x7fffffffLL)
+  if (pl.chunked && !launch_fits(8 * blk_off, 256))
     return bfail(c, RT_EINVAL, "rt_batch: too many rays for one chunked march launch "
-                               "(use RT_BATCH_PERSISTENT or fewer chunk_points)");
+                               "(use RT_BATCH_PERSISTENT)");
   pl.max_cells = max_cells;
   pl.line_evals = limit_points > 0 ? 0.0 : evals;
   pl.slab_stride = (pl.chunked ? cell_off : max_cells) * t.chunk_points;

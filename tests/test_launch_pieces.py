@@ -1,6 +1,7 @@
 """Tables of more blocks than one launch may hold (2^32 threads) go out in
 several launches: the split that the line sums' launches use, compiled alone on
-the host, over tables up to the card's memory and around the limit.
+the host, over tables up to the card's memory and around the limit.  A batch of
+more rays than its march launch may hold is refused before anything is launched.
 """
 import os
 import shutil
@@ -88,3 +89,26 @@ def test_one_group_that_does_not_fit(split):
     assert split(4, LIMIT // 256 + 1, 0, 256) == ([], False)
     assert split(4, 1, LIMIT // 256, 256) == ([], False)
     assert split(0, 5, 0, 256) == ([], True)
+
+
+LIB = os.path.join(ROOT, "paper_cs_0703028_amd", "librtlbl.so")
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="librtlbl.so not built")
+@pytest.mark.parametrize("n_rays,fits", [((1 << 26) - 32, True), (1 << 26, False), (1 << 30, False)])
+def test_batch_rays(n_rays, fits):
+    from paper_cs_0703028_amd import inputs as I
+    from paper_cs_0703028_amd import rtlbl as rt
+    L = I.line_list(5, 1000.0, 1001.0, seed=1, dnu=0.01, n_nu=100)
+    case = I.Workload("c", I.linear_T_grid(2, 0.1), L, n_rays, 1)
+    host = rt.Tracer.host_only()
+    host.setup_lines(L)
+    try:
+        size = host.batch_workspace_size([case])
+    except rt.RtError as e:
+        size, status = 0, e.status
+    assert (size > 0) == fits and (fits or status == rt.RT_EINVAL)
+    tun = rt.Tracer.default_tuning()
+    tun.mode, tun.slots = rt.BATCH_PERSISTENT, 2
+    assert host.batch_workspace_size([case], tun) > 0
+    host.close()
