@@ -188,9 +188,6 @@ rt_status build_plan(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch
   pl.total_rows = row_off;
   pl.total_rays = ray_off;
   pl.ray_blocks = blk_off;
-  if (pl.chunked && !launch_fits(8 * blk_off, 256))
-    return bfail(c, RT_EINVAL, "rt_batch: too many rays for one chunked march launch "
-                               "(use RT_BATCH_PERSISTENT)");
   pl.max_cells = max_cells;
   pl.line_evals = limit_points > 0 ? 0.0 : evals;
   pl.slab_stride = (pl.chunked ? cell_off : max_cells) * t.chunk_points;
@@ -383,6 +380,9 @@ rt_status prepare_impl(rt_ctx c, int n_cases, const rt_case* cases, int kappa_mo
   int64_t need = 0;
   rt_status s = build_plan(c, n_cases, cases, t, limit_points, *pl, &need);
   if (s == RT_OK && need > bytes) s = bfail(c, RT_EINVAL, "rt_batch: workspace too small");
+  if (s == RT_OK && pl->chunked && !launch_fits(8 * pl->ray_blocks, 256))
+    s = bfail(c, RT_EINVAL, "rt_batch: too many rays for one chunked march launch "
+                            "(use RT_BATCH_PERSISTENT)");
   pl->comp = kappa_mode == RT_KAPPA_COMPENSATED;
   c->batch = pl;
   if (s == RT_OK) s = materialize(c, n_cases, cases, *pl, ws);

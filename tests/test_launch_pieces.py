@@ -97,18 +97,22 @@ LIB = os.path.join(ROOT, "paper_cs_0703028_amd", "librtlbl.so")
 @pytest.mark.skipif(not os.path.exists(LIB), reason="librtlbl.so not built")
 @pytest.mark.parametrize("n_rays,fits", [((1 << 26) - 32, True), (1 << 26, False), (1 << 30, False)])
 def test_batch_rays(n_rays, fits):
+    """On a host-only handle, which stops where the first device call would be;
+    the workspace's size is answered for any number of rays."""
+    import ctypes as C
+
     from paper_cs_0703028_amd import inputs as I
     from paper_cs_0703028_amd import rtlbl as rt
     L = I.line_list(5, 1000.0, 1001.0, seed=1, dnu=0.01, n_nu=100)
     case = I.Workload("c", I.linear_T_grid(2, 0.1), L, n_rays, 1)
     host = rt.Tracer.host_only()
     host.setup_lines(L)
-    try:
-        size = host.batch_workspace_size([case])
-    except rt.RtError as e:
-        size, status = 0, e.status
-    assert (size > 0) == fits and (fits or status == rt.RT_EINVAL)
+    arr, keep = host._cases([case])
     tun = rt.Tracer.default_tuning()
     tun.mode, tun.slots = rt.BATCH_PERSISTENT, 2
-    assert host.batch_workspace_size([case], tun) > 0
+    for t, want in ((None, rt.RT_EUNSUPPORTED if fits else rt.RT_EINVAL), (tun, rt.RT_EUNSUPPORTED)):
+        size = host.batch_workspace_size([case], t)
+        assert size > 0
+        assert rt.lib.rt_batch_prepare(host._h, 1, arr, rt.KAPPA_PLAIN, C.byref(t) if t else None,
+                                       C.c_void_p(256), size) == want
     host.close()
