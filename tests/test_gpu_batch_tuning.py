@@ -69,3 +69,26 @@ def test_no_tuning_and_one_slab_give_the_same_bits(rt, n_nu):
     for a, b in zip(free, given):
         for x, y in zip(a, b):
             assert np.array_equal(x, y)
+
+
+def test_a_tuning_timed_on_other_kernels_is_not_served(rt, tmp_path):
+    """Entries of the cache's key v6 were timed on other line sums and marches,
+    and some ran in halves unasked: they are timed anew."""
+    import torch
+    cases = [I.Workload("c", I.linear_T_grid(4, 0.1, x=0.1), I.line_list(
+        20, 1000.0, 1010.0, seed=1, dnu=0.01, n_nu=1000), 100, 3)]
+    t = rt.Tracer(0)
+    t.setup_lines(cases[0].lines)
+    big = _tuning(rt, 4 * rt.MARCH_CHUNK, 8)
+    ws = torch.empty(t.batch_workspace_size(cases, big), dtype=torch.uint8, device="cuda")
+    path = tmp_path / "tune.json"
+    print("cache key", flush=True)
+    t.batch_autotune(cases, rt.KAPPA_PLAIN, ws, str(path))
+    text = path.read_text()
+    key = text.split('"')[1]
+    path.write_text('{\n  "v6|%s": [%d, 16, 64, 2, 7, 0]\n}\n'
+                    % (key.split("|", 1)[1], 64 * rt.MARCH_CHUNK))
+    best = t.batch_autotune(cases, rt.KAPPA_PLAIN, ws, str(path))
+    assert best.chunk_points <= 4 * rt.MARCH_CHUNK and best.slots != 7
+    assert key in path.read_text()
+    t.close()
