@@ -381,7 +381,10 @@ __device__ __forceinline__ void far_reduce(const float (&F)[kFarNodes], int lane
 }
 
 // The node sums of a span (far_reduce's lo and hi) at its points, added to acc:
-// points pt and pt + 32 for 4 cells (see kappa_tile_far).
+// points pt and pt + 32 for 4 cells (see kappa_tile_far).  Where a line's
+// amplitude is beyond float every node holds the infinity that each point's term
+// would be: the points take it from the node they are relative to, and the
+// differences, which would be NaN, are left out.
 __device__ __forceinline__ void far_points(float lo, float hi, int lane, float* fx,
                                            float (&acc)[2][4]) {
   constexpr int C = kKappaCells;
@@ -391,8 +394,9 @@ __device__ __forceinline__ void far_points(float lo, float hi, int lane, float* 
   const float ref = __int_as_float(
       __builtin_amdgcn_ds_bpermute(4 * (8 * kFarRef + (lane & 7)), __float_as_int(lo)));
   __builtin_amdgcn_wave_barrier();
-  fx[lane] = lo - ref;
-  if (lane < 32) fx[64 + lane] = hi - ref;
+  const float dlo = lo - ref, dhi = hi - ref;
+  fx[lane] = __builtin_isfinite(dlo) ? dlo : 0.f;
+  if (lane < 32) fx[64 + lane] = __builtin_isfinite(dhi) ? dhi : 0.f;
   if (lane < C) fx[2 * kFarValues + lane] = ref;
   __builtin_amdgcn_wave_barrier();
   float v[2][4];
@@ -643,12 +647,17 @@ __device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float*
       const int half = (wj0 / 64 + p) & 1;
       const float* dl = far_tables.down[half][lane >> 3];
       const float* dh = far_tables.down[half][n_hi];
+      const float lo0 = lo, hi0 = hi;
 #pragma unroll
       for (int k = 0; k < kFarNodes; ++k) {
         const float f = fx[kFarValues + k * C + (lane & 7)];
         lo = fmaf(dl[k], f, lo);
         hi = fmaf(dh[k], f, hi);
       }
+      // an infinity at the pair's nodes (see far_points)
+      const float f = fx[kFarValues + kFarRef * C + (lane & 7)];
+      if (!__builtin_isfinite(lo)) lo = lo0 + f;
+      if (!__builtin_isfinite(hi)) hi = hi0 + f;
     }
     far_points(lo, hi, lane, fx, acc[p]);
   }
