@@ -1737,16 +1737,16 @@ __device__ __forceinline__ void march_plain(const MarchWave& a, const int2* sg, 
         av[q] = x > kThinX ? ser : av[q];
       }
     }
-    float ab = 0.f, em = 0.f;
+    float ab2[2] = {0.f, 0.f}, em2[2] = {0.f, 0.f};  // two chains: half the roundings in a row
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      ab = fmaf(I[q], av[q], ab);
-      em = fmaf(B[q], av[q], em);
+      ab2[q & 1] = fmaf(I[q], av[q], ab2[q & 1]);
+      em2[q & 1] = fmaf(B[q], av[q], em2[q & 1]);
       // I <- I - (I - B) a, in place: the compiler would form it beside I, keep
       // a and B live across the flush and copy the Q results back around the loop
       asm volatile("v_fmac_f32 %0, %1, %2" : "+v"(I[q]) : "v"(B[q] - I[q]), "v"(av[q]));
     }
-    plain_stage(stage, np, lane, ab, em);
+    plain_stage(stage, np, lane, ab2[0] + ab2[1], em2[0] + em2[1]);
     if (++np == PlainStage::kSegs) {
       plain_flush(a, stage, sg, ns, k0, np, lane, row0, 0);
       k0 += np;
