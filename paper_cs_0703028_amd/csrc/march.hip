@@ -345,16 +345,18 @@ bool planck_cubic_fits(double T_min, double T_max, double nu0, double dnu, int n
 
 // Where the visits of a cell's rows (of n_rays_total rays, a mean path of 3 /
 // (1/nx + 1/ny + 1/nz) segments) are few for the size of the grid, the rows
-// come from beyond L2 and 4 points per lane are faster.  The line, from 16^3 to
-// 28^3 cells (8 against 4, microseconds): 16^3, 10,000 points 80 visits 2647,
-// 2582; 160 4464, 5113.  20^3 80: 6052, 5260; 160 10,533, 10,041.  24^3 160:
-// 19,727, 17,370; 320 29,633, 34,912.  12^3 40: 1103, 1141.  It depends on the
-// ray set and not on the part of it in a call, so that every split of a set
-// adds the same sums.
+// come from beyond L2 and 4 points per lane are faster.  The line, at 20,000
+// points (8 against 4, microseconds; 6,000 and 10,000 points cross at the same
+// visits): 14^3 cells, 40 visits 1988, 1810; 80 3064, 3374.  16^3, 80 5142, 5026;
+// 120 7182, 7446.  18^3, 120 11,634, 10,761; 160 13,835, 14,282.  20^3, 160 20,862,
+// 19,741; at 10,000 points 200 visits 11,790, 12,543.  24^3, 10,000 points, 200
+// 22,735, 21,596; 6,000 points, 250 15,847, 16,244.  12^3, 40 1082, 1108.  It
+// depends on the ray set and not on the part of it in a call, so that every split
+// of a set adds the same sums.
 int prec_points(rt_ctx c, double n_rays_total) {
   const double cells = (double)c->n_cells;
   const double segs = 3.0 / (1.0 / c->nx + 1.0 / c->ny + 1.0 / c->nz);
-  return cells >= 4096 && n_rays_total * segs / cells <= std::min(cells / 64, 200.0) &&
+  return cells >= 2048 && n_rays_total * segs / cells <= std::min(cells / 50, 200.0) &&
                  c->n_nu <= (1 << 22)  // a grid's y ends at 65,535
              ? 4
              : 8;
