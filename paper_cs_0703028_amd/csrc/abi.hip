@@ -337,7 +337,8 @@ rt_status rt_create(rt_ctx* out, int hip_device, void* hip_stream) {
   // tally sums and ticket, segment count, kept evaluations
   const size_t counters = (2 * rt::kAccRow + 3) * sizeof(unsigned long long);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->d_tally_sums), counters);
-  if (e == hipSuccess) e = hipMemset(c->d_tally_sums, 0, counters);
+  // on the handle's stream, which may be one that the null stream does not wait for
+  if (e == hipSuccess) e = hipMemsetAsync(c->d_tally_sums, 0, counters, c->stream);
   c->d_segcount = c->d_tally_sums ? c->d_tally_sums + 2 * rt::kAccRow + 1 : nullptr;
   c->d_adapt_evals = c->d_tally_sums ? c->d_tally_sums + 2 * rt::kAccRow + 2 : nullptr;
   if (e != hipSuccess) {
