@@ -331,6 +331,7 @@ rt_status rt_create(rt_ctx* out, int hip_device, void* hip_stream) {
   rt_ctx c = new (std::nothrow) rt_ctx_s();
   if (!c) return fail(nullptr, RT_ENOMEM, "rt_create: out of host memory");
   c->device = hip_device;
+  c->cus = prop.multiProcessorCount;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   e = hipSetDevice(hip_device);
   if (e == hipSuccess) e = scratch_address(hip_device, n, &c->noalloc_scratch);

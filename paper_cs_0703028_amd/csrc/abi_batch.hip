@@ -109,7 +109,7 @@ bool halves_pay(rt_ctx c, int n_cases, const rt_case* cases, const rt_batch_tuni
   }
   const double sum_s = c->line_evals_per_cell * (double)cells * 1e-13, march_s = updates * 1e-12;
   const int64_t half_tiles = cells / dev::kKappaCells * (t.chunk_points / 2 / dev::kKappaTilePoints);
-  return c->n_nu > t.chunk_points && half_tiles >= 8 * 256 &&
+  return c->n_nu > t.chunk_points && half_tiles >= 8 * c->cus &&
          std::min(sum_s, march_s) >= std::max(sum_s, march_s) / 16;
 }
 

@@ -572,10 +572,11 @@ hipError_t launch_batch(rt_ctx c, const BatchPlan& pl, hipStream_t s) {
       const dim3 mg((unsigned)march_blocks,
                     (unsigned)plain_chunks(std::min<int64_t>(cp, c->n_nu - t.col0)));
       // six wavefronts per SIMD where the rows a part of the chunk reads exceed
-      // the 32 MB of the L2s, for which fewer then compete (3 cases of 16^3 to
-      // 32^3 cells, 20,000 rays, per launch: 13.4 ms, with eight 14.2; 4 cases
-      // of 11^3 to 21^3, 60,000 rays: 23.7, 23.0; fewer than six lose where the
-      // rays are dense)
+      // the 32 MB of the L2s, for which fewer then compete (a batch's launch,
+      // six and eight: 3 cases of 16^3 to 32^3 cells, 20,000 rays or twice that
+      // 27.9 ms, 32.0; 6 such cases, 32,768 rays 82.7, 90.6; 4 cases of 11^3 to
+      // 21^3, 60,000 rays a march of 23.7, 23.0; fewer than six lose where the rays
+      // are dense)
       const bool beyond = pl.max_cells * (int64_t)(kMarchPoints * sizeof(float)) > (int64_t(32) << 20);
       const unsigned pad = beyond ? 10000 : 0;
       if (pl.any_cubic) hipLaunchKernelGGL(chunk_march_kernel<true>, mg, dim3(256), pad, s, m);

@@ -693,9 +693,9 @@ __device__ void kappa_tile_far(const KappaTile& a, int j0, int64_t cell0, float*
 // blocks, and takes of a block the lines that meet it: the others would add zeros.
 //
 // Issue-bound (0.96 of the issue slots).  One span a wavefront instead of two
-// passes over the lines that miss it and leaves registers for seven wavefronts per
-// SIMD instead of five, and eight wavefronts share a stage as four of two spans
-// did.  A call with its Planck table, two spans -> one: 16^3 cells, 20,000 points,
+// passes over the lines that miss it and leaves room for six wavefronts per
+// SIMD (three blocks, each two on every SIMD) instead of five, and eight wavefronts
+// share a stage as four of two spans did.  A call with its Planck table, two spans -> one: 16^3 cells, 20,000 points,
 // 5,000 lines 2.81 -> 2.73 ms; 12^3 cells, 12,000 points, 78,000 lines in windows
 // of 200 points 9.67 -> 6.17 ms, 3,000 lines in windows of 1000 points 0.82 ->
 // 0.77 ms; 5 x 6 x 7 cells, 3,037 points, 760 lines 0.096 -> 0.070 ms.  16^3 cells

@@ -469,7 +469,8 @@ static hipError_t launch_sum(KappaArgs a, int64_t groups, int64_t walls, hipStre
 
 // The plain line sum of a.n_tiles tiles of kKappaTilePoints points for
 // `groups` groups of cells, or of twice as many tiles of half the points, with
-// the same values bit for bit.  Half tiles have six wavefronts a SIMD instead
+// the same values bit for bit (of whole sums: a tile's shares, a.parts > 1, are cut
+// from the lines that meet the tile).  Half tiles have six wavefronts a SIMD instead
 // of five and a tail half as long, and form a line's parameters and a span's
 // interpolation from its far nodes in more blocks.  They win (whole against
 // half tiles, microseconds):
@@ -487,11 +488,11 @@ static hipError_t launch_sum(KappaArgs a, int64_t groups, int64_t walls, hipStre
 //   3672, 4155.
 // With a walls' row (a.wall.out) its blocks follow.  Tables of more blocks than a
 // launch holds (137 GB in half tiles) take several.
-static hipError_t launch_plain(KappaArgs a, int64_t groups, hipStream_t s) {
+static hipError_t launch_plain(rt_ctx c, KappaArgs a, int64_t groups, hipStream_t s) {
   const int64_t blocks = groups * a.n_tiles * a.parts;
   const int64_t walls = a.wall.out ? a.wall.ld / kKappaThreads : 0;
   const double lines_per_point = (double)a.t.L.n / ((double)a.t.n_nu + 2.0 * a.t.K);
-  if (blocks < 6 * 256 || a.t.K <= 256 || (a.t.K <= 512 && lines_per_point >= 0.9)) {
+  if (blocks < 6 * c->cus || a.t.K <= 256 || (a.t.K <= 512 && lines_per_point >= 0.9)) {
     a.n_tiles *= 2;
     a.tile_begin *= 2;
     return launch_sum<kPlainSum, 1>(a, groups, walls, s);
@@ -516,7 +517,7 @@ hipError_t launch_kappa(rt_ctx c, bool compensated) {
   a.tile_begin = 0;
   const int64_t groups = (c->n_cells + kKappaCells - 1) / kKappaCells;
   auto launch = [&]() {
-    if (!compensated) return launch_plain(a, groups, c->stream);
+    if (!compensated) return launch_plain(c, a, groups, c->stream);
     // the precision form: FP32 line parameters
     return launch_sum<kPrecSum, kKappaPoints>(a, groups, 0, c->stream);
   };
@@ -546,7 +547,7 @@ hipError_t launch_kappa_tiles(rt_ctx c, const KappaTile& t, int64_t n_cell_group
   a.tile_begin = tile_begin;
   a.parts = parts < 1 ? 1 : parts;
   a.part_stride = part_stride;
-  if (!comp) return launch_plain(a, n_cell_groups, s);
+  if (!comp) return launch_plain(c, a, n_cell_groups, s);
   // the compensated sum has its own tiles of 256 points
   a.n_tiles *= kKappaPoints;
   a.tile_begin *= kKappaPoints;

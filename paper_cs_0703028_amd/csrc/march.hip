@@ -400,7 +400,9 @@ hipError_t launch_march(rt_ctx c, const RayScratch& s, int64_t count, double wei
   const int64_t n_chunks = march_chunks(c->n_nu, prec_q);
   // x: at most 2^21 rays a batch, 2^19 blocks; y: n_nu < 2^24 points, 2^15 chunks
   const dim3 g((unsigned)(8 * a.ray_blocks_x), (unsigned)n_chunks), t(256);
-  // seven wavefronts per SIMD instead of eight: 32^3 workload 498 -> 496 ms
+  // Plain form: seven wavefronts per SIMD.  32^3 cells, 50,000 points, eight, seven
+  // and six: 2^18 rays 168, 155, 145 ms, 2^20 500, 502, 510; 24^3, 20,000 points,
+  // 32,768 rays 8.23, 7.94, 7.63
   const unsigned pad = 6000;
   if (prec_q == 4) {
     if (exit_dev) hipLaunchKernelGGL((march_prec_kernel<true, 4>), g, t, 0, c->stream, a);

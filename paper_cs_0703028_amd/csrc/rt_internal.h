@@ -164,6 +164,7 @@ struct Surrogate;
 
 struct rt_ctx_s {
   int device = 0;
+  int cus = 256;  // compute units of the device
   hipStream_t stream = nullptr;
   std::string err;
 
