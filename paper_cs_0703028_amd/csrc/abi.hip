@@ -284,13 +284,14 @@ rt_status ensure_batch(rt_ctx c, int64_t need) {
   dev_free(c->d_counts);
   dev_free(c->d_keys);
   dev_free(c->d_perm);
+  c->batch_rays = 0;  // until every array is there
   c->max_segs = max_segs;
-  c->batch_rays = want;
   RT_HIP(c, dev_alloc(&c->d_segs, (size_t)want * max_segs));
   RT_HIP(c, dev_alloc(&c->d_counts, (size_t)want));
   RT_HIP(c, dev_alloc(&c->d_keys, (size_t)want));
   RT_HIP(c, dev_alloc(&c->d_perm, (size_t)want));
   if (!c->d_hist) RT_HIP(c, dev_alloc(&c->d_hist, (size_t)rt::kOrderBuckets));
+  c->batch_rays = want;
   return RT_OK;
 }
 
@@ -1065,6 +1066,7 @@ rt_status rt_trace_explicit(rt_ctx c, int n_rays, const int64_t* O, const int64_
     if (rt_status s = ensure_cells(c)) return s;
   if (c->explicit_cap < n_rays) {
     dev_free(c->d_rays_explicit);
+    c->explicit_cap = 0;
     RT_HIP(c, dev_alloc(&c->d_rays_explicit, (size_t)n_rays * 6));
     c->explicit_cap = n_rays;
   }
@@ -1075,6 +1077,7 @@ rt_status rt_trace_explicit(rt_ctx c, int n_rays, const int64_t* O, const int64_
     const int64_t need = (int64_t)n_rays * c->ld;
     if (c->exit_cap < need) {
       dev_free(c->d_exit);
+      c->exit_cap = 0;
       RT_HIP(c, dev_alloc(&c->d_exit, (size_t)need));
       c->exit_cap = need;
     }
@@ -1154,6 +1157,7 @@ rt_status rt_debug_segments(rt_ctx c, uint64_t seed, uint64_t ray_begin, uint64_
   if (rt_status s = ensure_batch(c, (int64_t)count)) return s;
   if (c->explicit_cap < c->batch_rays) {
     dev_free(c->d_rays_explicit);
+    c->explicit_cap = 0;
     RT_HIP(c, dev_alloc(&c->d_rays_explicit, (size_t)c->batch_rays * 6));
     c->explicit_cap = c->batch_rays;
   }
