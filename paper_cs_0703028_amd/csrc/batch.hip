@@ -93,10 +93,10 @@ __device__ __forceinline__ bool wait_count(const unsigned* p, unsigned target, u
 }
 
 // Five wavefronts per SIMD (at most 102 VGPRs): the march items wait on memory
-// and need the wavefronts to hide it.  At five, 59 VGPRs of the combined code
+// and need the wavefronts to hide it.  At five, 61 VGPRs of the combined code
 // paths go to scratch, which costs less than the wavefronts gain (64 cases of
 // 16^3 to 48^3 cells, five blocks per CU: 4.51 s at three, 4.12 s at four, 3.99 s
-// at five).
+// at five; with the march's radiances updated in place 3.84 s).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void batch_kernel(BatchArgs a) {
   // line-sum tiles stage line records here; march items stage their
   // per-segment partial sums (4 wavefronts) in the same memory

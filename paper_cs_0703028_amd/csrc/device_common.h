@@ -1634,16 +1634,16 @@ __device__ __forceinline__ void planck_lane(const PlanckLane& p, double th, floa
 //
 // Issue-bound where rays are dense: a point takes its multiply, the
 // exponential, a, B, I - B, the update, two sums and half a maximum, 8.5
-// instructions, and a segment 24 more (Planck cubic, test, staging, flush, the
+// instructions, and a segment 26 more (Planck cubic, test, staging, flush, the
 // ray's ends), shared by the lane's kPlainQ points.  24 points per lane spread
 // those best but put 6 KB of each crossed cell's row in flight per wavefront, a
-// whole XCD's L2.  32^3 cells, 50,000 points, 2^20 rays: 10.5 instructions per
-// update and 2.6 TB past L2 in 512 ms at 12 points (at 24 points with general
-// Planck values, the result copied around the loop, it was 11.6 instructions,
-// 3.45 TB and 562 ms).  Where rays are sparse
-// (about 100 per cell) each row is read from beyond L2 for nearly every
-// crossing, at 7 TB/s, and fewer wavefronts in flight are better: the launches
-// pad the block's LDS to hold 6 or 7 per SIMD.
+// whole XCD's L2.  32^3 cells, 50,000 points, 2^20 rays: 10.7 instructions per
+// update and 2.6 TB past L2 in 505 to 512 ms at 12 points (at 24 points with
+// general Planck values, the result copied around the loop, it was 11.6
+// instructions, 3.45 TB and 562 ms).  Where rays are sparse (about 100 per cell)
+// each row is read from beyond L2 for nearly every crossing, at 7 TB/s, and fewer
+// wavefronts in flight are better: the launches pad the block's LDS to hold 6 or 7
+// per SIMD.
 //
 // Both the sums and the update of I take a and not e^-tau: sums of I e^-tau and
 // (I - B) e^-tau + B save an instruction a point and lose a thin cell's a, and
